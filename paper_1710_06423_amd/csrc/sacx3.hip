@@ -800,9 +800,9 @@ __global__ __launch_bounds__(TX *TY, 1) void k3_stage(Stage3Args a) {
                 m2 = fmax(m2, lds.red[2][k]); bb = fmax(bb, lds.red[3][k]);
             }
             const int ns = sc->cur ^ 1;
-            atomicMax(&sc->cacc[ns][0], (unsigned long long)__double_as_longlong(m0));
-            atomicMax(&sc->cacc[ns][1], (unsigned long long)__double_as_longlong(m1));
-            atomicMax(&sc->cacc[ns][2], (unsigned long long)__double_as_longlong(m2));
+            sacx::raise_max(&sc->cacc[ns][0], m0);
+            sacx::raise_max(&sc->cacc[ns][1], m1);
+            sacx::raise_max(&sc->cacc[ns][2], m2);
             if (bb > 0.0) atomicOr(&sc->nonphys, 1);
         }
     }
@@ -943,9 +943,9 @@ __global__ void k3_wavespeed(const double *U, int64_t fs, Layout3 L, double gamm
         for (int k = 0; k < (int)(blockDim.x >> 6); ++k) {
             m0 = fmax(m0, red[0][k]); m1 = fmax(m1, red[1][k]); m2 = fmax(m2, red[2][k]); bb = fmax(bb, red[3][k]);
         }
-        atomicMax(&sc->cacc[slot][0], (unsigned long long)__double_as_longlong(m0));
-        atomicMax(&sc->cacc[slot][1], (unsigned long long)__double_as_longlong(m1));
-        atomicMax(&sc->cacc[slot][2], (unsigned long long)__double_as_longlong(m2));
+        sacx::raise_max(&sc->cacc[slot][0], m0);
+        sacx::raise_max(&sc->cacc[slot][1], m1);
+        sacx::raise_max(&sc->cacc[slot][2], m2);
         if (bb > 0.0) atomicOr(&sc->nonphys, 1);
     }
 }

@@ -57,6 +57,19 @@ struct DevScalars {
     int pad;
 };
 
+// Raise a wave-speed accumulator (the IEEE bits of a non-negative double) to
+// v.  Atomics on one word are carried out one after the other, about 11 ns
+// each: 4096 blocks x 4 waves x 2 maxima of an initial state took 380 us at
+// every grid size.  Each block sends one maximum; in a launch of more than
+// 256 blocks only one above what the accumulator already holds (a read that
+// lags behind sends one too many).  With fewer blocks the read's latency,
+// about 1 us at the end of every block, costs more than the atomics it saves.
+__device__ __forceinline__ void raise_max(unsigned long long *p, double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    if (gridDim.x * gridDim.y <= 256 || b > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(p, b);
+}
+
 // grid constants of the scheme, computed once on the host in FP64
 // (reciprocals of grid spacings, closure constants, compression-term scales)
 struct SchemeConsts {

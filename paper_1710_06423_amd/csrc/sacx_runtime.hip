@@ -391,6 +391,7 @@ __global__ void k_export(FPtr<real> Sx, MPtr<T> dst, uint32_t mask, Layout L, in
 // wave speeds of a state into accumulator slot `slot`
 template <typename real>
 __global__ void k_wavespeed(FPtr<real> U, FPtr<real> B, int bg, Layout L, double gamma, DevScalars *sc, int slot) {
+    __shared__ double red[2][4];
     double cx = 0.0, cy = 0.0;
     int bad = 0;
     const real gm1 = (real)(gamma - 1.0), half = (real)0.5, gam = (real)gamma;
@@ -428,9 +429,15 @@ __global__ void k_wavespeed(FPtr<real> U, FPtr<real> B, int bg, Layout L, double
         bad |= __shfl_xor(bad, off);
     }
     if ((threadIdx.x & 63) == 0) {
-        atomicMax(&sc->cacc[slot][0], (unsigned long long)__double_as_longlong(cx));
-        atomicMax(&sc->cacc[slot][1], (unsigned long long)__double_as_longlong(cy));
+        red[0][threadIdx.x >> 6] = cx;
+        red[1][threadIdx.x >> 6] = cy;
         if (bad) atomicOr(&sc->nonphys, 1);
+    }
+    __syncthreads();
+    // one maximum of each direction per block of 256 threads
+    if (threadIdx.x < 2) {
+        const double *r = red[threadIdx.x];
+        raise_max(&sc->cacc[slot][threadIdx.x], fmax(fmax(r[0], r[1]), fmax(r[2], r[3])));
     }
 }
 
@@ -746,7 +753,7 @@ int stage(sacx_ctx *c, int s, void *const *S, void *const *U, void *const *A, vo
 int wavespeed_into(sacx_ctx *c, int slot) {
     const int64_t n = (int64_t)c->L.nx * c->L.ny;
     const int T = 256;
-    int blocks = (int)std::min<int64_t>((n + T - 1) / T, 4096);
+    int blocks = (int)std::min<int64_t>((n + T - 1) / T, 2048);
     if (c->grid.precision == SACX_FP64)
         hipLaunchKernelGGL(k_wavespeed<double>, dim3(blocks), dim3(T), 0, c->stream, fptr<double>(c->U, NF),
                            fptr<double>(c->grid.background_on ? c->BG : c->U, NBG), c->grid.background_on, c->L,

@@ -629,8 +629,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
             for (int k = 0; k < NT / 64; ++k) { mx_ = fmax(mx_, red[0][k]); my_ = fmax(my_, red[1][k]); bb = fmax(bb, red[2][k]); }
             DevScalars *scw = a.sc;
             const int nslot = scw->cur ^ 1;
-            atomicMax(&scw->cacc[nslot][0], (unsigned long long)__double_as_longlong(mx_));
-            atomicMax(&scw->cacc[nslot][1], (unsigned long long)__double_as_longlong(my_));
+            raise_max(&scw->cacc[nslot][0], mx_);
+            raise_max(&scw->cacc[nslot][1], my_);
             if (bb > 0.0) atomicOr(&scw->nonphys, 1);
         }
     }
@@ -829,8 +829,8 @@ __device__ __forceinline__ void stage_tile_1d(const StageArgs<real> &a, int tile
             for (int k = 0; k < NT / 64; ++k) { mx_ = fmax(mx_, red[0][k]); my_ = fmax(my_, red[1][k]); bb = fmax(bb, red[2][k]); }
             DevScalars *scw = a.sc;
             const int nslot = scw->cur ^ 1;
-            atomicMax(&scw->cacc[nslot][0], (unsigned long long)__double_as_longlong(mx_));
-            atomicMax(&scw->cacc[nslot][1], (unsigned long long)__double_as_longlong(my_));
+            raise_max(&scw->cacc[nslot][0], mx_);
+            raise_max(&scw->cacc[nslot][1], my_);
             if (bb > 0.0) atomicOr(&scw->nonphys, 1);
         }
     }

@@ -321,6 +321,29 @@ __global__ void k_fill_y(FPtr<real> S, int nf, Layout L, int periodic, int skip,
     }
 }
 
+// every ghost cell of both directions in one launch, each read straight from
+// the cell it copies (corners included); for contexts whose every side is read through its map
+template <typename real>
+__global__ void k_fill_ghosts(FPtr<real> S, Layout L, SideMap mx, SideMap my) {
+    const int W = L.nx + 2 * G;
+    const int64_t ny_part = (int64_t)2 * G * W, n = ny_part + (int64_t)2 * G * L.ny;
+    const int f = blockIdx.y;
+    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
+        int i, j;
+        if (k < ny_part) {
+            const int g = (int)(k / W);
+            i = (int)(k % W) - G;
+            j = g < G ? g - G : L.ny + g - G;
+        } else {
+            const int64_t k2 = k - ny_part;
+            const int g = (int)(k2 % (2 * G));
+            j = (int)(k2 / (2 * G));
+            i = g < G ? g - G : L.nx + g - G;
+        }
+        S.p[f][eidx(L, i, j)] = S.p[f][eidx(L, mx.at(i), my.at(j))];
+    }
+}
+
 // caller arrays <-> internal storage
 template <typename T>
 struct CPtr {
@@ -449,14 +472,21 @@ __global__ void k_reset_scalars(DevScalars *sc, double t0) {
     sc->cacc[0][0] = sc->cacc[0][1] = sc->cacc[1][0] = sc->cacc[1][1] = 0ull;
     sc->last_cx = sc->last_cy = sc->last_cmax = 0.0;
     sc->steps = 0;
+    sc->steps0 = 0;
     sc->cur = 0;
     sc->active = 1;
     sc->nonphys = 0;
     sc->pad = 0;
 }
 
-// dt for the step about to start (CFL time step with the end-time clamp)
-__global__ void k_step_begin(DevScalars *sc, double t_end, StepConsts k) { step_begin_dev(sc, t_end, k); }
+// dt for the step about to start (CFL time step with the end-time clamp);
+// `prev`: the step before it, of the same call, ends first (one launch for
+// both); otherwise the call begins here
+__global__ void k_step_begin(DevScalars *sc, double t_end, StepConsts k, int prev) {
+    if (prev) step_end_dev(sc);
+    else sc->steps0 = sc->steps;
+    step_begin_dev(sc, t_end, k);
+}
 
 __global__ void k_step_end(DevScalars *sc) { step_end_dev(sc); }
 
@@ -584,17 +614,54 @@ void fill_dir_t(sacx_ctx *c, void *const *fields, int nf, bool gated, int dir) {
     }
 }
 
-template <typename real>
-int fill_halo_t(sacx_ctx *c, void *const *fields, int nf, bool gated) {
-    fill_dir_t<real>(c, fields, nf, gated, 0);
-    fill_dir_t<real>(c, fields, nf, gated, 1);
+bool has_exchange(const sacx_ctx *c) {
+    for (int s = 0; s < 4; ++s)
+        if (c->bc[s] == SACX_EXCHANGE) return true;
+    return false;
+}
+
+// a periodic direction with fewer than G cells, whose ghosts are filled
+// before the stages (one read of its side map reaches one image)
+bool narrow(const sacx_ctx *c, int dir) {
+    return c->bc[2 * dir] == SACX_PERIODIC && (dir == 0 ? c->L.nx : c->L.ny) < G;
+}
+
+// ghosts of one direction of a stage input (or of the background) where that
+// direction is narrow; x before y, as in fill_dir_t
+int fill_narrow(sacx_ctx *c, void *const *fields, int nf, bool gated, int dir) {
+    if (!narrow(c, dir)) return SACX_OK;
+    // a tube's one-row stage reads nothing above or below its row
+    if (dir == 1 && c->L.ny == 1 && c->L.nx >= 2 && !c->grid.background_on) return SACX_OK;
+    if (c->grid.precision == SACX_FP64) fill_dir_t<double>(c, fields, nf, gated, dir);
+    else fill_dir_t<float>(c, fields, nf, gated, dir);
     HIPCHK(hipGetLastError());
     return SACX_OK;
 }
 
-int fill_halo(sacx_ctx *c, void *const *fields, int nf, bool gated) {
-    return c->grid.precision == SACX_FP64 ? fill_halo_t<double>(c, fields, nf, gated)
-                                          : fill_halo_t<float>(c, fields, nf, gated);
+int fill_narrow(sacx_ctx *c, void *const *fields, int nf, bool gated) {
+    const int rc = fill_narrow(c, fields, nf, gated, 0);
+    return rc ? rc : fill_narrow(c, fields, nf, gated, 1);
+}
+
+// the ghost cells of the state U (the stage kernels do not need them: the
+// kernels of the learned coefficient and sacx_halo_pack's corners read them)
+template <typename real>
+int fill_halo_t(sacx_ctx *c) {
+    if (has_exchange(c) || narrow(c, 0) || narrow(c, 1)) {
+        fill_dir_t<real>(c, c->U, NF, false, 0);
+        fill_dir_t<real>(c, c->U, NF, false, 1);
+    } else {
+        const int64_t n = (int64_t)2 * G * (c->L.nx + 2 * G + c->L.ny);
+        hipLaunchKernelGGL(k_fill_ghosts<real>, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096), NF), dim3(256),
+                           0, c->stream, fptr<real>(c->U, NF), c->L, side_map(c->L.nx, c->bc[0], c->bc[1]),
+                           side_map(c->L.ny, c->bc[2], c->bc[3]));
+    }
+    HIPCHK(hipGetLastError());
+    return SACX_OK;
+}
+
+int fill_halo(sacx_ctx *c) {
+    return c->grid.precision == SACX_FP64 ? fill_halo_t<double>(c) : fill_halo_t<float>(c);
 }
 
 // the state the next stage differences: U between steps, then w1, w2, w3
@@ -605,12 +672,6 @@ void *const *stage_input(sacx_ctx *c) {
         case 3: return c->B1;
         default: return c->U;
     }
-}
-
-bool has_exchange(const sacx_ctx *c) {
-    for (int s = 0; s < 4; ++s)
-        if (c->bc[s] == SACX_EXCHANGE) return true;
-    return false;
 }
 
 // grid spacing and the scheme constants derived from it, in the same FP64
@@ -655,6 +716,8 @@ StageArgs<real> stage_args(sacx_ctx *c) {
     StageArgs<real> a;
     std::memset(&a, 0, sizeof(a));
     a.L = c->L;
+    a.mx = side_map(c->L.nx, c->bc[0], c->bc[1]);
+    a.my = side_map(c->L.ny, c->bc[2], c->bc[3]);
     a.ty = c->ty;
     a.nt = c->nt;
     a.split = c->split;
@@ -687,7 +750,7 @@ RatioArgs<real> ratio_args(sacx_ctx *c) {
 // surrogate refresh at a step start: predict the ratio planes from U (unless
 // the caller supplies them) and check them against the plain ratios of U
 int sur_refresh(sacx_ctx *c) {
-    int rc = fill_halo(c, c->U, NF, false);
+    int rc = fill_halo(c);
     if (rc) return rc;
     const int nx = c->L.nx, ny = c->L.ny;
     InputNorm nm;
@@ -740,9 +803,9 @@ int run_stage(sacx_ctx *c, int stage, void *const *S, void *const *U, void *cons
 }
 
 int stage(sacx_ctx *c, int s, void *const *S, void *const *U, void *const *A, void *const *o1, void *const *o2) {
-    {
+    if (narrow(c, 0) || narrow(c, 1)) {
         ProfScope ps(c, 4);
-        int rc = fill_halo(c, S, NF, true);
+        int rc = fill_narrow(c, S, NF, true);
         if (rc) return rc;
     }
     ProfScope ps(c, s - 1);
@@ -990,10 +1053,10 @@ int sacx_set_boundaries(sacx_ctx *ctx, const int32_t bc[4]) {
     for (int s = 0; s < 4; ++s) ctx->bc[s] = bc[s];
     ctx->gen += 1;
     if (ctx->initialized && ctx->grid.background_on) {
-        // the static background's halos follow the new boundaries
+        // the static background's ghosts follow the new boundaries
         DeviceGuard dg(ctx->device);
         if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
-        return fill_halo(ctx, ctx->BG, NBG, false);
+        return fill_narrow(ctx, ctx->BG, NBG, false);
     }
     return SACX_OK;
 }
@@ -1003,7 +1066,7 @@ int sacx_set_boundaries(sacx_ctx *ctx, const int32_t bc[4]) {
 static int finish_init(sacx_ctx *ctx, double t0) {
     HIPCHK(hipGetLastError());
     hipLaunchKernelGGL(k_reset_scalars, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t0);
-    int rc = fill_halo(ctx, ctx->U, NF, false);
+    int rc = fill_halo(ctx);
     if (rc) return rc;
     rc = wavespeed_into(ctx, 0);
     if (rc) return rc;
@@ -1056,7 +1119,7 @@ int sacx_init_state(sacx_ctx *ctx, const void *const *d_fields, const void *cons
     import(ctx->U, d_fields, NF);
     if (ctx->grid.background_on) {
         import(ctx->BG, d_bg, NBG);
-        int rc = fill_halo(ctx, ctx->BG, NBG, false);
+        int rc = fill_narrow(ctx, ctx->BG, NBG, false);
         if (rc) return rc;
     }
     return finish_init(ctx, t0);
@@ -1107,12 +1170,7 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
     if (ctx->stage_next) return fail(SACX_ESTATE, "a step begun with sacx_stage is in progress");
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
-    long long steps0 = 0;
     const bool sync = steps_done || t_now;
-    if (sync) {
-        HIPCHK(hipMemcpyAsync(&steps0, &ctx->sc->steps, sizeof(steps0), hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-    }
     const StepConsts sk = step_consts(ctx);
     // A synchronising call enqueues in chunks and stops early once the device
     // reports that stepping ended (end time reached or non-physical state).
@@ -1122,7 +1180,7 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
         for (int n = n0; n < n1; ++n) {
             {
                 ProfScope ps(ctx, 5);
-                hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t_end, sk);
+                hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t_end, sk, n > 0);
             }
             int rc;
             if (ctx->sur_on) {
@@ -1136,10 +1194,6 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
             if ((rc = stage(ctx, 2, ctx->B1, ctx->U, nullptr, ctx->B2, ctx->A))) return rc;
             if ((rc = stage(ctx, 3, ctx->B2, ctx->U, nullptr, ctx->B1, nullptr))) return rc;
             if ((rc = stage(ctx, 4, ctx->B1, nullptr, ctx->A, ctx->U, nullptr))) return rc;
-            {
-                ProfScope ps(ctx, 5);
-                hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, ctx->stream, ctx->sc);
-            }
             HIPCHK(hipGetLastError());
         }
         if (sync && n1 < nsteps) {
@@ -1149,11 +1203,16 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
             if (!act) break;
         }
     }
+    if (nsteps > 0) {
+        ProfScope ps(ctx, 5);
+        hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, ctx->stream, ctx->sc);
+        HIPCHK(hipGetLastError());
+    }
     if (sync) {
         DevScalars h;
         HIPCHK(hipMemcpyAsync(&h, ctx->sc, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
         HIPCHK(hipStreamSynchronize(ctx->stream));
-        if (steps_done) *steps_done = (int32_t)(h.steps - steps0);
+        if (steps_done) *steps_done = nsteps > 0 ? (int32_t)(h.steps - h.steps0) : 0;
         if (t_now) *t_now = h.t;
         if (h.nonphys) return fail(SACX_ENONPHYS, "non-physical state after %lld steps", h.steps);
     }
@@ -1320,7 +1379,7 @@ int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int3
             hipLaunchKernelGGL(k_step_begin_global, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, c_max[0], c_max[1],
                                (const double *)nullptr, step_consts(ctx));
         else
-            hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, 0.0, step_consts(ctx));
+            hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, 0.0, step_consts(ctx), 0);
         HIPCHK(hipGetLastError());
     }
     int rc;
@@ -1549,7 +1608,7 @@ int sacx_hd_ratio_fields(sacx_ctx *ctx, float *d_r, float *d_d1, int64_t pitch) 
     if (pitch < ctx->L.nx) return fail(SACX_EINVAL, "pitch must be >= nx");
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
-    int rc = fill_halo(ctx, ctx->U, NF, false);
+    int rc = fill_halo(ctx);
     if (rc) return rc;
     HIPCHK(ctx->grid.precision == SACX_FP64
                ? launch_ratio_fields<double>(ratio_args<double>(ctx), d_r, d_d1, pitch, ctx->stream)
@@ -2154,12 +2213,14 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
         for (int i = 0; i < n; ++i)
             if ((rc = sacx_wave_speeds_max((*d->subs)[i], d->cmax))) return rc;
         for (int s = 0; s < 4; ++s) {
-            for (int i = 0; i < n; ++i)
-                if ((rc = sacx_fill_boundaries((*d->subs)[i], 0))) return rc;
-            if ((rc = domain_exchange(d, 0))) return rc;
-            for (int i = 0; i < n; ++i)
-                if ((rc = sacx_fill_boundaries((*d->subs)[i], 1))) return rc;
-            if ((rc = domain_exchange(d, 1))) return rc;
+            // (periodic and open sides need no fill, narrow directions apart)
+            for (int dir = 0; dir < 2; ++dir) {
+                for (int i = 0; i < n; ++i) {
+                    sacx_ctx *c = (*d->subs)[i];
+                    if ((rc = fill_narrow(c, stage_input(c), NF, false, dir))) return rc;
+                }
+                if ((rc = domain_exchange(d, dir))) return rc;
+            }
             for (int i = 0; i < n; ++i)
                 if ((rc = sacx_stage((*d->subs)[i], d->cmax, 1, nullptr))) return rc;
         }

@@ -224,7 +224,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
     auto &sh_gy = lds.gy;
     auto &sh_hx = lds.hx;
 
-    const int64_t colofs = (int64_t)L.xoff + (colv ? c : L.nx + G - 1);
+    // where this column and a row (c, r from -G) are stored
+    const int64_t colofs = (int64_t)L.xoff + a.mx.at(colv ? c : L.nx + G - 1);
+    auto rowofs = [&](int row) { return (int64_t)(a.my.at(row) + G) * L.pitch; };
     const int rbeg = y0 - G, rend = y1 - 1 + G;
     // surrogate: this column's periodic image in the ratio planes, and its
     // column of check tiles
@@ -272,7 +274,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
     // prefetch of the next state row
     Row6<real> nxt;
     {
-        const int64_t ro = colofs + (int64_t)(rbeg + G) * L.pitch;
+        const int64_t ro = colofs + rowofs(rbeg);
 #pragma unroll
         for (int f = 0; f < NF; ++f) nxt.v[f] = a.S[0][ro + f * fs];
     }
@@ -289,7 +291,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
     }
 
     for (int r = rbeg; r <= rend; ++r) {
-        const int64_t ro = colofs + (int64_t)(r + G) * L.pitch;
+        const int64_t ro = BG ? colofs + rowofs(r) : 0;
         // surrogate ratios of this iteration's faces: x faces of row r-1,
         // y faces (r-3)+1/2, issued before the iteration's other loads
         // (a wave none of whose lanes is in a kept tile takes the plain path)
@@ -311,7 +313,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
         // for an exact count of the loads in flight: past the last row the
         // next-row load re-reads that row, unused)
         if (SUR || r < rend) {
-            const int64_t rn = colofs + (int64_t)((SUR ? min(r + 1, rend) : r + 1) + G) * L.pitch;
+            const int64_t rn = colofs + rowofs(SUR ? min(r + 1, rend) : r + 1);
 #pragma unroll
             for (int f = 0; f < NF; ++f) nxt.v[f] = a.S[0][rn + f * fs];
         }
@@ -417,7 +419,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
             bgn0 = (eight * (sh_q[slot][QVX][tp1] - sh_q[slot][QVX][tm1]) - (sh_q[slot][QVX][tp2] - sh_q[slot][QVX][tm2])) * i12dx;
             bgn1 = (eight * (sh_q[slot][QVY][tp1] - sh_q[slot][QVY][tm1]) - (sh_q[slot][QVY][tp2] - sh_q[slot][QVY][tm2])) * i12dx;
             // e~ of row r-2 gets -p_tb div v + sum_kl B_bk B_bl d_k v_l
-            const int64_t r2 = colofs + (int64_t)((r - 2 < -G ? -G : r - 2) + G) * L.pitch;
+            const int64_t r2 = colofs + rowofs(r - 2 < -G ? -G : r - 2);
             const real eb2 = a.BG[0][r2 + 1 * fs], bxb2 = a.BG[0][r2 + 2 * fs], byb2 = a.BG[0][r2 + 3 * fs];
             const real dxvx = bgx[0][0], dxvy = bgx[0][1];
             const real dyvx = (eight * (qw[QVX][4] - qw[QVX][2]) - (qw[QVX][5] - qw[QVX][1])) * i12dy;
@@ -671,7 +673,8 @@ __device__ __forceinline__ void stage_tile_1d(const StageArgs<real> &a, int tile
     auto &sh_s = lds.s;
     auto &sh_hx = lds.hx;
     // row 0 of the subdomain (interior row)
-    const int64_t ro = (int64_t)L.xoff + (colv ? c : L.nx + G - 1) + (int64_t)G * L.pitch;
+    const int64_t ro = (int64_t)L.xoff + a.mx.at(colv ? c : L.nx + G - 1) +
+                       (int64_t)G * L.pitch;
     const int64_t oo = (int64_t)L.xoff + c + (int64_t)G * L.pitch;
     Row6<real> pS, pU;
     if (outcol) {

@@ -60,7 +60,12 @@ struct SplitCommon {
     real gamma, gm1, igm1, i12dx, i12dy, idx, idy, i2dx, i2dy, third, gx, gy;
     int t, c, y0, rbeg, rend, tm1, tm2, tp1, tp2, tp3;
     bool outcol, cross, grav;
-    int64_t colofs;
+    int64_t colofs;                // where this column is stored
+    int pitch;
+    SideMap my;
+
+    // where row r (from -G) is stored
+    __device__ __forceinline__ int64_t rowofs(int r) const { return (int64_t)(my.at(r) + G) * pitch; }
 
     __device__ __forceinline__ SplitCommon(const StageArgs<real> &a, int tx_, int ty_, int t_) {
         constexpr int TX = NC - 2 * G;
@@ -90,7 +95,9 @@ struct SplitCommon {
         tp2 = t + 2 < NC ? t + 2 : NC - 1;
         tp3 = t + 3 < NC ? t + 3 : NC - 1;
         const bool colv = c < L.nx + G;
-        colofs = (int64_t)L.xoff + (colv ? c : L.nx + G - 1);
+        colofs = (int64_t)L.xoff + a.mx.at(colv ? c : L.nx + G - 1);
+        pitch = L.pitch;
+        my = a.my;
     }
 };
 
@@ -164,7 +171,7 @@ __device__ __forceinline__ void split_x(const StageArgs<real> &a, const SplitCom
     Row6<real> n1, n2;
     real g1[NBG], g2[NBG];
     {
-        const int64_t ro = m.colofs + (int64_t)(m.rbeg + G) * L.pitch;
+        const int64_t ro = m.colofs + m.rowofs(m.rbeg);
 #pragma unroll
         for (int f = 0; f < NF; ++f) n1.v[f] = a.S[0][ro + f * fs];
         if (BG) {
@@ -172,11 +179,12 @@ __device__ __forceinline__ void split_x(const StageArgs<real> &a, const SplitCom
             for (int f = 0; f < NBG; ++f) g1[f] = a.BG[0][ro + f * fs];
         }
         if (m.rbeg < m.rend) {
+            const int64_t ro1 = m.colofs + m.rowofs(m.rbeg + 1);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) n2.v[f] = a.S[0][ro + L.pitch + f * fs];
+            for (int f = 0; f < NF; ++f) n2.v[f] = a.S[0][ro1 + f * fs];
             if (BG) {
 #pragma unroll
-                for (int f = 0; f < NBG; ++f) g2[f] = a.BG[0][ro + L.pitch + f * fs];
+                for (int f = 0; f < NBG; ++f) g2[f] = a.BG[0][ro1 + f * fs];
             }
         }
     }
@@ -225,7 +233,7 @@ __device__ __forceinline__ void split_x(const StageArgs<real> &a, const SplitCom
         // it re-reads that row, unused)
         if (SUR || r + 2 <= m.rend) {
             const int rn_row = SUR ? min(r + 2, m.rend) : r + 2;
-            const int64_t rn = m.colofs + (int64_t)(rn_row + G) * L.pitch;
+            const int64_t rn = m.colofs + m.rowofs(rn_row);
 #pragma unroll
             for (int f = 0; f < NF; ++f) n2.v[f] = a.S[0][rn + f * fs];
             if (BG) {
@@ -501,9 +509,9 @@ __device__ __forceinline__ void split_y(const StageArgs<real> &a, const SplitCom
         // zeros of the one-thread tile
         real eb = 0, bxb = 0, byb = 0, rb2 = 0, eb2 = 0, bxb2 = 0, byb2 = 0, rb3 = 0, bxb3 = 0;
         if (BG) {
-            const int64_t rr = m.colofs + (int64_t)(r + G) * L.pitch;
-            const int64_t r2 = m.colofs + (int64_t)((r - 2 < -G ? -G : r - 2) + G) * L.pitch;
-            const int64_t r3 = m.colofs + (int64_t)((r - 3 < -G ? -G : r - 3) + G) * L.pitch;
+            const int64_t rr = m.colofs + m.rowofs(r);
+            const int64_t r2 = m.colofs + m.rowofs(r - 2 < -G ? -G : r - 2);
+            const int64_t r3 = m.colofs + m.rowofs(r - 3 < -G ? -G : r - 3);
             eb = a.BG[0][rr + 1 * fs]; bxb = a.BG[0][rr + 2 * fs]; byb = a.BG[0][rr + 3 * fs];
             rb2 = a.BG[0][r2]; eb2 = a.BG[0][r2 + 1 * fs]; bxb2 = a.BG[0][r2 + 2 * fs]; byb2 = a.BG[0][r2 + 3 * fs];
             rb3 = a.BG[0][r3]; bxb3 = a.BG[0][r3 + 2 * fs];

@@ -312,10 +312,12 @@ int sacx_domain_destroy(sacx_domain *d);
  * twice as many) and `rows` output rows per
  * block strip (1..4096; each strip recomputes 6 rows of halo).  0 keeps the
  * current value.  Until rows is set, the strip height is chosen from the
- * device (compute units x resident blocks per unit): strips balanced to fit
- * one round of resident blocks when that needs at most 512 rows, else 256
- * rows (halved while there are fewer than 1024 blocks); it is chosen again
- * whenever threads or the tile kind change.  Results do not depend on the
+ * device (compute units x resident blocks per unit), and until either is set
+ * the columns too: the cheapest shape of one round of resident blocks when
+ * that needs at most 160 rows; else strips balanced to fit one round when
+ * that needs at most 512 rows, else 256 rows (halved while there are fewer
+ * than 1024 blocks).  Both are chosen again whenever threads or the tile kind
+ * change.  Setting rows alone takes 128 columns in FP64 and 256 in FP32.  Results do not depend on the
  * shape (bit-identical); only speed does.  Used by the tile autotuner. */
 int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows);
 int sacx_get_launch(const sacx_ctx *ctx, int32_t *threads, int32_t *rows);

@@ -78,7 +78,7 @@ struct sacx_ctx {
     bool initialized;
     int ty, nt;
     int split;         // FP64 hyper-diffusion tiles: two threads per column
-    bool ty_auto;      // strip height chosen by auto_rows (until set explicitly)
+    bool nt_auto, ty_auto;  // columns / strip height chosen by auto_rows (until set explicitly)
     double dx, dy;
     SchemeConsts kc;
     // profiling: event pairs recorded around launch groups, resolved at read
@@ -188,13 +188,75 @@ int rows_for_slots(const Layout &L, int nt, int64_t slots) {
     return ty;
 }
 
-// the strip height for the context's current launch settings: resident
-// blocks from the device's compute units and the kernel's occupancy
+// Time per row of a block with 1, 2, ... blocks on its compute unit, in us
+// (MI355X, the mean of the four stages, 24-row strips whose state stays in
+// the caches; the third of the first row raised by what 1024^2 shows), by kernel
+// and columns per block (64, 128, 256; 0: not
+// measured, the last value stands).
+enum { KIND_SPLIT = 0, KIND_SPLIT_BG, KIND_F64_NOHD, KIND_F32, KIND_F32_NOHD, KINDS };
+const float kRowUs[KINDS][3][8] = {
+    {{1.44f, 2.08f, 2.35f, 2.67f}, {1.66f, 2.68f}, {3.1f}},
+    {{1.69f, 2.54f, 3.02f, 3.56f}, {2.10f, 3.54f}, {4.0f}},
+    {{0.85f, 1.10f, 1.20f, 1.45f, 2.40f, 3.10f}, {1.07f, 1.60f, 3.00f}, {3.0f}},
+    {{1.67f, 1.69f, 1.70f, 1.70f, 1.95f, 2.20f, 2.36f, 2.52f}, {1.88f, 2.12f, 2.29f, 2.45f}, {1.99f, 2.56f}},
+    {{0.75f, 0.80f, 0.83f, 0.94f, 1.05f, 1.15f, 1.40f, 1.67f}, {0.86f, 0.95f, 1.20f, 1.60f}, {0.95f, 1.57f}},
+};
+
+// the smallest strip height whose blocks are at most `blocks`
+int rows_for_blocks(const Layout &L, int nt, int64_t blocks) {
+    const int64_t xt = (L.nx + nt - 2 * G - 1) / (nt - 2 * G);
+    const int64_t strips = blocks / xt;
+    return strips < 1 ? INT32_MAX : (int)((L.ny + strips - 1) / strips);
+}
+
+// The launch shape where the grid fits in one round of resident blocks: for
+// each width and each number k of blocks per compute unit, the strip height
+// that gives every unit k blocks takes about rows + 9 row times (6 warm-up
+// rows, and about 3 for the launch); the cheapest is taken.  Narrow blocks
+// and short strips pay where wide ones leave units idle: FP64 at 300 x 136
+// takes 75 us per step with 128 x 2 strips and 109 with 128 x 8 (51 blocks),
+// at 512^2 137 against 158; FP32 at 300 x 136 72 against 117, at 2048^2 397
+// against 431; 1501 x 997 without hyper-diffusion 196 against 253.  Strips
+// above 160 rows keep the default width: there the widths differ by less than
+// the spread of the figures above.
+bool shape_for_slots(const sacx_ctx *c, int cus, int *nt, int *ty) {
+    const bool fp64 = c->grid.precision == SACX_FP64;
+    const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
+    if (c->L.ny <= 8 || (fp64 && hd && !c->split)) return false;
+    const int kind = fp64 ? (hd ? (bg ? KIND_SPLIT_BG : KIND_SPLIT) : KIND_F64_NOHD) : (hd ? KIND_F32 : KIND_F32_NOHD);
+    double best = 0.0;
+    bool found = false;
+    for (int w = 0; w < (fp64 ? 2 : 3); ++w) {
+        const int cols = 64 << w;
+        int per = 0;
+        const hipError_t e = fp64 ? stage_blocks_per_cu<double>(cols, hd, bg, true, &per)
+                                  : stage_blocks_per_cu<float>(cols, hd, bg, true, &per);
+        if (e != hipSuccess) { (void)hipGetLastError(); continue; }
+        for (int k = 1; k <= std::min(per, 8); ++k) {
+            const float us = kRowUs[kind][w][k - 1];
+            if (us == 0.0f) break;
+            const int rows = rows_for_blocks(c->L, cols, (int64_t)cus * k);
+            if (rows > 160) continue;
+            const double cost = us * (rows + 9.0);
+            if (!found || cost < best) { found = true; best = cost; *nt = cols; *ty = rows; }
+        }
+    }
+    return found;
+}
+
+// the launch shape for the context's current settings: resident blocks from
+// the device's compute units and the kernel's occupancy.  Measured on MI355X:
+// larger grids are best with 128 columns in FP64 (OT 8000^2, also with a
+// background at 4000^2) and 256 in FP32.
 void auto_rows(sacx_ctx *c) {
     int cus = 0, per = 0;
     const bool fp64 = c->grid.precision == SACX_FP64;
     const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
+    if (c->nt_auto) {
+        c->nt = fp64 ? 128 : 256;
+        if (e == hipSuccess && cus >= 1 && shape_for_slots(c, cus, &c->nt, &c->ty)) return;
+    }
     if (e == hipSuccess)
         e = fp64 ? stage_blocks_per_cu<double>(c->nt, hd, bg, c->split != 0, &per)
                  : stage_blocks_per_cu<float>(c->nt, hd, bg, c->split != 0, &per);
@@ -913,11 +975,8 @@ int sacx_create(const sacx_grid *grid, const sacx_params *params, void *d_ws, si
     c->hx[1] = c->ws + P.off_hx + P.hx_bytes;
     c->hy[0] = c->ws + P.off_hy;
     c->hy[1] = c->ws + P.off_hy + P.hy_bytes;
-    // measured on MI355X: FP64 is best with 128-column blocks (OT 8000^2,
-    // also with a background at 4000^2), FP32 with 256-column blocks
-    c->nt = grid->precision == SACX_FP64 ? 128 : 256;
     c->split = 1;
-    c->ty_auto = true;
+    c->nt_auto = c->ty_auto = true;
     set_spacing(c, (grid->x1 - grid->x0) / grid->nx, (grid->y1 - grid->y0) / grid->ny);
     c->initialized = false;
     c->prof_on = false;
@@ -960,7 +1019,14 @@ int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows) {
     if (threads != 0 && threads != 64 && threads != 128 && threads != 256)
         return fail(SACX_EINVAL, "threads must be 64, 128 or 256 (got %d)", threads);
     if (rows < 0 || rows > 4096) return fail(SACX_EINVAL, "rows must be in 1..4096 (got %d)", rows);
-    if (threads) ctx->nt = threads;
+    if (threads) {
+        ctx->nt = threads;
+        ctx->nt_auto = false;
+    } else if (rows && ctx->nt_auto) {
+        // rows alone: with the default width, not the one chosen for the automatic height
+        ctx->nt = ctx->grid.precision == SACX_FP64 ? 128 : 256;
+        ctx->nt_auto = false;
+    }
     if (rows) {
         ctx->ty = rows;
         ctx->ty_auto = false;

@@ -358,8 +358,8 @@ int sacx_profile_read(sacx_ctx *ctx, sacx_profile *out);
 
 /* ---------------------------------------------------------------------
  * Batches: many independent subdomains (shock tubes, vortex boxes of
- * different sizes, gamma, boundaries and time steps) advanced by one
- * persistent cooperative launch.  Each instance is an ordinary context
+ * different sizes, gamma, boundaries and time steps) advanced together: one
+ * launch per stage over the tiles of every instance.  Each instance is an ordinary context
  * (sacx_batch_context) carved from the batch workspace: initialise, read and
  * inspect it with sacx_init_state / sacx_read_fields / sacx_diagnostics; it
  * may also be advanced alone with sacx_advance.  A batched step of an
@@ -385,12 +385,15 @@ int sacx_batch_context(sacx_batch *b, int32_t i, sacx_ctx **out);
 
 /* Tile shapes: threads per block for the whole launch (64/128/256; 0 keeps)
  * and output rows per tile strip for each instance (rows[n], 1..4096; NULL
- * keeps).  One-dimensional instances always use one-row tiles.  Results do
- * not depend on the shapes.  Used by the tile autotuner. */
+ * keeps).  Until the first call both are chosen from the device and the
+ * instances' sizes.  One-dimensional instances always use one-row tiles.
+ * Results do not depend on the shapes.  Used by the tile autotuner. */
 int sacx_batch_set_tiles(sacx_batch *b, int32_t threads, const int32_t *rows);
 
-/* Advance every instance by nsteps RK4 steps (each with its own dt) in one
- * persistent launch per 512 steps.  Every instance must have been
+/* Advance every instance by nsteps RK4 steps (each with its own dt).  With the
+ * environment variable SACX_BATCH_SPIN_LIMIT set, by a persistent cooperative
+ * launch whose dependency waits give up after that many polls (EDEVICE, and
+ * the instance states are undefined).  Every instance must have been
  * initialised (ESTATE otherwise).  With sync != 0 the call synchronises and
  * returns SACX_ENONPHYS if any instance stopped on a non-physical state.
  * The batch uses the plain hyper-diffusion coefficient: an instance whose

@@ -1,4 +1,5 @@
-// sacx_batch_kernel.h -- the batched persistent launch of many subdomains, as
+// sacx_batch_kernel.h -- the batched launches of many subdomains (one per stage,
+// or one persistent launch), as
 // templates; each precision is instantiated in its own translation unit with
 // the same floating-point contraction as that precision's stage kernel, so an
 // instance evolves in a batch exactly as it does alone.
@@ -201,6 +202,74 @@ __global__ __launch_bounds__(NT, sizeof(real) == 4 ? 2 : 1) void k_batch(BatchAr
         if (threadIdx.x == 0 && kind >= 0)
             __hip_atomic_fetch_add(kind == BATCH_TILE ? tiles + inst : fills + inst, 1, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Stage launches: one launch per stage runs that stage's tiles of every
+// instance, one block per entry of the tile list, over the whole chip; the
+// launch boundary is the dependency.  A tile is the same device code, so the
+// bits are those of the persistent launch and of an instance alone.
+// ---------------------------------------------------------------------------
+template <typename real, int NT, int STAGE>
+__global__ __launch_bounds__(NT, sizeof(real) == 4 ? 2 : 1) void k_batch_stage(const BatchInst<real> *__restrict__ inst,
+                                                                               const BatchItem *__restrict__ items) {
+    __shared__ TileLds<real, NT> lds;
+    // runs of 4 neighbouring tiles share an XCD (and the apron in its L2)
+    const int n = (int)gridDim.x, b = (int)blockIdx.x;
+    const int i = b / kBatchQueues;
+    const int l = b < n - n % (4 * kBatchQueues) ? ((i / 4) * kBatchQueues + b % kBatchQueues) * 4 + i % 4 : b;
+    const BatchItem w = items[l];
+    const StageArgs<real> a = inst[w.inst].st[STAGE - 1];
+    if (inst[w.inst].oned) stage_tile_1d<real, NT, STAGE, true>(a, w.tx, lds);
+    else stage_tile<real, NT, STAGE, true, false>(a, w.tx, w.ty, lds);
+}
+
+// step scalars of every instance: the step before ends (prev), the next
+// begins (next); ending the last one raises *nonphys for any instance that
+// stopped on a non-physical state
+template <typename real>
+__global__ void k_batch_scalars(const BatchInst<real> *__restrict__ inst, int n, int prev, int next, int *nonphys) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    DevScalars *sc = inst[i].sc;
+    if (prev) step_end_dev(sc);
+    if (next) step_begin_dev(sc, 0.0, inst[i].sk);
+    else if (sc->nonphys) *nonphys = 1;
+}
+
+template <typename real, int NT>
+static hipError_t launch_batch_stage_nt(const BatchArgs<real> &b, int stage, int tiles, hipStream_t s) {
+    switch (stage) {
+        case 1: hipLaunchKernelGGL((k_batch_stage<real, NT, 1>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
+        case 2: hipLaunchKernelGGL((k_batch_stage<real, NT, 2>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
+        case 3: hipLaunchKernelGGL((k_batch_stage<real, NT, 3>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
+        default: hipLaunchKernelGGL((k_batch_stage<real, NT, 4>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
+    }
+    return hipGetLastError();
+}
+
+template <typename real>
+hipError_t launch_batch_stage(const BatchArgs<real> &b, int nt, int stage, int tiles, hipStream_t s) {
+    switch (nt) {
+        case 64: return launch_batch_stage_nt<real, 64>(b, stage, tiles, s);
+        case 128: return launch_batch_stage_nt<real, 128>(b, stage, tiles, s);
+        default: return launch_batch_stage_nt<real, 256>(b, stage, tiles, s);
+    }
+}
+
+template <typename real>
+hipError_t launch_batch_scalars(const BatchArgs<real> &b, bool prev, bool next, int *nonphys, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_scalars<real>, dim3((b.n + 63) / 64), dim3(64), 0, s, b.inst, b.n, prev, next, nonphys);
+    return hipGetLastError();
+}
+
+template <typename real>
+hipError_t batch_stage_blocks_per_cu(int nt, int *blocks) {
+    switch (nt) {
+        case 64: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, 64, 1>, 64, 0);
+        case 128: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, 128, 1>, 128, 0);
+        default: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, 256, 1>, 256, 0);
     }
 }
 

@@ -250,7 +250,8 @@ struct BatchItem {
 constexpr int kBatchQueues = 8;
 
 // Batch synchronisation words: the abort flag of a dependency wait that
-// exceeded its bound (sticky), per queue its work counter and the count of
+// exceeded its bound (sticky), per queue its work counter (the first of which
+// holds the stage launches' non-physical flag) and the count of
 // blocks serving it, then per instance the count of completed ghost fills and
 // of completed tiles.  All but the abort flag are zeroed before every launch.
 enum { BATCH_ABORT = 0, BATCH_QUEUE0 = 1, BATCH_BLOCKS0 = 1 + kBatchQueues, BATCH_SYNC0 = 1 + 2 * kBatchQueues };
@@ -290,5 +291,11 @@ template <typename real>
 hipError_t launch_batch(const BatchArgs<real> &b, int nt, int blocks, hipStream_t s);
 template <typename real>
 hipError_t batch_blocks_per_cu(int nt, int *blocks);
+template <typename real>
+hipError_t launch_batch_stage(const BatchArgs<real> &b, int nt, int stage, int tiles, hipStream_t s);
+template <typename real>
+hipError_t launch_batch_scalars(const BatchArgs<real> &b, bool prev, bool next, int *nonphys, hipStream_t s);
+template <typename real>
+hipError_t batch_stage_blocks_per_cu(int nt, int *blocks);
 
 }  // namespace sacx

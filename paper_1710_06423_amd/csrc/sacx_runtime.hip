@@ -1702,6 +1702,8 @@ struct sacx_batch {
     int nitems;
     int nt;
     std::vector<int> *rows;
+    bool shape_auto;    // threads and rows chosen by batch_shape (until set explicitly)
+    bool stages;        // the tables are those of the stage launches; else of the persistent launch
     bool dirty;
     unsigned long long gen_built;  // sum of the instance generations the table was built from
     int blocks;
@@ -1709,10 +1711,6 @@ struct sacx_batch {
 
 namespace {
 
-// polls of a batch dependency wait before it gives up (about a second);
-// SACX_BATCH_SPIN_LIMIT replaces it (a debugging knob: 0 makes every wait
-// that is not already satisfied abort the launch)
-constexpr int kBatchSpinLimit = 1 << 20;
 constexpr size_t kInstBytes = sizeof(BatchInst<double>) > sizeof(BatchInst<float>) ? sizeof(BatchInst<double>)
                                                                                     : sizeof(BatchInst<float>);
 
@@ -1769,9 +1767,49 @@ __global__ void k_zero_ints(int *p, int n) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
+// Threads and strip rows of the stage launches, as shape_for_slots chooses
+// them for one grid: the cheapest (time per row) x (rows + 9) over the widths
+// and the numbers of blocks per compute unit, the rows of every box those
+// that bring the tiles of all of them to that many blocks.
+template <typename real>
+void batch_shape(sacx_batch *b, int cus) {
+    const int kind = sizeof(real) == 8 ? KIND_SPLIT : KIND_F32;
+    double best = 0.0;
+    int rows = 64, nt = sizeof(real) == 8 ? 128 : 256;
+    for (int w = 0; w < 3; ++w) {
+        const int cols = 64 << w, TX = cols - 2 * G;
+        int per = 0;
+        if (batch_stage_blocks_per_cu<real>(cols, &per) != hipSuccess) { (void)hipGetLastError(); continue; }
+        for (int k = 1; k <= std::min(per, 8); ++k) {
+            const float us = kRowUs[kind][w][k - 1];
+            if (us == 0.0f) break;
+            auto tiles = [&](int ty) {
+                int64_t t = 0;
+                for (sacx_ctx *c : *b->ctx)
+                    if (c->L.ny > 1) t += (int64_t)((c->L.nx + TX - 1) / TX) * ((c->L.ny + ty - 1) / ty);
+                return t;
+            };
+            int lo = 1, hi = 257;   // the fewest rows whose tiles fit (257: none up to 256)
+            while (lo < hi) {
+                const int mid = (lo + hi) / 2;
+                if (tiles(mid) <= (int64_t)cus * k) hi = mid; else lo = mid + 1;
+            }
+            if (lo > 256) continue;
+            const double cost = us * (lo + 9.0);
+            if (best == 0.0 || cost < best) { best = cost; nt = cols; rows = lo; }
+        }
+    }
+    b->nt = nt;
+    for (int i = 0; i < b->n; ++i)
+        (*b->rows)[i] = (*b->ctx)[i]->grid.ny == 1 ? 1 : std::min(best == 0.0 ? 256 : rows, (*b->ctx)[i]->grid.ny);
+}
+
 template <typename real>
 int batch_build(sacx_batch *b) {
     const int n = b->n;
+    int cus = 0;
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
+    if (b->shape_auto && b->stages) batch_shape<real>(b, cus);
     const int TX = b->nt - 2 * G;
     std::vector<BatchInst<real>> tab(n);
     struct Costed { int64_t cost; BatchItem it; };
@@ -1845,7 +1883,15 @@ int batch_build(sacx_batch *b) {
     }
     std::vector<BatchItem> flat;
     std::vector<int> qinst;
-    for (int k = 0; k < kBatchQueues; ++k) {
+    if (b->stages) {
+        // the boxes' tiles, instance by instance, then the tubes'
+        for (int tube = 0; tube < 2; ++tube)
+            for (int i = 0; i < n; ++i)
+                if (tab[i].oned == tube)
+                    for (const Costed &t : tiles[i]) flat.push_back(t.it);
+        qinst.assign(n, 0);
+    }
+    for (int k = 0; k < kBatchQueues && !b->stages; ++k) {
         b->qoff[k] = (int)flat.size();
         b->ioff[k] = (int)qinst.size();
         for (int i : group[k]) {
@@ -1863,9 +1909,8 @@ int batch_build(sacx_batch *b) {
     HIPCHK(hipMemcpyAsync(b->items, flat.data(), sizeof(BatchItem) * flat.size(), hipMemcpyHostToDevice, b->stream));
     // host vectors go out of scope: finish the copies first
     HIPCHK(hipStreamSynchronize(b->stream));
-    int per_cu = 0, cus = 0;
+    int per_cu = 0;
     HIPCHK(batch_blocks_per_cu<real>(b->nt, &per_cu));
-    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
     if (per_cu < 1) return fail(SACX_EUNSUP, "batched kernel does not fit on a compute unit with %d threads", b->nt);
     b->blocks = per_cu * cus;
     b->dirty = false;
@@ -1883,6 +1928,28 @@ void batch_args(const sacx_batch *b, int nsteps, int spin, BatchArgs<real> *a) {
     a->sync = b->sync;
     a->nsteps = nsteps;
     a->spin_limit = spin;
+}
+
+// nsteps steps by stage launches; the word behind the abort flag collects the
+// instances' non-physical flags after the last one
+template <typename real>
+int batch_stages(sacx_batch *b, int nsteps) {
+    BatchArgs<real> a;
+    batch_args(b, 0, 0, &a);
+    int *flag = b->sync + BATCH_QUEUE0;
+    hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, b->stream, flag, 1);
+    for (int s = 0; s < nsteps; ++s) {
+        HIPCHK(launch_batch_scalars<real>(a, s > 0, true, flag, b->stream));
+        for (int st = 1; st <= 4; ++st) {
+            for (sacx_ctx *c : *b->ctx) {
+                int rc = fill_narrow(c, st == 1 ? c->U : (st == 3 ? c->B2 : c->B1), NF, true);
+                if (rc) return rc;
+            }
+            HIPCHK(launch_batch_stage<real>(a, b->nt, st, b->nitems, b->stream));
+        }
+    }
+    HIPCHK(launch_batch_scalars<real>(a, nsteps > 0, false, flag, b->stream));
+    return SACX_OK;
 }
 
 }  // namespace
@@ -1959,6 +2026,7 @@ int sacx_batch_create(int32_t n, const sacx_grid *grids, const sacx_params *para
         }
         b->rows->push_back(grids[i].ny == 1 ? 1 : std::min(64, grids[i].ny));
     }
+    b->shape_auto = true;
     b->dirty = true;
     *out = b;
     return SACX_OK;
@@ -1978,6 +2046,7 @@ int sacx_batch_set_tiles(sacx_batch *b, int32_t threads, const int32_t *rows) {
     if (rows)
         for (int i = 0; i < b->n; ++i)
             if (rows[i] < 1 || rows[i] > 4096) return fail(SACX_EINVAL, "rows[%d] = %d out of 1..4096", i, rows[i]);
+    if (threads || rows) b->shape_auto = false;
     if (threads) b->nt = threads;
     if (rows)
         for (int i = 0; i < b->n; ++i) (*b->rows)[i] = (*b->ctx)[i]->grid.ny == 1 ? 1 : rows[i];
@@ -1997,13 +2066,34 @@ int sacx_batch_advance(sacx_batch *b, int32_t nsteps, int32_t sync) {
     }
     DeviceGuard dg(b->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the batch device");
-    if (b->dirty || gsum != b->gen_built) {
+    // One launch per stage over the tiles of every instance, against the
+    // persistent launch in which each instance stays on one XCD (us per step):
+    // 64 instances of the benchmark's ranges 1018 against 1588, 8 tubes and 8
+    // boxes 219 against 925, 3 small tubes and boxes 93 against 274 at its
+    // best shape, 12 tubes 24 against 81: a stage launch has no fill entries,
+    // no waits between entries and uses the whole chip for every instance.
+    // The persistent launch runs where the bound of its waits is set.
+    const char *env = getenv("SACX_BATCH_SPIN_LIMIT");
+    const bool stages = env == nullptr;
+    if (b->dirty || gsum != b->gen_built || stages != b->stages) {
+        b->stages = stages;
         int rc = b->precision == SACX_FP64 ? batch_build<double>(b) : batch_build<float>(b);
         if (rc) return rc;
         b->gen_built = gsum;
     }
-    int spin = kBatchSpinLimit;
-    if (const char *env = getenv("SACX_BATCH_SPIN_LIMIT")) spin = std::max(0, atoi(env));
+    if (b->stages) {
+        const int rc = b->precision == SACX_FP64 ? batch_stages<double>(b, nsteps) : batch_stages<float>(b, nsteps);
+        if (rc) return rc;
+        if (sync) {
+            int w[2] = {0, 0};   // the abort flag, and the word behind it
+            HIPCHK(hipMemcpyAsync(w, b->sync + BATCH_ABORT, sizeof(w), hipMemcpyDeviceToHost, b->stream));
+            HIPCHK(hipStreamSynchronize(b->stream));
+            if (w[0]) return fail(SACX_EDEVICE, "a batch dependency wait exceeded its bound; the instance states are undefined");
+            if (w[1]) return fail(SACX_ENONPHYS, "a batch instance reached a non-physical state");
+        }
+        return SACX_OK;
+    }
+    const int spin = std::max(0, atoi(env));
     // steps per launch: every queue index stays within an int
     int qmax = 1;
     for (int k = 0; k < kBatchQueues; ++k) qmax = std::max(qmax, b->qlen[k]);

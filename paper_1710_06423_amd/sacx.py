@@ -533,7 +533,7 @@ class Solver:
 
 
 class Batch:
-    """Many independent subdomains advanced by one persistent launch
+    """Many independent subdomains advanced together, one launch per stage
     (sacx_batch_*).  Instance i is a borrowed context: ``batch[i]`` is a
     Solver view of it (init_state / read_fields / diagnostics / advance)."""
 

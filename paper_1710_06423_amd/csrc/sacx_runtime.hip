@@ -309,9 +309,11 @@ __global__ void k_unpack_x(FPtr<real> S, int nf, Layout L, const real *b0, const
     for (int g = 0; g < G; ++g) S.p[f][eidx(L, cg + g, j)] = b[((int64_t)f * G + g) * L.ny + j];
 }
 
-// y strips over the padded width: buffer [f][g][i + G], i in [-G, nx + G)
+// y strips over the padded width: buffer [f][g][i + G], i in [-G, nx + G),
+// cells outside x read through the x sides' map (exchange sides: the ghosts)
 template <typename real>
-__global__ void k_pack_y(FPtr<real> S, int nf, Layout L, real *b0, real *b1, int sides, const DevScalars *sc) {
+__global__ void k_pack_y(FPtr<real> S, int nf, Layout L, SideMap mx, real *b0, real *b1, int sides,
+                         const DevScalars *sc) {
     if (sc && !step_active(sc)) return;
     const int w = L.nx + 2 * G;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -321,7 +323,7 @@ __global__ void k_pack_y(FPtr<real> S, int nf, Layout L, real *b0, real *b1, int
     real *b = side == 0 ? b0 : b1;
     const int r0 = side == 0 ? 0 : L.ny - G;
 #pragma unroll
-    for (int g = 0; g < G; ++g) b[((int64_t)f * G + g) * w + i] = S.p[f][eidx(L, i - G, r0 + g)];
+    for (int g = 0; g < G; ++g) b[((int64_t)f * G + g) * w + i] = S.p[f][eidx(L, mx.at(i - G), r0 + g)];
 }
 
 template <typename real>
@@ -473,41 +475,37 @@ __global__ void k_export(FPtr<real> Sx, MPtr<T> dst, uint32_t mask, Layout L, in
         if (mask & (1u << f)) dst.p[f][(int64_t)j * pitch + i] = (T)Sx.p[f][eidx(L, i, j)];
 }
 
-// wave speeds of a state into accumulator slot `slot`
+// |v_d| + c_f of one cell raised into cx, cy; bad where it is non-physical
 template <typename real>
-__global__ void k_wavespeed(FPtr<real> U, FPtr<real> B, int bg, Layout L, double gamma, DevScalars *sc, int slot) {
-    __shared__ double red[2][4];
-    double cx = 0.0, cy = 0.0;
-    int bad = 0;
-    const real gm1 = (real)(gamma - 1.0), half = (real)0.5, gam = (real)gamma;
-    const int64_t n = (int64_t)L.nx * L.ny;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(k % L.nx), j = (int)(k / L.nx);
-        const int64_t e = eidx(L, i, j);
-        real rb = 0, eb = 0, bxb = 0, byb = 0;
-        if (bg) { rb = B.p[0][e]; eb = B.p[1][e]; bxb = B.p[2][e]; byb = B.p[3][e]; }
-        const real rt = U.p[0][e], mx = U.p[1][e], my = U.p[2][e], et = U.p[3][e], bxt = U.p[4][e], byt = U.p[5][e];
-        const real r = rb + rt;
-        const real ir = (real)1 / r;
-        const real ux = mx * ir, uy = my * ir;
-        const real kin = half * (mx * ux + my * uy);
-        const real bbd = bxb * bxt + byb * byt;
-        const real bt2 = bxt * bxt + byt * byt;
-        const real pkt = gm1 * (((et - kin) - bbd) - half * bt2);
-        const real b2b = bxb * bxb + byb * byb;
-        const real pkb = gm1 * (eb - half * b2b);
-        const real pk = pkb + pkt;
-        const real bx = bxb + bxt, by = byb + byt;
-        const real cf = sqrt((gam * pk + (bx * bx + by * by)) * ir);
-        const bool fin = isfinite(rt) && isfinite(mx) && isfinite(my) && isfinite(et) && isfinite(bxt) &&
-                         isfinite(byt) && isfinite(cf);
-        if (!(r > (real)0) || !(pk > (real)0) || !fin) {
-            bad = 1;
-            continue;
-        }
-        cx = fmax(cx, (double)(fabs(ux) + cf));
-        cy = fmax(cy, (double)(fabs(uy) + cf));
+__device__ __forceinline__ void cell_speeds(const real (&u)[NF], real rb, real eb, real bxb, real byb, real gam,
+                                            real gm1, double &cx, double &cy, int &bad) {
+    const real half = (real)0.5;
+    const real rt = u[0], mx = u[1], my = u[2], et = u[3], bxt = u[4], byt = u[5];
+    const real r = rb + rt;
+    const real ir = (real)1 / r;
+    const real ux = mx * ir, uy = my * ir;
+    const real kin = half * (mx * ux + my * uy);
+    const real bbd = bxb * bxt + byb * byt;
+    const real bt2 = bxt * bxt + byt * byt;
+    const real pkt = gm1 * (((et - kin) - bbd) - half * bt2);
+    const real b2b = bxb * bxb + byb * byb;
+    const real pkb = gm1 * (eb - half * b2b);
+    const real pk = pkb + pkt;
+    const real bx = bxb + bxt, by = byb + byt;
+    const real cf = sqrt((gam * pk + (bx * bx + by * by)) * ir);
+    const bool fin = isfinite(rt) && isfinite(mx) && isfinite(my) && isfinite(et) && isfinite(bxt) && isfinite(byt) &&
+                     isfinite(cf);
+    if (!(r > (real)0) || !(pk > (real)0) || !fin) {
+        bad = 1;
+        return;
     }
+    cx = fmax(cx, (double)(fabs(ux) + cf));
+    cy = fmax(cy, (double)(fabs(uy) + cf));
+}
+
+// the maxima of a block of 256 threads into accumulator slot `slot`
+__device__ __forceinline__ void block_speeds(double cx, double cy, int bad, DevScalars *sc, int slot) {
+    __shared__ double red[2][4];
     for (int off = 32; off > 0; off >>= 1) {
         cx = fmax(cx, __shfl_xor(cx, off));
         cy = fmax(cy, __shfl_xor(cy, off));
@@ -519,11 +517,55 @@ __global__ void k_wavespeed(FPtr<real> U, FPtr<real> B, int bg, Layout L, double
         if (bad) atomicOr(&sc->nonphys, 1);
     }
     __syncthreads();
-    // one maximum of each direction per block of 256 threads
     if (threadIdx.x < 2) {
         const double *r = red[threadIdx.x];
         raise_max(&sc->cacc[slot][threadIdx.x], fmax(fmax(r[0], r[1]), fmax(r[2], r[3])));
     }
+}
+
+// the caller's evolved fields into the state, and in the same pass over them
+// the wave speeds of the state (background already in place) into slot 0
+// (as two passes, 8000^2 in FP64 took 1.09 + 0.67 ms)
+template <typename real, typename T, bool BG>
+__global__ __launch_bounds__(256) void k_import_state(FPtr<real> D, CPtr<T> src, FPtr<real> B, Layout L, int64_t pitch,
+                                                      double gamma, DevScalars *sc) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const real gam = (real)gamma, gm1 = (real)(gamma - 1.0);
+    double cx = 0.0, cy = 0.0;
+    int bad = 0;
+    if (i < L.nx) {
+        for (int j = blockIdx.y; j < L.ny; j += gridDim.y) {
+            const int64_t e = eidx(L, i, j);
+            real u[NF], b[NBG] = {0, 0, 0, 0};
+#pragma unroll
+            for (int f = 0; f < NF; ++f) u[f] = (real)src.p[f][(int64_t)j * pitch + i];
+            if (BG) {
+#pragma unroll
+                for (int f = 0; f < NBG; ++f) b[f] = B.p[f][e];
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) D.p[f][e] = u[f];
+            cell_speeds<real>(u, b[0], b[1], b[2], b[3], gam, gm1, cx, cy, bad);
+        }
+    }
+    block_speeds(cx, cy, bad, sc, 0);
+}
+
+// wave speeds of a state without a background into accumulator slot 0
+template <typename real>
+__global__ __launch_bounds__(256) void k_wavespeed(FPtr<real> U, Layout L, double gamma, DevScalars *sc) {
+    const real gam = (real)gamma, gm1 = (real)(gamma - 1.0), zero = (real)0;
+    double cx = 0.0, cy = 0.0;
+    int bad = 0;
+    const int64_t n = (int64_t)L.nx * L.ny;
+    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t e = eidx(L, (int)(k % L.nx), (int)(k / L.nx));
+        real u[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) u[f] = U.p[f][e];
+        cell_speeds<real>(u, zero, zero, zero, zero, gam, gm1, cx, cy, bad);
+    }
+    block_speeds(cx, cy, bad, sc, 0);
 }
 
 __global__ void k_reset_scalars(DevScalars *sc, double t0) {
@@ -605,6 +647,10 @@ __global__ void k_sums_final(const double *partials, int npart, double *out, dou
 
 // ------------------------------------------------------------------ host helpers
 
+// how a context's stored cells are read outside each direction
+SideMap x_map(const sacx_ctx *c) { return side_map(c->L.nx, c->bc[0], c->bc[1]); }
+SideMap y_map(const sacx_ctx *c) { return side_map(c->L.ny, c->bc[2], c->bc[3]); }
+
 // event marks: class 0..3 = stage kernels, 4 = halo, 5 = scalar kernels
 int prof_event(sacx_ctx *c) {
     if (c->ev_used == (int)c->ev_pool->size()) {
@@ -662,7 +708,7 @@ void fill_dir_t(sacx_ctx *c, void *const *fields, int nf, bool gated, int dir) {
             hipLaunchKernelGGL(k_unpack_x<real>, g, dim3(T), 0, c->stream, S, nf, L, (const real *)h[1],
                                (const real *)h[0], 2, sc);
         } else {
-            hipLaunchKernelGGL(k_pack_y<real>, g, dim3(T), 0, c->stream, S, nf, L, (real *)h[0], (real *)h[1], 2, sc);
+            hipLaunchKernelGGL(k_pack_y<real>, g, dim3(T), 0, c->stream, S, nf, L, x_map(c), (real *)h[0], (real *)h[1], 2, sc);
             hipLaunchKernelGGL(k_unpack_y<real>, g, dim3(T), 0, c->stream, S, nf, L, (const real *)h[1],
                                (const real *)h[0], 2, sc);
         }
@@ -706,7 +752,7 @@ int fill_narrow(sacx_ctx *c, void *const *fields, int nf, bool gated) {
 }
 
 // the ghost cells of the state U (the stage kernels do not need them: the
-// kernels of the learned coefficient and sacx_halo_pack's corners read them)
+// kernels of the learned coefficient read them)
 template <typename real>
 int fill_halo_t(sacx_ctx *c) {
     if (has_exchange(c) || narrow(c, 0) || narrow(c, 1)) {
@@ -715,8 +761,7 @@ int fill_halo_t(sacx_ctx *c) {
     } else {
         const int64_t n = (int64_t)2 * G * (c->L.nx + 2 * G + c->L.ny);
         hipLaunchKernelGGL(k_fill_ghosts<real>, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096), NF), dim3(256),
-                           0, c->stream, fptr<real>(c->U, NF), c->L, side_map(c->L.nx, c->bc[0], c->bc[1]),
-                           side_map(c->L.ny, c->bc[2], c->bc[3]));
+                           0, c->stream, fptr<real>(c->U, NF), c->L, x_map(c), y_map(c));
     }
     HIPCHK(hipGetLastError());
     return SACX_OK;
@@ -778,8 +823,8 @@ StageArgs<real> stage_args(sacx_ctx *c) {
     StageArgs<real> a;
     std::memset(&a, 0, sizeof(a));
     a.L = c->L;
-    a.mx = side_map(c->L.nx, c->bc[0], c->bc[1]);
-    a.my = side_map(c->L.ny, c->bc[2], c->bc[3]);
+    a.mx = x_map(c);
+    a.my = y_map(c);
     a.ty = c->ty;
     a.nt = c->nt;
     a.split = c->split;
@@ -875,20 +920,30 @@ int stage(sacx_ctx *c, int s, void *const *S, void *const *U, void *const *A, vo
                                           : run_stage<float>(c, s, S, U, A, o1, o2);
 }
 
-int wavespeed_into(sacx_ctx *c, int slot) {
+int initial_speeds(sacx_ctx *c) {
     const int64_t n = (int64_t)c->L.nx * c->L.ny;
-    const int T = 256;
-    int blocks = (int)std::min<int64_t>((n + T - 1) / T, 2048);
+    const dim3 g((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), t(256);
     if (c->grid.precision == SACX_FP64)
-        hipLaunchKernelGGL(k_wavespeed<double>, dim3(blocks), dim3(T), 0, c->stream, fptr<double>(c->U, NF),
-                           fptr<double>(c->grid.background_on ? c->BG : c->U, NBG), c->grid.background_on, c->L,
-                           c->params.gamma, c->sc, slot);
+        hipLaunchKernelGGL(k_wavespeed<double>, g, t, 0, c->stream, fptr<double>(c->U, NF), c->L, c->params.gamma, c->sc);
     else
-        hipLaunchKernelGGL(k_wavespeed<float>, dim3(blocks), dim3(T), 0, c->stream, fptr<float>(c->U, NF),
-                           fptr<float>(c->grid.background_on ? c->BG : c->U, NBG), c->grid.background_on, c->L,
-                           c->params.gamma, c->sc, slot);
+        hipLaunchKernelGGL(k_wavespeed<float>, g, t, 0, c->stream, fptr<float>(c->U, NF), c->L, c->params.gamma, c->sc);
     HIPCHK(hipGetLastError());
     return SACX_OK;
+}
+
+template <typename real, typename T>
+void import_state(sacx_ctx *c, const void *const *src, int64_t pitch) {
+    CPtr<T> t;
+    for (int k = 0; k < NF; ++k) t.p[k] = (const T *)src[k];
+    // about 8 blocks per compute unit, each over several rows
+    const int gx = (c->L.nx + 255) / 256;
+    const dim3 g(gx, std::max(1, std::min(c->L.ny, 2048 / gx)));
+    if (c->grid.background_on)
+        hipLaunchKernelGGL((k_import_state<real, T, true>), g, dim3(256), 0, c->stream, fptr<real>(c->U, NF), t,
+                           fptr<real>(c->BG, NBG), c->L, pitch, c->params.gamma, c->sc);
+    else
+        hipLaunchKernelGGL((k_import_state<real, T, false>), g, dim3(256), 0, c->stream, fptr<real>(c->U, NF), t,
+                           fptr<real>(c->U, NF), c->L, pitch, c->params.gamma, c->sc);
 }
 
 struct DeviceGuard {
@@ -1127,16 +1182,15 @@ int sacx_set_boundaries(sacx_ctx *ctx, const int32_t bc[4]) {
     return SACX_OK;
 }
 
-// after the evolved fields (and background) are in place: scalars, halos
-// and the first wave-speed reduction
-static int finish_init(sacx_ctx *ctx, double t0) {
-    HIPCHK(hipGetLastError());
+// the step scalars of a new state, and the ghosts it needs once its fields are in place
+static void begin_init(sacx_ctx *ctx, double t0) {
     hipLaunchKernelGGL(k_reset_scalars, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t0);
-    int rc = fill_halo(ctx);
-    if (rc) return rc;
-    rc = wavespeed_into(ctx, 0);
-    if (rc) return rc;
+}
+
+static int finish_init(sacx_ctx *ctx) {
     HIPCHK(hipGetLastError());
+    int rc = fill_narrow(ctx, ctx->U, NF, false);
+    if (rc) return rc;
     ctx->stage_next = 0;
     ctx->initialized = true;
     return SACX_OK;
@@ -1157,38 +1211,28 @@ int sacx_init_state(sacx_ctx *ctx, const void *const *d_fields, const void *cons
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
     const Layout &L = ctx->L;
-    dim3 g((L.nx + 255) / 256, L.ny);
-    const bool f64 = ctx->grid.precision == SACX_FP64;
-    auto import = [&](void *const *dst, const void *const *src, int nf) {
-        if (f64) {
-            if (in_precision == SACX_FP64) {
-                CPtr<double> t;
-                for (int k = 0; k < NF; ++k) t.p[k] = (const double *)src[k < nf ? k : 0];
-                hipLaunchKernelGGL((k_import<double, double>), g, dim3(256), 0, ctx->stream, fptr<double>(dst, nf), t, nf, L, pitch);
-            } else {
-                CPtr<float> t;
-                for (int k = 0; k < NF; ++k) t.p[k] = (const float *)src[k < nf ? k : 0];
-                hipLaunchKernelGGL((k_import<double, float>), g, dim3(256), 0, ctx->stream, fptr<double>(dst, nf), t, nf, L, pitch);
-            }
-        } else {
-            if (in_precision == SACX_FP64) {
-                CPtr<double> t;
-                for (int k = 0; k < NF; ++k) t.p[k] = (const double *)src[k < nf ? k : 0];
-                hipLaunchKernelGGL((k_import<float, double>), g, dim3(256), 0, ctx->stream, fptr<float>(dst, nf), t, nf, L, pitch);
-            } else {
-                CPtr<float> t;
-                for (int k = 0; k < NF; ++k) t.p[k] = (const float *)src[k < nf ? k : 0];
-                hipLaunchKernelGGL((k_import<float, float>), g, dim3(256), 0, ctx->stream, fptr<float>(dst, nf), t, nf, L, pitch);
-            }
-        }
-    };
-    import(ctx->U, d_fields, NF);
+    const bool f64 = ctx->grid.precision == SACX_FP64, in64 = in_precision == SACX_FP64;
+    begin_init(ctx, t0);
     if (ctx->grid.background_on) {
-        import(ctx->BG, d_bg, NBG);
+        const dim3 g((L.nx + 255) / 256, L.ny);
+        CPtr<double> bd;
+        CPtr<float> bf;
+        for (int k = 0; k < NF; ++k) {
+            bd.p[k] = (const double *)d_bg[k < NBG ? k : 0];
+            bf.p[k] = (const float *)d_bg[k < NBG ? k : 0];
+        }
+        if (f64 && in64) hipLaunchKernelGGL((k_import<double, double>), g, dim3(256), 0, ctx->stream, fptr<double>(ctx->BG, NBG), bd, NBG, L, pitch);
+        else if (f64) hipLaunchKernelGGL((k_import<double, float>), g, dim3(256), 0, ctx->stream, fptr<double>(ctx->BG, NBG), bf, NBG, L, pitch);
+        else if (in64) hipLaunchKernelGGL((k_import<float, double>), g, dim3(256), 0, ctx->stream, fptr<float>(ctx->BG, NBG), bd, NBG, L, pitch);
+        else hipLaunchKernelGGL((k_import<float, float>), g, dim3(256), 0, ctx->stream, fptr<float>(ctx->BG, NBG), bf, NBG, L, pitch);
         int rc = fill_narrow(ctx, ctx->BG, NBG, false);
         if (rc) return rc;
     }
-    return finish_init(ctx, t0);
+    if (f64 && in64) import_state<double, double>(ctx, d_fields, pitch);
+    else if (f64) import_state<double, float>(ctx, d_fields, pitch);
+    else if (in64) import_state<float, double>(ctx, d_fields, pitch);
+    else import_state<float, float>(ctx, d_fields, pitch);
+    return finish_init(ctx);
 }
 
 int sacx_init_problem(sacx_ctx *ctx, int32_t kind, const double *prm, int32_t nprm, double t0) {
@@ -1224,7 +1268,9 @@ int sacx_init_problem(sacx_ctx *ctx, int32_t kind, const double *prm, int32_t np
     else
         hipLaunchKernelGGL(k_init_problem<float>, grd, dim3(256), 0, ctx->stream, fptr<float>(ctx->U, NF), L, kind,
                            g.x0, hx, g.y0, hy, mid, along_y, ctx->params.gamma, p0, p1);
-    return finish_init(ctx, t0);
+    begin_init(ctx, t0);
+    rc = initial_speeds(ctx);
+    return rc ? rc : finish_init(ctx);
 }
 
 int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_done, double *t_now) {
@@ -1387,10 +1433,10 @@ static int halo_io(sacx_ctx *ctx, int32_t side, void *buf, bool pack) {
     } else {
         dim3 g((L.nx + 2 * G + T - 1) / T, NF, 1);
         if (f64) {
-            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, (double *)buf, (double *)buf, 10 + s, (const DevScalars *)nullptr);
+            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, x_map(ctx), (double *)buf, (double *)buf, 10 + s, (const DevScalars *)nullptr);
             else hipLaunchKernelGGL(k_unpack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, (const double *)buf, (const double *)buf, 10 + s, (const DevScalars *)nullptr);
         } else {
-            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, (float *)buf, (float *)buf, 10 + s, (const DevScalars *)nullptr);
+            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, x_map(ctx), (float *)buf, (float *)buf, 10 + s, (const DevScalars *)nullptr);
             else hipLaunchKernelGGL(k_unpack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, (const float *)buf, (const float *)buf, 10 + s, (const DevScalars *)nullptr);
         }
     }
@@ -2306,10 +2352,10 @@ static int halo_io_both(sacx_ctx *ctx, int dir, void *b0, void *b1, bool pack) {
         }
     } else {
         if (f64) {
-            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, (double *)b0, (double *)b1, 2, none);
+            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, x_map(ctx), (double *)b0, (double *)b1, 2, none);
             else hipLaunchKernelGGL(k_unpack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, (const double *)b0, (const double *)b1, 2, none);
         } else {
-            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, (float *)b0, (float *)b1, 2, none);
+            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, x_map(ctx), (float *)b0, (float *)b1, 2, none);
             else hipLaunchKernelGGL(k_unpack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, (const float *)b0, (const float *)b1, 2, none);
         }
     }

@@ -290,11 +290,13 @@ int sacx_wave_speeds_max(sacx_ctx *ctx, double *d_c_max);
  * domain is still the caller's (destroy the domain first); its own calls
  * keep working.
  *  sacx_domain_buffer_size: bytes of caller device memory the domain needs
- *    (one strip per EXCHANGE side and the maxima); host arithmetic.
+ *    (one strip per EXCHANGE side, the maxima and the tables of the stage
+ *    launches); host arithmetic.
  *  sacx_domain_create: d_buf (256-byte aligned, ENOSPC if smaller) must
  *    outlive the domain.
  *  sacx_domain_advance: enqueue nsteps steps of every subdomain on their
- *    stream (no synchronisation); ESTATE while a subdomain has a step begun
+ *    stream (no synchronisation, except before the first call's tables and
+ *    those after a change of a subdomain's settings are copied); ESTATE while a subdomain has a step begun
  *    with sacx_stage in progress or has other boundary kinds than when the
  *    domain was created.  A subdomain stopped by a non-physical state
  *    stays stopped (sacx_diagnostics); the others go on.

@@ -211,18 +211,14 @@ __global__ __launch_bounds__(NT, sizeof(real) == 4 ? 2 : 1) void k_batch(BatchAr
 // launch boundary is the dependency.  A tile is the same device code, so the
 // bits are those of the persistent launch and of an instance alone.
 // ---------------------------------------------------------------------------
-template <typename real, int NT, int STAGE>
+template <typename real, int NT, int STAGE, bool HD>
 __global__ __launch_bounds__(NT, sizeof(real) == 4 ? 2 : 1) void k_batch_stage(const BatchInst<real> *__restrict__ inst,
                                                                                const BatchItem *__restrict__ items) {
     __shared__ TileLds<real, NT> lds;
-    // runs of 4 neighbouring tiles share an XCD (and the apron in its L2)
-    const int n = (int)gridDim.x, b = (int)blockIdx.x;
-    const int i = b / kBatchQueues;
-    const int l = b < n - n % (4 * kBatchQueues) ? ((i / 4) * kBatchQueues + b % kBatchQueues) * 4 + i % 4 : b;
-    const BatchItem w = items[l];
+    const BatchItem w = items[listed_tile()];
     const StageArgs<real> a = inst[w.inst].st[STAGE - 1];
-    if (inst[w.inst].oned) stage_tile_1d<real, NT, STAGE, true>(a, w.tx, lds);
-    else stage_tile<real, NT, STAGE, true, false>(a, w.tx, w.ty, lds);
+    if (inst[w.inst].oned) stage_tile_1d<real, NT, STAGE, HD>(a, w.tx, lds);
+    else stage_tile<real, NT, STAGE, HD, false>(a, w.tx, w.ty, lds);
 }
 
 // step scalars of every instance: the step before ends (prev), the next
@@ -238,23 +234,27 @@ __global__ void k_batch_scalars(const BatchInst<real> *__restrict__ inst, int n,
     else if (sc->nonphys) *nonphys = 1;
 }
 
-template <typename real, int NT>
+template <typename real, int NT, bool HD>
 static hipError_t launch_batch_stage_nt(const BatchArgs<real> &b, int stage, int tiles, hipStream_t s) {
+    const dim3 g(tiles), t(NT);
     switch (stage) {
-        case 1: hipLaunchKernelGGL((k_batch_stage<real, NT, 1>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
-        case 2: hipLaunchKernelGGL((k_batch_stage<real, NT, 2>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
-        case 3: hipLaunchKernelGGL((k_batch_stage<real, NT, 3>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
-        default: hipLaunchKernelGGL((k_batch_stage<real, NT, 4>), dim3(tiles), dim3(NT), 0, s, b.inst, b.items); break;
+        case 1: hipLaunchKernelGGL((k_batch_stage<real, NT, 1, HD>), g, t, 0, s, b.inst, b.items); break;
+        case 2: hipLaunchKernelGGL((k_batch_stage<real, NT, 2, HD>), g, t, 0, s, b.inst, b.items); break;
+        case 3: hipLaunchKernelGGL((k_batch_stage<real, NT, 3, HD>), g, t, 0, s, b.inst, b.items); break;
+        default: hipLaunchKernelGGL((k_batch_stage<real, NT, 4, HD>), g, t, 0, s, b.inst, b.items); break;
     }
     return hipGetLastError();
 }
 
 template <typename real>
-hipError_t launch_batch_stage(const BatchArgs<real> &b, int nt, int stage, int tiles, hipStream_t s) {
+hipError_t launch_batch_stage(const BatchArgs<real> &b, int nt, int stage, bool hd, int tiles, hipStream_t s) {
     switch (nt) {
-        case 64: return launch_batch_stage_nt<real, 64>(b, stage, tiles, s);
-        case 128: return launch_batch_stage_nt<real, 128>(b, stage, tiles, s);
-        default: return launch_batch_stage_nt<real, 256>(b, stage, tiles, s);
+        case 64: return hd ? launch_batch_stage_nt<real, 64, true>(b, stage, tiles, s)
+                           : launch_batch_stage_nt<real, 64, false>(b, stage, tiles, s);
+        case 128: return hd ? launch_batch_stage_nt<real, 128, true>(b, stage, tiles, s)
+                            : launch_batch_stage_nt<real, 128, false>(b, stage, tiles, s);
+        default: return hd ? launch_batch_stage_nt<real, 256, true>(b, stage, tiles, s)
+                           : launch_batch_stage_nt<real, 256, false>(b, stage, tiles, s);
     }
 }
 
@@ -264,12 +264,18 @@ hipError_t launch_batch_scalars(const BatchArgs<real> &b, bool prev, bool next, 
     return hipGetLastError();
 }
 
+template <typename real, int NT>
+static hipError_t batch_stage_blocks_nt(bool hd, int *blocks) {
+    return hd ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, NT, 1, true>, NT, 0)
+              : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, NT, 1, false>, NT, 0);
+}
+
 template <typename real>
-hipError_t batch_stage_blocks_per_cu(int nt, int *blocks) {
+hipError_t batch_stage_blocks_per_cu(int nt, bool hd, int *blocks) {
     switch (nt) {
-        case 64: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, 64, 1>, 64, 0);
-        case 128: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, 128, 1>, 128, 0);
-        default: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch_stage<real, 256, 1>, 256, 0);
+        case 64: return batch_stage_blocks_nt<real, 64>(hd, blocks);
+        case 128: return batch_stage_blocks_nt<real, 128>(hd, blocks);
+        default: return batch_stage_blocks_nt<real, 256>(hd, blocks);
     }
 }
 

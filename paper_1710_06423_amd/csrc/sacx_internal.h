@@ -231,7 +231,7 @@ struct BatchInst {
     int oned;                // ny == 1: one-dimensional tiles
     int ntiles;              // tiles of one stage
     int nfill;               // ghost-fill pieces of one stage
-    int pad;
+    int exchange;            // bit per side (x-, x+, y-, y+): an exchange side
 };
 
 // ghost cells (all fields) per ghost-fill piece of a batched instance
@@ -244,6 +244,13 @@ enum { BATCH_TILE = 0, BATCH_FILL = 1 };
 struct BatchItem {
     int inst, tx, ty, kind;
 };
+
+// The entry of a stage launch's tile list that a block takes: runs of 4
+// neighbouring tiles share an XCD (and the apron in its L2).
+__device__ __forceinline__ int listed_tile() {
+    const int n = (int)gridDim.x, b = (int)blockIdx.x, i = b / 8;
+    return b < n - n % 32 ? ((i / 4) * 8 + b % 8) * 4 + i % 4 : b;
+}
 
 // The batch's work is split into one queue per XCD (instances assigned to
 // queues by cost); a block serves the queue of the XCD it runs on.
@@ -292,10 +299,13 @@ hipError_t launch_batch(const BatchArgs<real> &b, int nt, int blocks, hipStream_
 template <typename real>
 hipError_t batch_blocks_per_cu(int nt, int *blocks);
 template <typename real>
-hipError_t launch_batch_stage(const BatchArgs<real> &b, int nt, int stage, int tiles, hipStream_t s);
+hipError_t launch_batch_stage(const BatchArgs<real> &b, int nt, int stage, bool hd, int tiles, hipStream_t s);
 template <typename real>
 hipError_t launch_batch_scalars(const BatchArgs<real> &b, bool prev, bool next, int *nonphys, hipStream_t s);
 template <typename real>
-hipError_t batch_stage_blocks_per_cu(int nt, int *blocks);
+hipError_t batch_stage_blocks_per_cu(int nt, bool hd, int *blocks);
+// the same with the two-role FP64 tile (2-D instances with hyper-diffusion)
+hipError_t launch_batch_split_fp64(const BatchArgs<double> &b, int nc, int stage, int tiles, hipStream_t s);
+hipError_t split_blocks_per_cu_fp64(int nc, bool bg, int *blocks);
 
 }  // namespace sacx

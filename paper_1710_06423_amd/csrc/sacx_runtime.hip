@@ -599,10 +599,9 @@ __global__ void k_step_end(DevScalars *sc) { step_end_dev(sc); }
 // From a device array (dc != nullptr) the values are checked here: one that
 // is not finite, negative, or zero along a direction with more than one cell
 // stops stepping like a non-physical state.
-__global__ void k_step_begin_global(DevScalars *sc, double cx, double cy, const double *dc, StepConsts k) {
-    if (dc) {
-        cx = dc[0];
-        cy = dc[1];
+__device__ __forceinline__ void step_begin_global_dev(DevScalars *sc, double cx, double cy, bool check,
+                                                      const StepConsts &k) {
+    if (check) {
         const bool ok = isfinite(cx) && isfinite(cy) && cx >= 0.0 && cy >= 0.0 && (!k.ax || cx > 0.0) &&
                         (!k.ay || cy > 0.0);
         if (!ok) sc->nonphys = 1;
@@ -610,6 +609,84 @@ __global__ void k_step_begin_global(DevScalars *sc, double cx, double cy, const 
     sc->cacc[sc->cur][0] = (unsigned long long)__double_as_longlong(cx);
     sc->cacc[sc->cur][1] = (unsigned long long)__double_as_longlong(cy);
     step_begin_dev(sc, 0.0, k);
+}
+
+__global__ void k_step_begin_global(DevScalars *sc, double cx, double cy, const double *dc, StepConsts k) {
+    if (dc) {
+        cx = dc[0];
+        cy = dc[1];
+    }
+    step_begin_global_dev(sc, cx, cy, dc != nullptr, k);
+}
+
+// The step scalars of every subdomain of a domain, by one block of 256
+// threads: the step before ends (prev); the maxima over all of them begin the
+// next (next).  As separate launches this was one to end each, one to clear
+// the maxima, one to raise them and one to begin each.
+template <typename real>
+__global__ __launch_bounds__(256) void k_domain_scalars(const BatchInst<real> *__restrict__ inst, int n, int prev,
+                                                        int next, double *cmax) {
+    __shared__ unsigned long long red[2][256];
+    unsigned long long m0 = 0ull, m1 = 0ull;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        DevScalars *sc = inst[i].sc;
+        if (prev) step_end_dev(sc);
+        const unsigned long long a = sc->cacc[sc->cur][0], b = sc->cacc[sc->cur][1];
+        m0 = a > m0 ? a : m0;
+        m1 = b > m1 ? b : m1;
+    }
+    if (!next) return;
+    red[0][threadIdx.x] = m0;
+    red[1][threadIdx.x] = m1;
+    for (int h = 128; h > 0; h >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < h) {
+            for (int d = 0; d < 2; ++d) {
+                const unsigned long long o = red[d][threadIdx.x + h];
+                if (o > red[d][threadIdx.x]) red[d][threadIdx.x] = o;
+            }
+        }
+    }
+    __syncthreads();
+    const double cx = __longlong_as_double((long long)red[0][0]), cy = __longlong_as_double((long long)red[1][0]);
+    if (threadIdx.x == 0) {
+        cmax[0] = cx;
+        cmax[1] = cy;
+    }
+    for (int i = threadIdx.x; i < n; i += 256) step_begin_global_dev(inst[i].sc, cx, cy, true, inst[i].sk);
+}
+
+// The ghost cells of every exchange side of every subdomain, each read
+// straight from the cell of the neighbour (or the diagonal neighbour) that it
+// images; one launch per stage in place of a pack and an unpack per subdomain
+// and direction.
+template <typename real>
+__global__ __launch_bounds__(256) void k_domain_ghosts(const BatchInst<real> *__restrict__ inst, int stage, int px,
+                                                       int py) {
+    const int sub = blockIdx.z, f = blockIdx.y;
+    const BatchInst<real> &I = inst[sub];
+    const int nx = I.L.nx, ny = I.L.ny, W = nx + 2 * G, rows = 2 * G * W, n = rows + 2 * G * ny;
+    real *S = const_cast<real *>(I.st[stage].S[f]);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+        int i, j;
+        if (k < rows) {
+            const int g = k / W;
+            i = k % W - G;
+            j = g < G ? g - G : ny + g - G;
+        } else {
+            const int g = (k - rows) % (2 * G);
+            j = (k - rows) / (2 * G);
+            i = g < G ? g - G : nx + g - G;
+        }
+        const int ox = i < 0 ? -1 : (i >= nx ? 1 : 0), oy = j < 0 ? -1 : (j >= ny ? 1 : 0);
+        if (ox && !(I.exchange & (ox < 0 ? 1 : 2))) continue;   // read through the side's map instead
+        if (oy && !(I.exchange & (oy < 0 ? 4 : 8))) continue;
+        const int a = (sub % px + ox + px) % px, b = (sub / px + oy + py) % py;
+        const BatchInst<real> &N = inst[a + b * px];
+        const int si = ox < 0 ? N.L.nx + i : (ox > 0 ? i - nx : i);
+        const int sj = oy < 0 ? N.L.ny + j : (oy > 0 ? j - ny : j);
+        S[eidx(I.L, i, j)] = N.st[stage].S[f][eidx(N.L, si, sj)];
+    }
 }
 
 // the device stand-in of an all-reduce(max) over subdomains: this context's
@@ -1074,6 +1151,7 @@ int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows) {
     if (threads != 0 && threads != 64 && threads != 128 && threads != 256)
         return fail(SACX_EINVAL, "threads must be 64, 128 or 256 (got %d)", threads);
     if (rows < 0 || rows > 4096) return fail(SACX_EINVAL, "rows must be in 1..4096 (got %d)", rows);
+    ctx->gen += 1;
     if (threads) {
         ctx->nt = threads;
         ctx->nt_auto = false;
@@ -1096,6 +1174,7 @@ int sacx_set_column_split(sacx_ctx *ctx, int32_t on) {
     if (!ctx) return fail(SACX_EINVAL, "ctx must not be NULL");
     if (on != 0 && on != 1) return fail(SACX_EINVAL, "on must be 0 or 1 (got %d)", on);
     ctx->split = on;
+    ctx->gen += 1;
     if (ctx->ty_auto) {
         DeviceGuard dg(ctx->device);
         auto_rows(ctx);
@@ -1813,25 +1892,39 @@ __global__ void k_zero_ints(int *p, int n) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// Threads and strip rows of the stage launches, as shape_for_slots chooses
-// them for one grid: the cheapest (time per row) x (rows + 9) over the widths
-// and the numbers of blocks per compute unit, the rows of every box those
-// that bring the tiles of all of them to that many blocks.
+// which kernel runs the stage launches of several contexts with one scheme
 template <typename real>
-void batch_shape(sacx_batch *b, int cus) {
-    const int kind = sizeof(real) == 8 ? KIND_SPLIT : KIND_F32;
+bool many_split(const sacx_ctx *c) {
+    // (a tube's one-row tile is the one-thread kernel's)
+    return sizeof(real) == 8 && c->params.hd_on && c->split && c->L.ny > 1;
+}
+
+template <typename real>
+hipError_t many_blocks_per_cu(int cols, bool hd, bool split, int *per) {
+    return split ? split_blocks_per_cu_fp64(cols, false, per) : batch_stage_blocks_per_cu<real>(cols, hd, per);
+}
+
+// Columns and strip rows of stage launches over several contexts, as
+// shape_for_slots chooses them for one grid: the cheapest (time per row) x
+// (rows + 9) over the widths and the numbers of blocks per compute unit, the
+// rows those that bring the tiles of all the contexts to that many blocks.
+template <typename real>
+void shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int *nt, int *rows) {
+    const bool hd = ctx[0]->params.hd_on != 0;
+    const int kind = sizeof(real) == 8 ? (hd ? KIND_SPLIT : KIND_F64_NOHD) : (hd ? KIND_F32 : KIND_F32_NOHD);
     double best = 0.0;
-    int rows = 64, nt = sizeof(real) == 8 ? 128 : 256;
+    *rows = 256;
+    *nt = sizeof(real) == 8 ? 128 : 256;
     for (int w = 0; w < 3; ++w) {
         const int cols = 64 << w, TX = cols - 2 * G;
         int per = 0;
-        if (batch_stage_blocks_per_cu<real>(cols, &per) != hipSuccess) { (void)hipGetLastError(); continue; }
+        if (many_blocks_per_cu<real>(cols, hd, split, &per) != hipSuccess) { (void)hipGetLastError(); continue; }
         for (int k = 1; k <= std::min(per, 8); ++k) {
             const float us = kRowUs[kind][w][k - 1];
             if (us == 0.0f) break;
             auto tiles = [&](int ty) {
                 int64_t t = 0;
-                for (sacx_ctx *c : *b->ctx)
+                for (const sacx_ctx *c : ctx)
                     if (c->L.ny > 1) t += (int64_t)((c->L.nx + TX - 1) / TX) * ((c->L.ny + ty - 1) / ty);
                 return t;
             };
@@ -1842,12 +1935,43 @@ void batch_shape(sacx_batch *b, int cus) {
             }
             if (lo > 256) continue;
             const double cost = us * (lo + 9.0);
-            if (best == 0.0 || cost < best) { best = cost; nt = cols; rows = lo; }
+            if (best == 0.0 || cost < best) { best = cost; *nt = cols; *rows = lo; }
         }
     }
-    b->nt = nt;
-    for (int i = 0; i < b->n; ++i)
-        (*b->rows)[i] = (*b->ctx)[i]->grid.ny == 1 ? 1 : std::min(best == 0.0 ? 256 : rows, (*b->ctx)[i]->grid.ny);
+}
+
+// one context's entry of an instance table, for tiles of nt columns and `rows` rows
+template <typename real>
+int table_entry(sacx_ctx *c, int nt, int rows, BatchInst<real> *out) {
+    BatchInst<real> &I = *out;
+    std::memset((void *)&I, 0, sizeof(I));
+    void *const *S[4] = {c->U, c->B1, c->B2, c->B1};
+    void *const *U[4] = {c->U, c->U, c->U, c->U};
+    void *const *A[4] = {c->A, c->A, c->A, c->A};
+    void *const *O1[4] = {c->B1, c->B2, c->B1, c->U};
+    void *const *O2[4] = {c->B1, c->A, c->B1, c->U};
+    for (int st = 0; st < 4; ++st) {
+        StageArgs<real> a = stage_args<real>(c);
+        a.nt = nt;
+        a.ty = rows;
+        for (int f = 0; f < NF; ++f) {
+            a.S[f] = (const real *)S[st][f];
+            a.U[f] = (const real *)U[st][f];
+            a.A[f] = (const real *)A[st][f];
+            a.out1[f] = (real *)O1[st][f];
+            a.out2[f] = (real *)O2[st][f];
+        }
+        if (!fields_uniform(a)) return fail(SACX_EINVAL, "internal: a context's buffers are not laid out at a uniform field stride");
+        I.st[st] = a;
+    }
+    I.sk = step_consts(c);
+    I.sc = c->sc;
+    I.L = c->L;
+    I.periodic_x = c->bc[0] == SACX_PERIODIC;
+    I.periodic_y = c->bc[2] == SACX_PERIODIC;
+    I.oned = (c->grid.ny == 1 && c->grid.nx >= 2) ? 1 : 0;
+    for (int k = 0; k < 4; ++k) I.exchange |= c->bc[k] == SACX_EXCHANGE ? 1 << k : 0;
+    return SACX_OK;
 }
 
 template <typename real>
@@ -1855,7 +1979,14 @@ int batch_build(sacx_batch *b) {
     const int n = b->n;
     int cus = 0;
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
-    if (b->shape_auto && b->stages) batch_shape<real>(b, cus);
+    if (b->shape_auto && b->stages) {
+        int rows = 0;
+        shape_for_many<real>(*b->ctx, cus, false, &b->nt, &rows);
+        for (int i = 0; i < n; ++i) {
+            const int ny = (*b->ctx)[i]->grid.ny;
+            (*b->rows)[i] = ny == 1 ? 1 : std::min(rows, ny);
+        }
+    }
     const int TX = b->nt - 2 * G;
     std::vector<BatchInst<real>> tab(n);
     struct Costed { int64_t cost; BatchItem it; };
@@ -1866,38 +1997,8 @@ int batch_build(sacx_batch *b) {
         if (c->sur_on)
             return fail(SACX_EUNSUP, "instance %d has a learned coefficient set: the batch kernel uses the plain one", i);
         BatchInst<real> &I = tab[i];
-        std::memset((void *)&I, 0, sizeof(I));
-        void *const *S[4] = {c->U, c->B1, c->B2, c->B1};
-        void *const *U[4] = {c->U, c->U, c->U, c->U};
-        void *const *A[4] = {c->A, c->A, c->A, c->A};
-        void *const *O1[4] = {c->B1, c->B2, c->B1, c->U};
-        void *const *O2[4] = {c->B1, c->A, c->B1, c->U};
-        for (int st = 0; st < 4; ++st) {
-            StageArgs<real> a = stage_args<real>(c);
-            a.nt = b->nt;
-            a.ty = (*b->rows)[i];
-            for (int f = 0; f < NF; ++f) {
-                a.S[f] = (const real *)S[st][f];
-                a.U[f] = (const real *)U[st][f];
-                a.A[f] = (const real *)A[st][f];
-                a.out1[f] = (real *)O1[st][f];
-                a.out2[f] = (real *)O2[st][f];
-            }
-            if (!fields_uniform(a))
-                return fail(SACX_EINVAL, "internal: instance %d buffers are not laid out at a uniform field stride", i);
-            I.st[st] = a;
-        }
-        I.sk.cfl = c->params.cfl;
-        I.sk.dx = c->dx;
-        I.sk.dy = c->dy;
-        for (int m = 0; m < 4; ++m) I.sk.c2[m] = c->params.c2[m];
-        I.sk.ax = c->grid.nx > 1;
-        I.sk.ay = c->grid.ny > 1;
-        I.sc = c->sc;
-        I.L = c->L;
-        I.periodic_x = c->bc[0] == SACX_PERIODIC;
-        I.periodic_y = c->bc[2] == SACX_PERIODIC;
-        I.oned = (c->grid.ny == 1 && c->grid.nx >= 2) ? 1 : 0;
+        int rc = table_entry<real>(c, b->nt, (*b->rows)[i], &I);
+        if (rc) return rc;
         const int xt = (c->L.nx + TX - 1) / TX;
         if (I.oned) {
             for (int x = 0; x < xt; ++x) tiles[i].push_back({1, {i, x, 0, BATCH_TILE}});
@@ -1991,7 +2092,7 @@ int batch_stages(sacx_batch *b, int nsteps) {
                 int rc = fill_narrow(c, st == 1 ? c->U : (st == 3 ? c->B2 : c->B1), NF, true);
                 if (rc) return rc;
             }
-            HIPCHK(launch_batch_stage<real>(a, b->nt, st, b->nitems, b->stream));
+            HIPCHK(launch_batch_stage<real>(a, b->nt, st, true, b->nitems, b->stream));
         }
     }
     HIPCHK(launch_batch_scalars<real>(a, nsteps > 0, false, flag, b->stream));
@@ -2222,7 +2323,108 @@ struct sacx_domain {
     std::vector<std::array<int, 4>> *nbr;     // per subdomain and side: the neighbour (exchange sides)
     std::vector<std::array<int, 4>> *bc;      // per subdomain: the boundary kinds the layout was checked with
     double *cmax;                             // the whole domain's wave-speed maxima (device)
+    // stage launches over all subdomains: device tables in the caller's
+    // buffer and the launch shape
+    char *tab;
+    BatchItem *items;
+    int ntiles, nt;
+    bool split;
+    bool built;
+    unsigned long long gen_built;
 };
+
+namespace {
+
+size_t domain_tab_bytes(int n) { return round_up((size_t)n * kInstBytes, kDomainAlign); }
+
+// entries of one stage's tile list (tiles of at most 58 columns and one row)
+size_t domain_items_bytes(int n, sacx_ctx *const *subs) {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += (int64_t)((subs[i]->grid.nx + 57) / 58) * subs[i]->grid.ny;
+    return round_up((size_t)t * sizeof(BatchItem), kDomainAlign);
+}
+
+// the tables of the stage launches, from the subdomains' current settings
+template <typename real>
+int domain_build(sacx_domain *d, unsigned long long gen) {
+    const std::vector<sacx_ctx *> &subs = *d->subs;
+    const int n = (int)subs.size();
+    sacx_ctx *c0 = subs[0];
+    d->split = true;
+    bool set = false;   // a launch shape set on some subdomain
+    for (const sacx_ctx *c : subs) {
+        d->split = d->split && many_split<real>(c);
+        set = set || !c->nt_auto || !c->ty_auto;
+    }
+    int rows = 0, cus = 0;
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c0->device));
+    if (set) d->nt = c0->nt;
+    else shape_for_many<real>(subs, cus, d->split, &d->nt, &rows);
+    std::vector<BatchInst<real>> tab(n);
+    std::vector<BatchItem> items;
+    const int TX = d->nt - 2 * G;
+    for (int i = 0; i < n; ++i) {
+        sacx_ctx *c = subs[i];
+        const int ty = set ? c->ty : std::min(rows, c->L.ny);
+        int rc = table_entry<real>(c, d->nt, ty, &tab[i]);
+        if (rc) return rc;
+        for (int y = 0; y < (c->L.ny + ty - 1) / ty; ++y)
+            for (int x = 0; x < (c->L.nx + TX - 1) / TX; ++x) items.push_back({i, x, y, BATCH_TILE});
+    }
+    d->ntiles = (int)items.size();
+    HIPCHK(hipMemcpyAsync(d->tab, tab.data(), sizeof(tab[0]) * n, hipMemcpyHostToDevice, c0->stream));
+    HIPCHK(hipMemcpyAsync(d->items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice, c0->stream));
+    // the host vectors go out of scope: finish the copies first
+    HIPCHK(hipStreamSynchronize(c0->stream));
+    d->gen_built = gen;
+    d->built = true;
+    return SACX_OK;
+}
+
+// nsteps steps, every launch over all subdomains
+template <typename real>
+int domain_steps(sacx_domain *d, int nsteps) {
+    sacx_ctx *c0 = (*d->subs)[0];
+    const int n = d->px * d->py;
+    BatchArgs<real> a;
+    std::memset((void *)&a, 0, sizeof(a));
+    a.inst = (const BatchInst<real> *)d->tab;
+    a.n = n;
+    a.items = d->items;
+    int64_t ghosts = 0;
+    bool exchange = false;
+    for (const sacx_ctx *c : *d->subs) {
+        ghosts = std::max<int64_t>(ghosts, 2 * G * ((int64_t)c->L.nx + 2 * G + c->L.ny));
+        exchange = exchange || has_exchange(c);
+    }
+    const dim3 gg((unsigned)std::min<int64_t>((ghosts + 255) / 256, 1024), NF, n);
+    for (int s = 0; s <= nsteps; ++s) {
+        {
+            ProfScope ps(c0, 5);
+            hipLaunchKernelGGL(k_domain_scalars<real>, dim3(1), dim3(256), 0, c0->stream, a.inst, n, s > 0, s < nsteps,
+                               d->cmax);
+        }
+        for (int st = 1; st <= 4 && s < nsteps; ++st) {
+            if (exchange) {
+                ProfScope ps(c0, 4);
+                hipLaunchKernelGGL(k_domain_ghosts<real>, gg, dim3(256), 0, c0->stream, a.inst, st - 1, d->px, d->py);
+            }
+            ProfScope ps(c0, st - 1);
+            const int tiles = d->ntiles;
+            if constexpr (sizeof(real) == 8) {
+                if (d->split) {
+                    HIPCHK(launch_batch_split_fp64(a, d->nt, st, tiles, c0->stream));
+                    continue;
+                }
+            }
+            HIPCHK(launch_batch_stage<real>(a, d->nt, st, c0->params.hd_on != 0, tiles, c0->stream));
+        }
+    }
+    HIPCHK(hipGetLastError());
+    return SACX_OK;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -2269,7 +2471,7 @@ static int domain_check(int32_t px, int32_t py, sacx_ctx *const *subs, size_t *b
                 total += round_up(sb, kDomainAlign);
             }
         }
-    *bytes = total;
+    *bytes = total + domain_tab_bytes(n) + domain_items_bytes(n, subs);
     return SACX_OK;
 }
 
@@ -2290,6 +2492,7 @@ int sacx_domain_create(int32_t px, int32_t py, sacx_ctx *const *subs, void *d_bu
     if (!d) return fail(SACX_EINVAL, "out of host memory");
     d->px = px;
     d->py = py;
+    d->built = false;
     d->subs = new (std::nothrow) std::vector<sacx_ctx *>(subs, subs + (size_t)px * py);
     d->buf = new (std::nothrow) std::vector<std::array<void *, 4>>((size_t)px * py);
     d->nbr = new (std::nothrow) std::vector<std::array<int, 4>>((size_t)px * py);
@@ -2301,6 +2504,10 @@ int sacx_domain_create(int32_t px, int32_t py, sacx_ctx *const *subs, void *d_bu
     char *p = (char *)d_buf;
     d->cmax = (double *)p;
     p += kDomainAlign;
+    d->tab = p;
+    p += domain_tab_bytes(px * py);
+    d->items = (BatchItem *)p;
+    p += domain_items_bytes(px * py, subs);
     for (int b = 0; b < py; ++b)
         for (int a = 0; a < px; ++a) {
             const int i = a + b * px;
@@ -2408,6 +2615,30 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
     sacx_ctx *c0 = (*d->subs)[0];
     DeviceGuard dg(c0->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the domain's device");
+    // One launch per stage (and one for its ghosts) over all subdomains: the
+    // subdomains' own launches ran one after the other, each too small for
+    // the chip, with 8 pack and unpack launches per stage in a 2 x 2 split.
+    // Not for narrow periodic directions, whose ghosts need fills, and not
+    // while the stream is captured: a graph must not read tables that a later
+    // call may replace.
+    bool together = true;
+    unsigned long long gen = 0;
+    for (const sacx_ctx *c : *d->subs) {
+        together = together && !narrow(c, 0) && (c->L.ny == 1 || !narrow(c, 1));
+        gen += c->gen;
+    }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (together && nsteps > 0) {
+        HIPCHK(hipStreamIsCapturing(c0->stream, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
+            const bool f64 = c0->grid.precision == SACX_FP64;
+            if (!d->built || d->gen_built != gen) {
+                const int rc = f64 ? domain_build<double>(d, gen) : domain_build<float>(d, gen);
+                if (rc) return rc;
+            }
+            return f64 ? domain_steps<double>(d, nsteps) : domain_steps<float>(d, nsteps);
+        }
+    }
     for (int step = 0; step < nsteps; ++step) {
         hipLaunchKernelGGL(k_zero_doubles, dim3(1), dim3(64), 0, c0->stream, d->cmax, 2);
         HIPCHK(hipGetLastError());

@@ -76,7 +76,6 @@ __global__ __launch_bounds__(NT) void k_stage_1d(StageArgs<real> a) {
 // the one-thread tile: these launch and size its kernels there.
 hipError_t launch_split_fp64(int stage, int nc, bool bg, bool sur, dim3 grid, const StageArgs<double> &a,
                              hipStream_t s);
-hipError_t split_blocks_per_cu_fp64(int nc, bool bg, int *blocks);
 
 template <typename real, int NT, int STAGE>
 static hipError_t launch_s(bool hd, bool bg, const StageArgs<real> &a, hipStream_t s) {

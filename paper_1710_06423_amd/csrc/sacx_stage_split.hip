@@ -33,7 +33,37 @@ hipError_t split_blocks_nc(bool bg, int *blocks) {
               : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_stage_split<double, NC, 1, false>, 2 * NC, 0);
 }
 
+// one stage's tiles of several subdomains, one block per entry of the list
+template <int NC, int STAGE>
+__global__ __launch_bounds__(2 * NC, 2) void k_batch_split(const BatchInst<double> *__restrict__ inst,
+                                                          const BatchItem *__restrict__ items) {
+    __shared__ SplitLds<double, NC, false> lds;
+    const BatchItem w = items[listed_tile()];
+    const StageArgs<double> a = inst[w.inst].st[STAGE - 1];
+    stage_tile_split<double, NC, STAGE, false, false>(a, w.tx, w.ty, lds);
+}
+
+template <int NC>
+hipError_t launch_batch_split_nc(const BatchArgs<double> &b, int stage, int tiles, hipStream_t s) {
+    const dim3 g(tiles), t(2 * NC);
+    switch (stage) {
+        case 1: hipLaunchKernelGGL((k_batch_split<NC, 1>), g, t, 0, s, b.inst, b.items); break;
+        case 2: hipLaunchKernelGGL((k_batch_split<NC, 2>), g, t, 0, s, b.inst, b.items); break;
+        case 3: hipLaunchKernelGGL((k_batch_split<NC, 3>), g, t, 0, s, b.inst, b.items); break;
+        default: hipLaunchKernelGGL((k_batch_split<NC, 4>), g, t, 0, s, b.inst, b.items); break;
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_batch_split_fp64(const BatchArgs<double> &b, int nc, int stage, int tiles, hipStream_t s) {
+    switch (nc) {
+        case 64: return launch_batch_split_nc<64>(b, stage, tiles, s);
+        case 128: return launch_batch_split_nc<128>(b, stage, tiles, s);
+        default: return launch_batch_split_nc<256>(b, stage, tiles, s);
+    }
+}
 
 hipError_t launch_split_fp64(int stage, int nc, bool bg, bool sur, dim3 grid, const StageArgs<double> &a,
                              hipStream_t s) {

@@ -17,13 +17,14 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libsacx.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["sacx_stage.hip", "sacx_stage_split.hip", "sacx_stage32.hip", "sacx_batch.hip", "sacx_batch32.hip",
+SOURCES = ["sacx_stage.hip", "sacx_stage_split.hip", "sacx_stage32.hip", "sacx_box.hip", "sacx_box32.hip", "sacx_batch.hip", "sacx_batch32.hip",
            "sacx_ratio.hip", "sacx3.hip", "sacx_runtime.hip", "sacx_cnn.hip"]
 # per-file floating-point contraction: the FP32 stage and batch units contract
 # the multiply-adds written within one expression (a rule of the source alone,
 # so both kernels round an instance the same way); every other unit rounds
 # each operation on its own
-CONTRACT = {"sacx_stage32.hip": "-ffp-contract=on", "sacx_batch32.hip": "-ffp-contract=on"}
+CONTRACT = {"sacx_stage32.hip": "-ffp-contract=on", "sacx_batch32.hip": "-ffp-contract=on",
+            "sacx_box32.hip": "-ffp-contract=on"}
 
 # per-file scheduling: the two-role FP64 stage kernel measured 2-3 % faster
 # with LLVM's iterative ILP-maximising scheduler (the one-thread tile slower)

@@ -1,0 +1,8 @@
+// sacx_box.hip -- the box stage kernel, double arithmetic.
+#include "sacx_box_kernel.h"
+
+namespace sacx {
+
+template hipError_t launch_box<double>(int, bool, int, const StageArgs<double> &, hipStream_t);
+
+}  // namespace sacx

@@ -1,0 +1,40 @@
+// sacx_box_kernel.h -- the box stage kernel and its launchers of the box stage kernel, as templates; each
+// precision is instantiated in a unit of its own with the contraction rule of
+// that precision's stage kernel.
+#pragma once
+
+#include "sacx_stage_kernel.h"
+#include "sacx_tile_box.h"
+
+namespace sacx {
+
+template <typename real, int W, int R, int STAGE, bool HD>
+__global__ __launch_bounds__(64 * W, R == 1 ? 4 : 2) void k_stage_box(StageArgs<real> a) {
+    __shared__ BoxLds<real, W, R, HD> lds;
+    int tx, ty;
+    xcd_tile<4>(tx, ty);
+    stage_tile_box<real, W, R, STAGE, HD>(a, tx, ty, lds);
+}
+
+template <typename real, int W, int R, bool HD>
+static hipError_t launch_box_r(int stage, const StageArgs<real> &a, hipStream_t s) {
+    const dim3 g((a.L.nx + 57) / 58, (a.L.ny + W * R - 1) / (W * R)), t(64 * W);
+    switch (stage) {
+        case 1: hipLaunchKernelGGL((k_stage_box<real, W, R, 1, HD>), g, t, 0, s, a); break;
+        case 2: hipLaunchKernelGGL((k_stage_box<real, W, R, 2, HD>), g, t, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((k_stage_box<real, W, R, 3, HD>), g, t, 0, s, a); break;
+        default: hipLaunchKernelGGL((k_stage_box<real, W, R, 4, HD>), g, t, 0, s, a); break;
+    }
+    return hipGetLastError();
+}
+
+// rows: 8 (one row per wave) or, FP32 with hyper-diffusion, 16 (two)
+template <typename real>
+hipError_t launch_box(int stage, bool hd, int rows, const StageArgs<real> &a, hipStream_t s) {
+    if constexpr (sizeof(real) == 4) {
+        if (hd && rows == 16) return launch_box_r<real, 8, 2, true>(stage, a, s);
+    }
+    return hd ? launch_box_r<real, 8, 1, true>(stage, a, s) : launch_box_r<real, 8, 1, false>(stage, a, s);
+}
+
+}  // namespace sacx

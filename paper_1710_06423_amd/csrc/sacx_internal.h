@@ -280,6 +280,10 @@ struct BatchArgs {
 // host-side launchers (defined in the .hip units)
 template <typename real>
 hipError_t launch_stage(int stage, bool hd, bool bg, const StageArgs<real> &a, hipStream_t s);
+// the box kernel, 58 columns x `rows` rows per block (8, or 16 in FP32 with
+// hyper-diffusion); no background, plain coefficient
+template <typename real>
+hipError_t launch_box(int stage, bool hd, int rows, const StageArgs<real> &a, hipStream_t s);
 template <typename real>
 hipError_t stage_blocks_per_cu(int nt, bool hd, bool bg, bool split, int *blocks);
 template <typename real>

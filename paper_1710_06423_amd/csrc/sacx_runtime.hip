@@ -78,6 +78,7 @@ struct sacx_ctx {
     bool initialized;
     int ty, nt;
     int split;         // FP64 hyper-diffusion tiles: two threads per column
+    int box;           // rows of the box kernel's blocks (8, 16); 0: the marching kernels
     bool nt_auto, ty_auto;  // columns / strip height chosen by auto_rows (until set explicitly)
     double dx, dy;
     SchemeConsts kc;
@@ -219,7 +220,7 @@ int rows_for_blocks(const Layout &L, int nt, int64_t blocks) {
 // against 431; 1501 x 997 without hyper-diffusion 196 against 253.  Strips
 // above 160 rows keep the default width: there the widths differ by less than
 // the spread of the figures above.
-bool shape_for_slots(const sacx_ctx *c, int cus, int *nt, int *ty) {
+bool shape_for_slots(const sacx_ctx *c, int cus, int *nt, int *ty, double *cost_us) {
     const bool fp64 = c->grid.precision == SACX_FP64;
     const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
     if (c->L.ny <= 8 || (fp64 && hd && !c->split)) return false;
@@ -241,8 +242,40 @@ bool shape_for_slots(const sacx_ctx *c, int cus, int *nt, int *ty) {
             if (!found || cost < best) { found = true; best = cost; *nt = cols; *ty = rows; }
         }
     }
+    *cost_us = best;
     return found;
 }
+
+// A stage by the box kernel with `tiles` blocks: about 3 us to launch, `one`
+// for the first block of a compute unit, and `round` for every two blocks per
+// unit past the first 0.6 of that (us, MI355X, mean of the four stages).
+struct BoxTime {
+    float one, round;
+};
+const BoxTime kBoxUs[2][2][2] = {
+    // no hyper-diffusion            with: 8 rows, 16 rows
+    {{{4.2f, 7.8f}, {0.0f, 0.0f}}, {{7.5f, 11.4f}, {0.0f, 0.0f}}},   // FP64
+    {{{3.5f, 4.4f}, {0.0f, 0.0f}}, {{5.0f, 5.5f}, {6.2f, 9.9f}}},    // FP32
+};
+
+double box_us(const BoxTime &b, int64_t tiles, int cus) {
+    return 3.0 + b.one + b.round * std::max(0.0, (double)tiles / (2.0 * cus) - 0.6);
+}
+
+// The box kernel's rows where it is expected to take less than 0.95 of
+// `march_us` (the marching shape's expected time) over the given tile
+// counts (8 rows, 16 rows); 0 where it is not.
+int box_for(bool fp32, bool hd, int64_t tiles8, int64_t tiles16, int cus, double march_us) {
+    double best = 0.95 * march_us;
+    int rows = 0;
+    for (int k = 0; k < (fp32 && hd ? 2 : 1); ++k) {
+        const double us = box_us(kBoxUs[fp32][hd][k], k ? tiles16 : tiles8, cus);
+        if (us < best) { best = us; rows = k ? 16 : 8; }
+    }
+    return rows;
+}
+
+int64_t box_tiles(const Layout &L, int rows) { return (int64_t)((L.nx + 57) / 58) * ((L.ny + rows - 1) / rows); }
 
 // the launch shape for the context's current settings: resident blocks from
 // the device's compute units and the kernel's occupancy.  Measured on MI355X:
@@ -252,10 +285,15 @@ void auto_rows(sacx_ctx *c) {
     int cus = 0, per = 0;
     const bool fp64 = c->grid.precision == SACX_FP64;
     const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
+    c->box = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
     if (c->nt_auto) {
         c->nt = fp64 ? 128 : 256;
-        if (e == hipSuccess && cus >= 1 && shape_for_slots(c, cus, &c->nt, &c->ty)) return;
+        double us = 0.0;
+        if (e == hipSuccess && cus >= 1 && shape_for_slots(c, cus, &c->nt, &c->ty, &us)) {
+            if (!bg) c->box = box_for(!fp64, hd, box_tiles(c->L, 8), box_tiles(c->L, 16), cus, us);
+            return;
+        }
     }
     if (e == hipSuccess)
         e = fp64 ? stage_blocks_per_cu<double>(c->nt, hd, bg, c->split != 0, &per)
@@ -982,6 +1020,10 @@ int run_stage(sacx_ctx *c, int stage, void *const *S, void *const *U, void *cons
         a.out2[f] = (real *)(o2 ? o2[f] : o1[f]);
     }
     if (!fields_uniform(a)) return fail(SACX_EINVAL, "internal: stage buffers are not laid out at a uniform field stride");
+    if (c->box && !a.Rs) {
+        HIPCHK(launch_box<real>(stage, c->params.hd_on != 0, c->box, a, c->stream));
+        return SACX_OK;
+    }
     HIPCHK(launch_stage<real>(stage, c->params.hd_on != 0, c->grid.background_on != 0, a, c->stream));
     return SACX_OK;
 }
@@ -1152,6 +1194,7 @@ int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows) {
         return fail(SACX_EINVAL, "threads must be 64, 128 or 256 (got %d)", threads);
     if (rows < 0 || rows > 4096) return fail(SACX_EINVAL, "rows must be in 1..4096 (got %d)", rows);
     ctx->gen += 1;
+    if (threads || rows) ctx->box = 0;
     if (threads) {
         ctx->nt = threads;
         ctx->nt_auto = false;
@@ -1184,8 +1227,9 @@ int sacx_set_column_split(sacx_ctx *ctx, int32_t on) {
 
 int sacx_get_launch(const sacx_ctx *ctx, int32_t *threads, int32_t *rows) {
     if (!ctx || !threads || !rows) return fail(SACX_EINVAL, "ctx/threads/rows must not be NULL");
-    *threads = ctx->nt;
-    *rows = ctx->ty;
+    const bool box = ctx->box && !ctx->sur_on;
+    *threads = box ? 64 : ctx->nt;
+    *rows = box ? ctx->box : ctx->ty;
     return SACX_OK;
 }
 

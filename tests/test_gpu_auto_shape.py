@@ -8,7 +8,7 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nx,ny", [(58, 9), (59, 10), (64, 64), (123, 200), (300, 136), (1024, 64), (40, 1000)])
+@pytest.mark.parametrize("nx,ny", [(58, 9), (59, 10), (64, 64), (123, 200), (300, 136), (1024, 64), (40, 1000), (1030, 1001)])
 @pytest.mark.parametrize("precision,hd,background", [(0, True, False), (0, False, False), (0, True, True),
                                                      (1, True, False), (1, False, False)])
 def test_automatic_shape_equals_fixed_shape(nx, ny, precision, hd, background):

@@ -308,6 +308,9 @@ template <typename real>
 hipError_t launch_batch_scalars(const BatchArgs<real> &b, bool prev, bool next, int *nonphys, hipStream_t s);
 template <typename real>
 hipError_t batch_stage_blocks_per_cu(int nt, bool hd, int *blocks);
+// the same with boxes of `rows` rows (launch_box)
+template <typename real>
+hipError_t launch_batch_box(const BatchArgs<real> &b, int rows, int stage, bool hd, int tiles, hipStream_t s);
 // the same with the two-role FP64 tile (2-D instances with hyper-diffusion)
 hipError_t launch_batch_split_fp64(const BatchArgs<double> &b, int nc, int stage, int tiles, hipStream_t s);
 hipError_t split_blocks_per_cu_fp64(int nc, bool bg, int *blocks);

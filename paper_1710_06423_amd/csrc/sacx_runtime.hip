@@ -1871,6 +1871,7 @@ struct sacx_batch {
     int nitems;
     int nt;
     std::vector<int> *rows;
+    int box;            // rows of the stage launches' boxes; 0: marching tiles
     bool shape_auto;    // threads and rows chosen by batch_shape (until set explicitly)
     bool stages;        // the tables are those of the stage launches; else of the persistent launch
     bool dirty;
@@ -1948,12 +1949,24 @@ hipError_t many_blocks_per_cu(int cols, bool hd, bool split, int *per) {
     return split ? split_blocks_per_cu_fp64(cols, false, per) : batch_stage_blocks_per_cu<real>(cols, hd, per);
 }
 
+constexpr int kTubeCells = 512 - 2 * G;   // a tube's cells per block of the box kernel
+
+// the tiles of one context in a list: boxes of 58 x `box` cells, or (box 0)
+// strips of nt columns and `rows` rows
+void list_tiles(const sacx_ctx *c, int i, int nt, int rows, int box, std::vector<BatchItem> *out) {
+    const bool tube = c->L.ny == 1;
+    const int tx = box ? (tube ? kTubeCells : 58) : nt - 2 * G;
+    const int ty = tube ? 1 : (box ? box : rows);
+    for (int y = 0; y < (c->L.ny + ty - 1) / ty; ++y)
+        for (int x = 0; x < (c->L.nx + tx - 1) / tx; ++x) out->push_back({i, x, y, BATCH_TILE});
+}
+
 // Columns and strip rows of stage launches over several contexts, as
 // shape_for_slots chooses them for one grid: the cheapest (time per row) x
 // (rows + 9) over the widths and the numbers of blocks per compute unit, the
 // rows those that bring the tiles of all the contexts to that many blocks.
 template <typename real>
-void shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int *nt, int *rows) {
+void shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int *nt, int *rows, int *box) {
     const bool hd = ctx[0]->params.hd_on != 0;
     const int kind = sizeof(real) == 8 ? (hd ? KIND_SPLIT : KIND_F64_NOHD) : (hd ? KIND_F32 : KIND_F32_NOHD);
     double best = 0.0;
@@ -1982,6 +1995,16 @@ void shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int
             if (best == 0.0 || cost < best) { best = cost; *nt = cols; *rows = lo; }
         }
     }
+    // boxes instead where they are expected to be faster (past the shapes
+    // above a marching block takes 256 rows, which the boxes do not beat)
+    int64_t t8 = 0, t16 = 0;
+    for (const sacx_ctx *c : ctx) {
+        t8 += c->L.ny > 1 ? box_tiles(c->L, 8) : (c->L.nx + kTubeCells - 1) / kTubeCells;
+        t16 += c->L.ny > 1 ? box_tiles(c->L, 16) : (c->L.nx + kTubeCells - 1) / kTubeCells;
+    }
+    bool boxes = false;   // (tubes alone run in blocks of their own width)
+    for (const sacx_ctx *c : ctx) boxes = boxes || c->L.ny > 1;
+    *box = best == 0.0 || !boxes ? 0 : box_for(sizeof(real) == 4, hd, t8, t16, cus, best);
 }
 
 // one context's entry of an instance table, for tiles of nt columns and `rows` rows
@@ -2023,9 +2046,10 @@ int batch_build(sacx_batch *b) {
     const int n = b->n;
     int cus = 0;
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
+    b->box = 0;
     if (b->shape_auto && b->stages) {
         int rows = 0;
-        shape_for_many<real>(*b->ctx, cus, false, &b->nt, &rows);
+        shape_for_many<real>(*b->ctx, cus, false, &b->nt, &rows, &b->box);
         for (int i = 0; i < n; ++i) {
             const int ny = (*b->ctx)[i]->grid.ny;
             (*b->rows)[i] = ny == 1 ? 1 : std::min(rows, ny);
@@ -2078,8 +2102,7 @@ int batch_build(sacx_batch *b) {
         // the boxes' tiles, instance by instance, then the tubes'
         for (int tube = 0; tube < 2; ++tube)
             for (int i = 0; i < n; ++i)
-                if (tab[i].oned == tube)
-                    for (const Costed &t : tiles[i]) flat.push_back(t.it);
+                if (tab[i].oned == tube) list_tiles((*b->ctx)[i], i, b->nt, (*b->rows)[i], b->box, &flat);
         qinst.assign(n, 0);
     }
     for (int k = 0; k < kBatchQueues && !b->stages; ++k) {
@@ -2136,7 +2159,8 @@ int batch_stages(sacx_batch *b, int nsteps) {
                 int rc = fill_narrow(c, st == 1 ? c->U : (st == 3 ? c->B2 : c->B1), NF, true);
                 if (rc) return rc;
             }
-            HIPCHK(launch_batch_stage<real>(a, b->nt, st, true, b->nitems, b->stream));
+            HIPCHK(b->box ? launch_batch_box<real>(a, b->box, st, true, b->nitems, b->stream)
+                          : launch_batch_stage<real>(a, b->nt, st, true, b->nitems, b->stream));
         }
     }
     HIPCHK(launch_batch_scalars<real>(a, nsteps > 0, false, flag, b->stream));
@@ -2371,7 +2395,7 @@ struct sacx_domain {
     // buffer and the launch shape
     char *tab;
     BatchItem *items;
-    int ntiles, nt;
+    int ntiles, nt, box;
     bool split;
     bool built;
     unsigned long long gen_built;
@@ -2401,19 +2425,20 @@ int domain_build(sacx_domain *d, unsigned long long gen) {
         set = set || !c->nt_auto || !c->ty_auto;
     }
     int rows = 0, cus = 0;
+    d->box = 0;
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c0->device));
     if (set) d->nt = c0->nt;
-    else shape_for_many<real>(subs, cus, d->split, &d->nt, &rows);
+    else shape_for_many<real>(subs, cus, d->split, &d->nt, &rows, &d->box);
     std::vector<BatchInst<real>> tab(n);
     std::vector<BatchItem> items;
-    const int TX = d->nt - 2 * G;
+    for (const sacx_ctx *c : subs)   // the one-thread tile was asked for
+        if (sizeof(real) == 8 && c->params.hd_on && !c->split) d->box = 0;
     for (int i = 0; i < n; ++i) {
         sacx_ctx *c = subs[i];
         const int ty = set ? c->ty : std::min(rows, c->L.ny);
         int rc = table_entry<real>(c, d->nt, ty, &tab[i]);
         if (rc) return rc;
-        for (int y = 0; y < (c->L.ny + ty - 1) / ty; ++y)
-            for (int x = 0; x < (c->L.nx + TX - 1) / TX; ++x) items.push_back({i, x, y, BATCH_TILE});
+        list_tiles(c, i, d->nt, ty, d->box, &items);
     }
     d->ntiles = (int)items.size();
     HIPCHK(hipMemcpyAsync(d->tab, tab.data(), sizeof(tab[0]) * n, hipMemcpyHostToDevice, c0->stream));
@@ -2455,6 +2480,10 @@ int domain_steps(sacx_domain *d, int nsteps) {
             }
             ProfScope ps(c0, st - 1);
             const int tiles = d->ntiles;
+            if (d->box) {
+                HIPCHK(launch_batch_box<real>(a, d->box, st, c0->params.hd_on != 0, tiles, c0->stream));
+                continue;
+            }
             if constexpr (sizeof(real) == 8) {
                 if (d->split) {
                     HIPCHK(launch_batch_split_fp64(a, d->nt, st, tiles, c0->stream));

@@ -645,8 +645,17 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
 // sequence adds them, so the results are the same bits as the 2-D path.
 // A tile is TX columns of the single row.
 // ---------------------------------------------------------------------------
-template <typename real, int NT, int STAGE, bool HD>
-__device__ __forceinline__ void stage_tile_1d(const StageArgs<real> &a, int tile_x, TileLds<real, NT> &lds) {
+template <typename real, int NT>
+struct TubeLds {
+    real fx[5][NT];        // x fluxes
+    real q[1][NQ][NT];     // the row
+    real s[NT];            // compression
+    real hx[5][NT];        // x-face fluxes H_x
+    double red[3][NT / 64];
+};
+
+template <typename real, int NT, int STAGE, bool HD, typename Lds>
+__device__ __forceinline__ void stage_tile_1d(const StageArgs<real> &a, int tile_x, Lds &lds) {
     constexpr int TX = NT - 2 * G;
     const DevScalars *sc = a.sc;
     if (!sc->active) return;

@@ -55,7 +55,7 @@ struct DevScalars {
     int cur;             // slot holding the maxima of the current state
     int active;          // 1 while the step in progress proceeds
     int nonphys;         // sticky: a non-physical state was reduced
-    int pad;
+    int prev_active;     // `active` of the step before the one in progress, of the same call
 };
 
 // Raise a wave-speed accumulator (the IEEE bits of a non-negative double) to
@@ -190,6 +190,19 @@ struct StageArgs {
     int rs_tile, rs_ntx;
 };
 
+// arguments of a tube's step kernel (a whole RK4 step in one launch)
+template <typename real>
+struct TubeArgs {
+    const real *U;       // field 0 of the step's start state (field f at + f * fstride)
+    real *out;           // field 0 of the new state
+    int64_t fstride;
+    Layout L;
+    int periodic, open_lo, open_hi;
+    SchemeConsts k;
+    DevScalars *sc;
+    int second;          // this step's U is the step before's out (the pair ends in the state buffer)
+};
+
 // arguments of the ratio-field kernels (plain ratios of a state whose halo is
 // filled; no background)
 template <typename real>
@@ -280,6 +293,8 @@ struct BatchArgs {
 // host-side launchers (defined in the .hip units)
 template <typename real>
 hipError_t launch_stage(int stage, bool hd, bool bg, const StageArgs<real> &a, hipStream_t s);
+template <typename real>
+hipError_t launch_tube_step(bool hd, const TubeArgs<real> &a, hipStream_t s);
 // the box kernel, 58 columns x `rows` rows per block (8, or 16 in FP32 with
 // hyper-diffusion); no background, plain coefficient
 template <typename real>

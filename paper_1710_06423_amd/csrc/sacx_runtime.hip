@@ -618,15 +618,19 @@ __global__ void k_reset_scalars(DevScalars *sc, double t0) {
     sc->cur = 0;
     sc->active = 1;
     sc->nonphys = 0;
-    sc->pad = 0;
+    sc->prev_active = 0;
 }
 
 // dt for the step about to start (CFL time step with the end-time clamp);
 // `prev`: the step before it, of the same call, ends first (one launch for
 // both); otherwise the call begins here
 __global__ void k_step_begin(DevScalars *sc, double t_end, StepConsts k, int prev) {
-    if (prev) step_end_dev(sc);
-    else sc->steps0 = sc->steps;
+    if (prev) {
+        step_end_dev(sc);
+        sc->prev_active = sc->active;
+    } else {
+        sc->steps0 = sc->steps;
+    }
     step_begin_dev(sc, t_end, k);
 }
 
@@ -1028,6 +1032,27 @@ int run_stage(sacx_ctx *c, int stage, void *const *S, void *const *U, void *cons
     return SACX_OK;
 }
 
+// one RK4 step of a tube in one launch, from buffer `from` to buffer `to`
+template <typename real>
+int tube_step(sacx_ctx *c, void *const *from, void *const *to, bool second) {
+    TubeArgs<real> a;
+    a.U = (const real *)from[0];
+    a.out = (real *)to[0];
+    a.fstride = (int64_t)(((const char *)c->U[1] - (const char *)c->U[0]) / (ptrdiff_t)sizeof(real));
+    for (int f = 1; f < NF; ++f)
+        if ((const real *)from[f] != a.U + f * a.fstride || (real *)to[f] != a.out + f * a.fstride)
+            return fail(SACX_EINVAL, "internal: state buffers are not laid out at a uniform field stride");
+    a.L = c->L;
+    a.periodic = c->bc[0] == SACX_PERIODIC;
+    a.open_lo = c->bc[0] == SACX_OPEN;
+    a.open_hi = c->bc[1] == SACX_OPEN;
+    a.k = c->kc;
+    a.sc = c->sc;
+    a.second = second;
+    HIPCHK(launch_tube_step<real>(c->params.hd_on != 0, a, c->stream));
+    return SACX_OK;
+}
+
 int stage(sacx_ctx *c, int s, void *const *S, void *const *U, void *const *A, void *const *o1, void *const *o2) {
     if (narrow(c, 0) || narrow(c, 1)) {
         ProfScope ps(c, 4);
@@ -1407,6 +1432,9 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
     const bool sync = steps_done || t_now;
     const StepConsts sk = step_consts(ctx);
+    // a tube's steps take one launch each, but for the last of an odd number
+    const bool tube = ctx->L.ny == 1 && ctx->L.nx >= 2 && !ctx->grid.background_on && !ctx->sur_on;
+    const int tube_steps = tube ? nsteps & ~1 : 0;
     // A synchronising call enqueues in chunks and stops early once the device
     // reports that stepping ended (end time reached or non-physical state).
     const int chunk = sync ? 128 : (nsteps > 0 ? nsteps : 1);
@@ -1424,6 +1452,16 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
                     if ((rc = sur_refresh(ctx))) return rc;
                 }
                 ctx->sur_since += 1;
+            }
+            if (n < tube_steps) {
+                // in pairs, U to B2 and back, so that a call ends with its state in U
+                ProfScope ps(ctx, 0);
+                const bool second = n & 1;
+                void *const *from = second ? ctx->B2 : ctx->U, *const *to = second ? ctx->U : ctx->B2;
+                if ((rc = ctx->grid.precision == SACX_FP64 ? tube_step<double>(ctx, from, to, second)
+                                                           : tube_step<float>(ctx, from, to, second)))
+                    return rc;
+                continue;
             }
             if ((rc = stage(ctx, 1, ctx->U, nullptr, nullptr, ctx->B1, nullptr))) return rc;
             if ((rc = stage(ctx, 2, ctx->B1, ctx->U, nullptr, ctx->B2, ctx->A))) return rc;

@@ -36,6 +36,7 @@ namespace cnn {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int NL = 4;
@@ -143,8 +144,10 @@ struct ConvArgs {
 // tap's B operand is a 16-byte LDS read.  One barrier per output row.
 constexpr int kStrip = 64;
 
+// (held to four waves per SIMD: 128 registers instead of 140, 24 to 19 us for a
+// hidden layer, 29 to 22 us backward)
 template <int CIN, int NCHUNK, int MB, int MODE>
-__global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
+__global__ __launch_bounds__(256, 4) void k_conv(ConvArgs a) {
     constexpr int LW = kStrip + 2;          // pixels of an LDS row
     constexpr int VPP = CIN / 8;            // 16-byte vectors per pixel
     constexpr int NV = LW * VPP;            // vectors per LDS row
@@ -354,25 +357,42 @@ __global__ __launch_bounds__(256) void k_loss_final(const double *__restrict__ p
 struct WgradArgs {
     const unsigned short *g;   // error signal of the layer's output, NHWC (COUTP)
     const unsigned short *x;   // the layer's input, NHWC (CINP)
-    float *part;               // per-block partial gradients [block][cout*cin*9 + cout]
+    float *part;               // per-block partial gradients [block][9 taps][cout][cin], then [cout] biases
     int n, h, w, rows;
     int cin, cout;
 };
 
-// A block owns a 32-pixel row segment of one image over `rows` rows.  Per row
-// the error signal (32 px x COUTP) and the three input rows around it
-// (34 px x CINP, stored as three x-shifted copies so every operand read is
-// an aligned 16-byte LDS load) are transposed into LDS; the 9 taps x
-// 16x16 (out, in) tiles are spread over the 4 waves.
+// A block owns a 32-pixel row segment of one image over `rows` rows; K of the
+// product runs over its pixels.  The input rows (34 pixels, one more on each
+// side) pass through an LDS ring of 4, each loaded once, the error signal
+// through two buffers, both as they lie in memory ([pixel][channel]); a row's
+// loads are issued two rows ahead, one barrier per row.  The matrix operands
+// need the pixels along K, so they are read with the transposing LDS load
+// (ds_read_b64_tr_b16: of 16 lanes that point at 4 rows x 16 channels, lane i
+// gets channel i of the 4 rows); a tap's column shift is a shift of rows.
+// Wave wv keeps one (out, in) pair of 16-channel blocks (one of two or four
+// waves of a pair takes every second tap where there are only two pairs).
+// 8 images of 256^2, 32 to 32 channels: 24 us, 80 with the rows
+// transposed by 2-byte LDS stores in three shifted copies, three rows again
+// for every output row (the two activations read once are 14 us at the card's
+// copy rate).
 template <int CINP, int COUTP>
 __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
-    constexpr int CN = CINP < 16 ? 16 : CINP;
-    constexpr int MB = COUTP / 16, NB = CN / 16;
-    constexpr int NTILE = 9 * MB * NB;
-    constexpr int TPW = (NTILE + 3) / 4;
-    __shared__ __align__(16) unsigned short sG[COUTP][32];
-    __shared__ __align__(16) unsigned short sX[3][3][CN][32];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    constexpr int CN = CINP < 16 ? 16 : CINP;       // input channels of an LDS pixel
+    constexpr int MB = COUTP / 16, NB = CN / 16, PAIRS = MB * NB;
+    constexpr int WPP = 4 / PAIRS;                  // waves per pair
+    constexpr int TPW = (9 + WPP - 1) / WPP;        // taps per wave
+    // elements from one LDS pixel to the next: 96 bytes for 32 channels, so
+    // that the 4 rows of a transposing load fall on different banks
+    constexpr int SX = CN == 32 ? 48 : CN, SG = COUTP == 32 ? 48 : COUTP;
+    constexpr int NVX = 34 * CINP / 8, NVG = 32 * COUTP / 8;   // 16-byte vectors of a row
+    static_assert(PAIRS * WPP == 4 && NVX <= 256 && NVG <= 256, "four waves, one vector of each row per thread");
+    __shared__ __align__(16) unsigned short sX[4][34 * SX];
+    __shared__ __align__(16) unsigned short sG[2][32 * SG];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int pair = wv % PAIRS, sub = wv / PAIRS;
+    const int mb = pair / NB, nb = pair % NB;
     const int nxs = a.w / 32;
     const int nyb = (a.h + a.rows - 1) / a.rows;
     const int b = blockIdx.x;
@@ -384,102 +404,146 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
     const int64_t ibase = (int64_t)img * a.h;
 
     if (CN > CINP) {
-        for (int i = tid; i < 3 * 3 * (CN - CINP) * 32; i += 256) {
-            const int p = i % 32, c = CINP + (i / 32) % (CN - CINP), s = i / (32 * (CN - CINP));
-            sX[s / 3][s % 3][c][p] = 0;
+        // the channels past the input's stay 0
+        for (int i = tid; i < 4 * 34 * (CN - CINP); i += 256) {
+            const int c = CINP + i % (CN - CINP), r = i / (CN - CINP);
+            sX[r / 34][(r % 34) * SX + c] = 0;
         }
     }
-    f32x4 acc[TPW];
+    // this thread's vector of a row of each array (the G vectors go to the
+    // last threads, so that few have both)
+    const int vx = tid, vg = tid - (256 - NVG);
+    const bool hasx = vx < NVX, hasg = vg >= 0;
+    const int px = vx / (CINP / 8), cx = (vx % (CINP / 8)) * 8;
+    const int64_t xcol = (int64_t)wrapi(x0 + px - 1, a.w) * CINP + cx;
+    const int lx = px * SX + cx;
+    const int lg = (vg / (COUTP / 8)) * SG + (vg % (COUTP / 8)) * 8;
+    auto load_x = [&](int y) __attribute__((always_inline)) {
+        return hasx ? *(const u32x4 *)(a.x + (ibase + wrapi(y, a.h)) * a.w * CINP + xcol) : u32x4{0u, 0u, 0u, 0u};
+    };
+    auto load_g = [&](int y) __attribute__((always_inline)) {
+        return hasg ? *(const u32x4 *)(a.g + ((ibase + y) * a.w + x0) * COUTP + vg * 8) : u32x4{0u, 0u, 0u, 0u};
+    };
+    {
+        const u32x4 v0 = load_x(y0 - 1), v1 = load_x(y0), v2 = load_x(y0 + 1), g0 = load_g(y0);
+        if (hasx) {
+            *(u32x4 *)&sX[0][lx] = v0;
+            *(u32x4 *)&sX[1][lx] = v1;
+            *(u32x4 *)&sX[2][lx] = v2;
+        }
+        if (hasg) *(u32x4 *)&sG[0][lg] = g0;
+    }
+    __syncthreads();
+
+    // operand of 16 channels from channel c0 and the 8 pixels of this lane's
+    // group, from pixel row p0 of a row of `str` channels per pixel
+    const int kr = 8 * (lane >> 4) + ((lane >> 2) & 3), kc = 4 * (lane & 3);
+    auto frag = [&](const unsigned short *row, int str, int p0, int c0) __attribute__((always_inline)) {
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const unsigned short *q = row + (p0 + kr) * str + c0 + kc;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)q);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(q + 4 * str));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    f32x4 acc[TPW], accb = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < TPW; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float db = 0.0f;
+    // the bias gradient is the product with ones, by the waves of input block
+    // 0 and the first taps
+    const bool bias = nb == 0 && sub == 0;
+    const unsigned one2 = 0x3f803f80u;
+    const bf16x8 ones = as_bf(u32x4{one2, one2, one2, one2});
 
-    for (int y = y0; y < y1; ++y) {
-        __syncthreads();
-        for (int v = tid; v < 32 * (COUTP / 8); v += 256) {
-            const int p = v / (COUTP / 8), cg = v % (COUTP / 8);
-            const u32x4 d = *(const u32x4 *)(a.g + (((ibase + y) * a.w + x0 + p) * COUTP + cg * 8));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sG[cg * 8 + 2 * e][p] = (unsigned short)(d[e] & 0xffff);
-                sG[cg * 8 + 2 * e + 1][p] = (unsigned short)(d[e] >> 16);
-            }
-        }
-        for (int v = tid; v < 3 * 34 * (CINP / 8); v += 256) {
-            const int dyi = v / (34 * (CINP / 8));
-            const int rr = v - dyi * 34 * (CINP / 8);
-            const int r = rr / (CINP / 8) - 1, cg = rr % (CINP / 8);
-            const int yy = wrapi(y + dyi - 1, a.h), xx = wrapi(x0 + r, a.w);
-            const u32x4 d = *(const u32x4 *)(a.x + (((ibase + yy) * a.w + xx) * CINP + cg * 8));
-#pragma unroll
-            for (int dxi = 0; dxi < 3; ++dxi) {
-                const int p = r - (dxi - 1);
-                if (p >= 0 && p < 32) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        sX[dyi][dxi][cg * 8 + 2 * e][p] = (unsigned short)(d[e] & 0xffff);
-                        sX[dyi][dxi][cg * 8 + 2 * e + 1][p] = (unsigned short)(d[e] >> 16);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (tid < COUTP) {
-            float s = 0.0f;
-            for (int p = 0; p < 32; ++p) s += bf2f(sG[tid][p]);
-            db += s;
-        }
+    auto multiply = [&](int y) __attribute__((always_inline)) {
+        const bf16x8 av = frag(sG[(y - y0) & 1], SG, 0, mb * 16);
+        if (bias) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, ones, accb, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < TPW; ++i) {
-            const int tile = wv + 4 * i;
-            if (tile < NTILE) {
-                const int t = tile / (MB * NB), r2 = tile % (MB * NB);
-                const int mb = r2 / NB, nb = r2 % NB;
-                const u32x4 av = *(const u32x4 *)&sG[mb * 16 + (lane & 15)][8 * (lane >> 4)];
-                const u32x4 bv = *(const u32x4 *)&sX[t / 3][t % 3][nb * 16 + (lane & 15)][8 * (lane >> 4)];
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(av), as_bf(bv), acc[i], 0, 0, 0);
+            const int t = sub + WPP * i;
+            if (t < 9) {
+                const bf16x8 bv = frag(sX[(y - y0 + t / 3) & 3], SX, t % 3, nb * 16);
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[i], 0, 0, 0);
             }
         }
+    };
+    // row y+2 takes the slot of row y-2, the next error row the other buffer:
+    // neither has been read since the last barrier
+    auto store = [&](int y, const u32x4 &nx, const u32x4 &ng) __attribute__((always_inline)) {
+        if (hasx) *(u32x4 *)&sX[(y - y0 + 3) & 3][lx] = nx;
+        if (hasg) *(u32x4 *)&sG[(y + 1 - y0) & 1][lg] = ng;
+    };
+    // loads run two rows ahead, in two register sets taken in turn (past the
+    // last row they re-read it, unused)
+    u32x4 xa = load_x(min(y0 + 2, y1)), ga = load_g(min(y0 + 1, y1 - 1)), xb, gb;
+    for (int y = y0; y < y1; y += 2) {
+        xb = load_x(min(y + 3, y1));
+        gb = load_g(min(y + 2, y1 - 1));
+        multiply(y);
+        store(y, xa, ga);
+        __syncthreads();
+        if (y + 1 >= y1) break;
+        xa = load_x(min(y + 4, y1));
+        ga = load_g(min(y + 3, y1 - 1));
+        multiply(y + 1);
+        store(y + 1, xb, gb);
+        __syncthreads();
     }
     const int nw = a.cout * a.cin * 9;
     float *pp = a.part + (int64_t)b * (nw + a.cout);
+    const int c = nb * 16 + (lane & 15);
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
-        const int tile = wv + 4 * i;
-        if (tile < NTILE) {
-            const int t = tile / (MB * NB), r2 = tile % (MB * NB);
-            const int mb = r2 / NB, nb = r2 % NB;
-            const int c = nb * 16 + (lane & 15);
+        const int t = sub + WPP * i;
+        if (t < 9) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int o = mb * 16 + 4 * (lane >> 4) + e;
-                if (o < a.cout && c < a.cin) pp[(o * a.cin + c) * 9 + t] = acc[i][e];
+                if (o < a.cout && c < a.cin) pp[(t * a.cout + o) * a.cin + c] = acc[i][e];
             }
         }
     }
-    if (tid < a.cout) pp[nw + tid] = db;
+    if (bias && (lane & 15) == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int o = mb * 16 + 4 * (lane >> 4) + e;
+            if (o < a.cout) pp[nw + o] = accb[e];
+        }
+    }
 }
 
-// fixed-order sum of the per-block partials, in two levels: group g of
-// blockIdx.y sums blocks [g*chunk, min((g+1)*chunk, nblocks)) in order and
-// leaves its sum in the first row of its chunk; k_reduce2 then sums the group
-// sums in order.  Each column is read and written by one thread only.
-__global__ void k_reduce(float *__restrict__ part, int nblocks, int np, int chunk) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b0 = blockIdx.y * chunk;
-    if (i >= np || b0 >= nblocks) return;
-    const int b1 = min(b0 + chunk, nblocks);
-    float s = 0.0f;
-    for (int b = b0; b < b1; ++b) s += part[(int64_t)b * np + i];
-    part[(int64_t)b0 * np + i] = s;
-}
-
-__global__ void k_reduce2(const float *__restrict__ part, int nblocks, int np, int chunk, float *__restrict__ dst) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np) return;
-    float s = 0.0f;
-    for (int b0 = 0; b0 < nblocks; b0 += chunk) s += part[(int64_t)b0 * np + i];
-    dst[i] = s;
+// Fixed-order sum of the per-block partials: groups of `chunk` consecutive
+// blocks (at most 64) are summed in order, then the group sums in order.  A
+// block takes 64 columns, its 16 waves the groups in turn.  (As two launches,
+// the second with one thread per column: 11.4 + 17.4 us at 1024 blocks x 9248
+// columns, under 10 us now; the partials are 38 MB.)
+// The taps go from the slowest index of a partial to the fastest of dst.
+__global__ __launch_bounds__(1024) void k_reduce(const float *__restrict__ part, int nblocks, int np, int oc, int chunk,
+                                                 float *__restrict__ dst) {
+    __shared__ float sum[64][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
+    const int groups = (nblocks + chunk - 1) / chunk;
+    const float *col = part + min(i, np - 1);
+    for (int g = wv; g < groups; g += 16) {
+        const int b0 = g * chunk, b1 = min(b0 + chunk, nblocks);
+        float s = 0.0f;
+        int bk = b0;
+        for (; bk + 8 <= b1; bk += 8) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = col[(int64_t)(bk + k) * np];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += v[k];
+        }
+        for (; bk < b1; ++bk) s += col[(int64_t)bk * np];
+        sum[g][lane] = s;
+    }
+    __syncthreads();
+    if (wv == 0 && i < np) {
+        float s = 0.0f;
+        for (int g = 0; g < groups; ++g) s += sum[g][lane];
+        dst[i < 9 * oc ? (i % oc) * 9 + i / oc : i] = s;
+    }
 }
 
 // ------------------------------------------------------------- Adam
@@ -497,11 +561,12 @@ __global__ void k_adam(float *__restrict__ th, float *__restrict__ m, float *__r
 }
 
 // ------------------------------------------------------------- host side
-// output rows per block: about 2048 blocks (a few per compute unit), at
+// output rows per block: about 1024 blocks (four per compute unit, one round:
+// 8 images of 256^2, 32 to 32 channels, 19.3 us, 22.2 with 2048 blocks), at
 // least 4 rows (each strip re-reads two apron rows)
 static int conv_rows(int n, int h, int w) {
     const int64_t strips = (int64_t)n * ((w + kStrip - 1) / kStrip);
-    const int64_t r = (strips * h + 2047) / 2048;
+    const int64_t r = (strips * h + 1023) / 1024;
     return (int)std::min<int64_t>(h, std::max<int64_t>(4, r));
 }
 
@@ -657,10 +722,7 @@ static int cnn_backward_on(const void *d_packed, const void *d_x, const void *d_
         const int np = cout_of(l) * cin_of(l) * 9 + cout_of(l);
         {
             const int chunk = std::max(1, (nbw + 63) / 64);   // at most 64 groups
-            const int groups = (nbw + chunk - 1) / chunk;
-            k_reduce<<<dim3((np + 255) / 256, groups), 256, 0, s>>>(part, nbw, np, chunk);
-            HIPCHK(hipGetLastError());
-            k_reduce2<<<(np + 255) / 256, 256, 0, s>>>(part, nbw, np, chunk, d_grad + woff(l));
+            k_reduce<<<(np + 63) / 64, 1024, 0, s>>>(part, nbw, np, cout_of(l) * cin_of(l), chunk, d_grad + woff(l));
             HIPCHK(hipGetLastError());
         }
         if (l > 0) {

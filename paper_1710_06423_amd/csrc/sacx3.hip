@@ -130,13 +130,18 @@ struct Stage3Args {
     int cross;
 };
 
-// The chip hands consecutive blocks to its 8 XCDs in turn; blocks are
-// renumbered so that runs of 4 neighbouring tiles share one XCD (and its L2)
-// for the apron they both read.  A bijection of the block indices.
-__device__ __forceinline__ int xcd_block() {
-    const int n = (int)gridDim.x, b = (int)blockIdx.x;
-    const int x = b % 8, i = b / 8;
-    return b < n - n % 32 ? ((i / 4) * 8 + x) * 4 + i % 4 : b;
+// The chip hands consecutive blocks to its 8 XCDs in turn.  Blocks are
+// renumbered within each strip of planes so that every XCD gets one contiguous
+// run of the strip's tiles in row-major order, a patch a few tile rows high:
+// the apron that neighbouring tiles share, along x and along y, is then read
+// into one L2.  A bijection of the block indices (the remainder of a strip's
+// tiles by 8 goes to its first XCDs).
+__device__ __forceinline__ int xcd_block(int tiles) {
+    const int b = (int)blockIdx.x, strip = b / tiles, i = b - strip * tiles;
+    // the XCD is that of the launch's block index; which one a strip starts
+    // with does not matter for the runs
+    const int x = i % 8, k = i / 8, q = tiles / 8, r = tiles % 8;
+    return strip * tiles + (x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k);
 }
 
 // Global accesses take a wave-uniform array base plus a 32-bit per-lane byte
@@ -169,7 +174,7 @@ __global__ __launch_bounds__(TX *TY, 2) void k3_faces(Face3Args a) {
     const Layout3 L = a.L;
     const Consts3 &kc = a.k;
     const int64_t fs = a.fs;
-    const int blk = xcd_block();
+    const int blk = xcd_block(a.ntx * a.nty);
     const int X0 = -1 + (blk % a.ntx) * TX;
     const int Y0 = -1 + ((blk / a.ntx) % a.nty) * TY;
     const int zb = -1 + (blk / (a.ntx * a.nty)) * a.tz;
@@ -404,7 +409,7 @@ __global__ __launch_bounds__(TX *TY, 1) void k3_stage(Stage3Args a) {
     const Layout3 L = a.L;
     const Consts3 &kc = a.k;
     const int64_t fs = a.fs;
-    const int blk = xcd_block();
+    const int blk = xcd_block(a.ntx * a.nty);
     const int X0 = (blk % a.ntx) * TX;
     const int Y0 = ((blk / a.ntx) % a.nty) * TY;
     const int zb = (blk / (a.ntx * a.nty)) * a.tz;

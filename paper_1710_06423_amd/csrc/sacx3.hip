@@ -311,27 +311,289 @@ __global__ __launch_bounds__(TX *TY, 2) void k3_faces(Face3Args a) {
 
 // ---------------------------------------------------------------- stage launch
 
-template <int TX, int TY, bool HD>
-struct StageLds3 {
-    double pr[7][TY + 4][TX + 4];   // rho, v_x, v_y, v_z, B_x, B_y, B_z of plane r
+// state -> primitives, and the parts that every flux of the cell shares
+struct Cell3 {
+    double rt, mx, my, mz, et, bx, by, bz, ux, uy, uz, pt, bv, ef;
+};
+
+__device__ __forceinline__ Cell3 cell3(const double (&s)[NF3], double gm1) {
+    const double half = 0.5;
+    Cell3 c;
+    c.rt = s[FR]; c.mx = s[FMX]; c.my = s[FMY]; c.mz = s[FMZ]; c.et = s[FE];
+    c.bx = s[FBX]; c.by = s[FBY]; c.bz = s[FBZ];
+    const double ir = 1.0 / c.rt;
+    c.ux = c.mx * ir; c.uy = c.my * ir; c.uz = c.mz * ir;
+    const double kin = half * ((c.mx * c.ux + c.my * c.uy) + c.mz * c.uz);
+    const double b2 = (c.bx * c.bx + c.by * c.by) + c.bz * c.bz;
+    const double pk = gm1 * ((c.et - kin) - half * b2);
+    c.pt = pk + half * b2;
+    c.bv = (c.bx * c.ux + c.by * c.uy) + c.bz * c.uz;
+    c.ef = c.et + c.pt;
+    return c;
+}
+
+// z fluxes of rho, m_x, m_y, m_z, e, B_x, B_y
+__device__ __forceinline__ void zflux(const Cell3 &c, double (&f)[7]) {
+    f[0] = c.mz;
+    f[1] = c.uz * c.mx - c.bz * c.bx;
+    f[2] = c.uz * c.my - c.bz * c.by;
+    f[3] = (c.uz * c.mz - c.bz * c.bz) + c.pt;
+    f[4] = c.uz * c.ef - c.bz * c.bv;
+    f[5] = c.uz * c.bx - c.bz * c.ux;
+    f[6] = c.uz * c.by - c.bz * c.uy;
+}
+
+// rho, v, B of a plane's tile and apron, and its x and y fluxes
+template <int TX, int TY>
+struct PlaneLds3 {
     double fx[7][TY + 4][TX + 4];   // x fluxes of rho, m_x, m_y, m_z, e, B_y, B_z
     double fy[7][TY + 4][TX + 4];   // y fluxes of rho, m_x, m_y, m_z, e, B_x, B_z
-    // with hyper-diffusion, the face quantities the x- and y-face fluxes of
-    // plane r read, staged from the face arrays once per plane: element
-    // [.][j][i] is the face stored at (X0 - 2 + i, Y0 - 1 + j).  Rows are
-    // GW = TX + 4 doubles, filled as 16-byte pairs from an even x, 128
-    // doubles per wave instruction; each tile is padded to whole instructions.
-    static constexpr int HX = HD ? TX : 0, HY = HD ? TY : 0, GW = HD ? TX + 4 : 2;
+    double red[4][TX * TY / 64];
+};
+
+template <class Lds>
+__device__ __forceinline__ void put_fluxes(Lds &lds, int by, int bx, const Cell3 &c) {
+    lds.fx[0][by][bx] = c.mx;
+    lds.fx[1][by][bx] = (c.ux * c.mx - c.bx * c.bx) + c.pt;
+    lds.fx[2][by][bx] = c.ux * c.my - c.bx * c.by;
+    lds.fx[3][by][bx] = c.ux * c.mz - c.bx * c.bz;
+    lds.fx[4][by][bx] = c.ux * c.ef - c.bx * c.bv;
+    lds.fx[5][by][bx] = c.ux * c.by - c.bx * c.uy;
+    lds.fx[6][by][bx] = c.ux * c.bz - c.bx * c.uz;
+    lds.fy[0][by][bx] = c.my;
+    lds.fy[1][by][bx] = c.uy * c.mx - c.by * c.bx;
+    lds.fy[2][by][bx] = (c.uy * c.my - c.by * c.by) + c.pt;
+    lds.fy[3][by][bx] = c.uy * c.mz - c.by * c.bz;
+    lds.fy[4][by][bx] = c.uy * c.ef - c.by * c.bv;
+    lds.fy[5][by][bx] = c.uy * c.bx - c.by * c.ux;
+    lds.fy[6][by][bx] = c.uy * c.bz - c.by * c.uz;
+}
+
+// box position of apron point i (TY + 4 rows of TX + 4 columns without the
+// TY x TX tile at (2, 2))
+template <int TX, int TY>
+__device__ __forceinline__ void frame_point(int i, int &bx, int &by) {
+    constexpr int BX = TX + 4;
+    if (i < 2 * BX) { by = i / BX; bx = i % BX; }
+    else if (i < 4 * BX) { by = TY + 2 + (i - 2 * BX) / BX; bx = (i - 2 * BX) % BX; }
+    else { const int j = i - 4 * BX, c4 = j % 4; by = 2 + j / 4; bx = c4 < 2 ? c4 : TX + c4; }
+}
+
+// -(D_x F_x + D_y F_y + D_z F_z) of the own cell: x and y fluxes from LDS, the
+// z fluxes of planes r-2 .. r+2 (w, fzn)
+template <class Lds>
+__device__ __forceinline__ void ideal_terms(const Lds &lds, int by, int bx, const Consts3 &kc,
+                                            const double (&w)[4][7], const double (&fzn)[7], double (&K)[NF3]) {
+    const double eight = 8.0, zero = 0.0;
+    double ax[7], ay[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        ax[k] = (eight * (lds.fx[k][by][bx + 1] - lds.fx[k][by][bx - 1]) -
+                 (lds.fx[k][by][bx + 2] - lds.fx[k][by][bx - 2])) * kc.i12[0];
+        ay[k] = (eight * (lds.fy[k][by + 1][bx] - lds.fy[k][by - 1][bx]) -
+                 (lds.fy[k][by + 2][bx] - lds.fy[k][by - 2][bx])) * kc.i12[1];
+    }
+    double ab[NF3], ez[NF3];
+    ab[FR] = ax[0] + ay[0];
+    ab[FMX] = ax[1] + ay[1];
+    ab[FMY] = ax[2] + ay[2];
+    ab[FMZ] = ax[3] + ay[3];
+    ab[FE] = ax[4] + ay[4];
+    ab[FBX] = zero + ay[5];
+    ab[FBY] = ax[5] + zero;
+    ab[FBZ] = ax[6] + ay[6];
+#pragma unroll
+    for (int f = 0; f < 7; ++f) ez[f] = (eight * (w[3][f] - w[1][f]) - (fzn[f] - w[0][f])) * kc.i12[2];
+    ez[FBZ] = zero;
+#pragma unroll
+    for (int f = 0; f < NF3; ++f) K[f] = -(ab[f] + ez[f]);
+}
+
+// wave speeds and physicality of the states a thread wrote at stage 4
+struct Speeds3 {
+    double c[3] = {0.0, 0.0, 0.0};
+    int bad = 0;
+    __device__ __forceinline__ void add(const double (&un)[NF3], double gm1, double gamma) {
+        const double half = 0.5;
+        const double ir = 1.0 / un[FR];
+        const double ux = un[FMX] * ir, uy = un[FMY] * ir, uz = un[FMZ] * ir;
+        const double kin = half * ((un[FMX] * ux + un[FMY] * uy) + un[FMZ] * uz);
+        const double b2 = (un[FBX] * un[FBX] + un[FBY] * un[FBY]) + un[FBZ] * un[FBZ];
+        const double pk = gm1 * ((un[FE] - kin) - half * b2);
+        const double cf = sqrt((gamma * pk + b2) * ir);
+        bool fin = isfinite(cf);
+#pragma unroll
+        for (int f = 0; f < NF3; ++f) fin = fin && isfinite(un[f]);
+        if (!(un[FR] > 0.0) || !(pk > 0.0) || !fin) {
+            bad = 1;
+        } else {
+            c[0] = fmax(c[0], fabs(ux) + cf);
+            c[1] = fmax(c[1], fabs(uy) + cf);
+            c[2] = fmax(c[2], fabs(uz) + cf);
+        }
+    }
+    // one result per wave into red (wave wv)
+    template <int NW>
+    __device__ __forceinline__ void reduce(double (&red)[4][NW], int wv, int lane) {
+        for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) c[d] = fmax(c[d], __shfl_xor(c[d], off));
+            bad |= __shfl_xor(bad, off);
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) red[d][wv] = c[d];
+            red[3][wv] = (double)bad;
+        }
+    }
+};
+
+template <int NW>
+__device__ __forceinline__ void raise_speeds(const double (&red)[4][NW], Dev3 *sc) {
+    double m[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < NW; ++k)
+        for (int d = 0; d < 4; ++d) m[d] = fmax(m[d], red[d][k]);
+    const int ns = sc->cur ^ 1;
+    for (int d = 0; d < 3; ++d) sacx::raise_max(&sc->cacc[ns][d], m[d]);
+    if (m[3] > 0.0) atomicOr(&sc->nonphys, 1);
+}
+
+// the RK4 combine of the own cell at byte offset o: so is the stage input,
+// uo U (stages 2, 3) or A (stage 4); un is the state written at stage 4
+template <int STAGE>
+__device__ __forceinline__ void combine3(const Stage3Args &a, int64_t fs, uint32_t o, const double (&so)[NF3],
+                                         const double (&uo)[NF3], const double (&K)[NF3], double dt, double hdt,
+                                         double dt6, double (&un)[NF3]) {
+#pragma unroll
+    for (int f = 0; f < NF3; ++f) {
+        if (STAGE == 1) {
+            sto(a.out1 + f * fs, o, so[f] + hdt * K[f]);
+        } else if (STAGE == 2) {
+            const double u = uo[f], sv = so[f];
+            sto(a.out1 + f * fs, o, u + hdt * K[f]);
+            sto(a.out2 + f * fs, o, (u + u) + ((sv - u) + dt * K[f]));
+        } else if (STAGE == 3) {
+            sto(a.out1 + f * fs, o, uo[f] + dt * K[f]);
+        } else {
+            const double av = uo[f], sv = so[f];
+            un[f] = (sv + (av - (sv + sv)) * a.k.third) + dt6 * K[f];
+            sto(a.out1 + f * fs, o, un[f]);
+        }
+    }
+}
+
+// without hyper-diffusion: one thread per column of the tile
+template <int STAGE, int TX, int TY>
+__global__ __launch_bounds__(TX *TY, 1) void k3_stage(Stage3Args a) {
+    __shared__ PlaneLds3<TX, TY> lds;
+    constexpr int BX = TX + 4, BY = TY + 4;
+    constexpr int NFRAME = BX * BY - TX * TY;
+    Dev3 *sc = a.sc;
+    if (!sc->active) return;
+    const Layout3 L = a.L;
+    const Consts3 &kc = a.k;
+    const int64_t fs = a.fs;
+    const int blk = xcd_block(a.ntx * a.nty);
+    const int X0 = (blk % a.ntx) * TX;
+    const int Y0 = ((blk / a.ntx) % a.nty) * TY;
+    const int zb = (blk / (a.ntx * a.nty)) * a.tz;
+    const int ze = min(zb + a.tz, L.nz);
+    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+    const int x = X0 + tx, y = Y0 + ty;
+    const bool colv = x < L.nx && y < L.ny;
+    const double dt = sc->dt, hdt = sc->hdt, dt6 = sc->dt6;
+    const double *usrc = STAGE == 4 ? a.A : a.U;
+    // the streamed column: the thread's own (x, y), clamped into the ghost
+    // layers like every box point
+    const int cx = min(x, L.nx + G - 1), cy = min(y, L.ny + G - 1);
+    auto column = [&](int k, double (&s)[NF3]) __attribute__((always_inline)) {
+        const uint32_t o = L.off(cx, cy, k);
+#pragma unroll
+        for (int f = 0; f < NF3; ++f) s[f] = ldo(a.S + f * fs, o);
+    };
+    double fzw[4][7];   // z fluxes of planes r-2..r+1
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        double s[NF3];
+        column(zb - 2 + m, s);
+        zflux(cell3(s, kc.gm1), fzw[m]);
+    }
+    Speeds3 sp;
+    // state of the own column, plane r+2, loaded one plane early
+    double psn[NF3];
+    column(zb + 2, psn);
+
+    for (int r = zb; r < ze; ++r) {
+        double so[NF3];   // own cell's stage input (the combine's pointwise operand)
+        for (int p = tid; p < TX * TY + NFRAME; p += TX * TY) {
+            int bx = tx + 2, by = ty + 2;
+            if (p >= TX * TY) frame_point<TX, TY>(p - TX * TY, bx, by);
+            const int gx = clampi(X0 - 2 + bx, -G, L.nx + G - 1), gy = clampi(Y0 - 2 + by, -G, L.ny + G - 1);
+            const uint32_t o = L.off(gx, gy, r);
+            double s[NF3];
+#pragma unroll
+            for (int f = 0; f < NF3; ++f) s[f] = ldo(a.S + f * fs, o);
+            if (p < TX * TY) {
+#pragma unroll
+                for (int f = 0; f < NF3; ++f) so[f] = s[f];
+            }
+            put_fluxes(lds, by, bx, cell3(s, kc.gm1));
+        }
+        __syncthreads();
+        double fzn[7];
+        zflux(cell3(psn, kc.gm1), fzn);
+        column(r + 3, psn);   // past the block's last plane: ghost planes, unused
+        __builtin_amdgcn_sched_barrier(0);
+        if (colv) {
+            double K[NF3], uo[NF3], un[NF3];
+            ideal_terms(lds, ty + 2, tx + 2, kc, fzw, fzn, K);
+            const uint32_t oo = L.off(x, y, r);
+            if (STAGE > 1) {
+#pragma unroll
+                for (int f = 0; f < NF3; ++f) uo[f] = ldo(usrc + f * fs, oo);
+            }
+            combine3<STAGE>(a, fs, oo, so, uo, K, dt, hdt, dt6, un);
+            if (STAGE == 4) sp.add(un, kc.gm1, kc.gamma);
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            fzw[0][k] = fzw[1][k]; fzw[1][k] = fzw[2][k]; fzw[2][k] = fzw[3][k]; fzw[3][k] = fzn[k];
+        }
+        __syncthreads();
+    }
+
+    if (STAGE == 4) {
+        sp.reduce(lds.red, tid >> 6, tid & 63);
+        __syncthreads();
+        if (tid == 0) raise_speeds(lds.red, sc);
+    }
+}
+
+template <int TX, int TY>
+struct StageLds3 {
+    double pr[7][TY + 4][TX + 4];   // rho, v_x, v_y, v_z, B_x, B_y, B_z of plane r
+    double fx[7][TY + 4][TX + 4];   // as in PlaneLds3
+    double fy[7][TY + 4][TX + 4];
+    // the face quantities the face fluxes of plane r read, staged from the
+    // face arrays once per plane: element [.][j][i] is the face stored at
+    // (X0 - 2 + i, Y0 - 1 + j).  Rows are GW = TX + 4 doubles, filled as
+    // 16-byte pairs from an even x, 128 doubles per wave instruction; each
+    // tile is padded to whole instructions.
+    static constexpr int GW = TX + 4;
     static constexpr int fill128(int rows) { return (rows * GW + 127) / 128 * 128; }
     struct GzTile {
-        alignas(16) double v[4][HY + 2][GW];   // G_z of v_x, B_x, v_y, B_y
-        double pad[fill128(4 * (HY + 2)) - 4 * (HY + 2) * GW + 2];
+        alignas(16) double v[4][TY + 2][GW];   // G_z of v_x, B_x, v_y, B_y
+        double pad[fill128(4 * (TY + 2)) - 4 * (TY + 2) * GW + 2];
     };
-    alignas(16) double gx[NQF][HY + 2][GW];    // G_x, all seven, plane r
-    double gx_pad[fill128(NQF * (HY + 2)) - NQF * (HY + 2) * GW + 2];
-    alignas(16) double gy[NQF][HY + 1][GW];    // G_y, all seven, plane r
-    double gy_pad[fill128(NQF * (HY + 1)) - NQF * (HY + 1) * GW + 2];
+    alignas(16) double gx[NQF][TY + 2][GW];    // G_x, all seven, plane r
+    double gx_pad[fill128(NQF * (TY + 2)) - NQF * (TY + 2) * GW + 2];
+    alignas(16) double gy[NQF][TY + 1][GW];    // G_y, all seven, plane r
+    double gy_pad[fill128(NQF * (TY + 1)) - NQF * (TY + 1) * GW + 2];
     GzTile gz[2];                              // planes r-1 and r (by parity)
+    // between the roles, one slot per column: rho, v, B of plane r+1 for the
+    // H role's z face, then the hyper-diffusive terms of plane r for the P
+    // role.  A slot is used by one thread of each role, in turn.
+    double ex[NF3][TX * TY];
     double red[4][TX * TY / 64];
 };
 
@@ -339,8 +601,8 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void glb_void;
 
 // Fill an LDS tile of face quantities with loads that write LDS directly: no
-// registers are held, and the loads overlap whatever the block does until its
-// next barrier (which waits for them).  The tile holds NQ quantities x H rows
+// registers hold the data, and the loads overlap whatever the wave does until
+// it waits for them.  The tile holds NQ quantities x H rows
 // x GW columns; row j of quantity q is slot q of direction d (for the G_z
 // tile, its q-th of v_x, B_x, v_y, B_y) at y = Y0 - 1 + j, x = X0 - 2 ..
 // X0 - 3 + GW, plane k.  Lane l of a wave instruction moves the pair p =
@@ -349,21 +611,34 @@ typedef __attribute__((address_space(1))) void glb_void;
 // tile repeat its last pair into the padding.  Positions past the ghost
 // layers read whatever follows in the array (a later row or plane: staged
 // planes end at n_z - 1 and three ghost planes follow); no output reads them.
+// Wave wv of NWAVE takes the instructions wv, wv + NWAVE, ...; their sources
+// are formed once (for the first plane) and moved up plane by plane.
 template <int NQ, int H, int GW, bool ZSEL, int NWAVE>
-__device__ __forceinline__ void dma_tile(double *dst, const double *Gf, int64_t fs, const Layout3 &L, int d, int X0,
-                                         int Y0, int k, int wv, int lane) {
-    constexpr int PR = GW / 2, NP = NQ * H * PR, NCH = (NP + 63) / 64;
+struct dma_tile {
+    static constexpr int PR = GW / 2, NP = NQ * H * PR, NCH = (NP + 63) / 64, NI = (NCH + NWAVE - 1) / NWAVE;
     static_assert(GW % 2 == 0, "rows are filled in pairs");
-#pragma unroll 1
-    for (int c = wv; c < NCH; c += NWAVE) {
-        const int p = min(c * 64 + lane, NP - 1);
-        const int row = p / PR, pr = p - row * PR;
-        const int q = row / H, j = row - q * H;
-        const int qs = ZSEL ? (q == 0 ? GVX : (q == 1 ? GB1 : (q == 2 ? GVY : GB2))) : q;
-        const char *src = (const char *)(Gf + (int64_t)(NQF * d + qs) * fs) + L.off(X0 - 2 + 2 * pr, Y0 - 1 + j, k);
-        __builtin_amdgcn_global_load_lds((glb_void *)src, (lds_void *)(dst + c * 128), 16, 0, 0);
+    const char *src[NI];
+    __device__ __forceinline__ dma_tile(const double *Gf, int64_t fs, const Layout3 &L, int d, int X0, int Y0, int k,
+                                        int wv, int lane) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int p = min((wv + i * NWAVE) * 64 + lane, NP - 1);
+            const int row = p / PR, pr = p - row * PR;
+            const int q = row / H, j = row - q * H;
+            const int qs = ZSEL ? (q == 0 ? GVX : (q == 1 ? GB1 : (q == 2 ? GVY : GB2))) : q;
+            src[i] = (const char *)(Gf + (int64_t)(NQF * d + qs) * fs) + L.off(X0 - 2 + 2 * pr, Y0 - 1 + j, k);
+        }
     }
-}
+    // fill dst from the current plane and move to the next
+    __device__ __forceinline__ void fill(double *dst, int wv, uint32_t plane_bytes) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int c = wv + i * NWAVE;
+            if (c < NCH) __builtin_amdgcn_global_load_lds((glb_void *)src[i], (lds_void *)(dst + c * 128), 16, 0, 0);
+            src[i] += plane_bytes;
+        }
+    }
+};
 
 // the eight face fluxes of one face from its seven G values, the cross-term
 // means A4 of the two other directions (first, second in x, y, z order) and
@@ -399,11 +674,45 @@ __device__ __forceinline__ FaceFlux face_flux(const double (&g)[NQF], double a4v
     return H;
 }
 
-template <int STAGE, bool HD, int TX, int TY>
-__global__ __launch_bounds__(TX *TY, 1) void k3_stage(Stage3Args a) {
-    __shared__ StageLds3<TX, TY, HD> lds;
-    constexpr int BX = TX + 4, BY = TY + 4;
-    constexpr int NFRAME = BX * BY - TX * TY;
+// LDS between the roles: the wave's own LDS accesses are complete before it
+// arrives, loads from memory stay in flight (the fills of the face tiles are
+// waited for where they are needed, by the waves that issued them)
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// pins a value's computation here: without it the compiler moves arithmetic
+// down to the value's use and holds all operands until then
+__device__ __forceinline__ void settle(double &v) { asm volatile("" : "+v"(v)); }
+template <int N>
+__device__ __forceinline__ void settle(double (&v)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) settle(v[k]);
+}
+
+// With hyper-diffusion a tile's columns have two threads each, in different
+// waves: the P role (waves 0 .. NW-1) keeps the column's states and z fluxes,
+// takes the ideal terms and the combine; the H role fills the face tiles,
+// takes the apron of the plane and all face fluxes of the cell.
+//
+// Bound by latency and memory: per cell it reads the 8 fields, the 21 face
+// quantities and at stages 2-4 the 8 stored operands, and writes 8 or 16
+// values.  With one thread per column it took 256 VGPRs, 148-190 AGPRs and so
+// one wave per SIMD, whose waves waited in 42 % of their cycles; each plane's
+// state was also read twice (for the plane's x and y terms, and two planes
+// early for the z fluxes).  Two roles with a loop each fit two waves per SIMD
+// (215-225 VGPRs, 153 KB of LDS), and the P role has the registers to keep a
+// state until its plane comes.  256^3 FP64, per launch: 2.65-3.0 -> 1.67-2.0 ms;
+// two whole steps 35.78 -> 27.68 ms; five of 75 x 53 x 61: 2.52 -> 2.03 ms.
+template <int STAGE, int TX, int TY>
+__global__ __launch_bounds__(2 * TX *TY, 1) void k3_stage_hd(Stage3Args a) {
+    __shared__ StageLds3<TX, TY> lds;
+    constexpr int BX = TX + 4, BY = TY + 4, NCOL = TX * TY, NW = NCOL / 64;
+    constexpr int NFRAME = BX * BY - NCOL;
+    static_assert(NFRAME <= NCOL, "one apron point per thread of the H role");
     Dev3 *sc = a.sc;
     if (!sc->active) return;
     const Layout3 L = a.L;
@@ -414,402 +723,281 @@ __global__ __launch_bounds__(TX *TY, 1) void k3_stage(Stage3Args a) {
     const int Y0 = ((blk / a.ntx) % a.nty) * TY;
     const int zb = (blk / (a.ntx * a.nty)) * a.tz;
     const int ze = min(zb + a.tz, L.nz);
-    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int x = X0 + tx, y = Y0 + ty;
-    const bool colv = x < L.nx && y < L.ny;
-    const int xc = min(x, L.nx - 1), yc = min(y, L.ny - 1);   // column clamped into the cells
-    const double gm1 = kc.gm1;
-    const double half = 0.5, eight = 8.0;
-    const double dt = sc->dt, hdt = sc->hdt, dt6 = sc->dt6;
-    const bool cross = a.cross != 0;
-    const double *Gf = a.Gf;
-    auto garr = [&](int d, int q) { return Gf + (int64_t)(NQF * d + q) * fs; };
+    const int wvb = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const bool prole = wvb < NW;
+    const int wv = prole ? wvb : wvb - NW;
+    const int tid = wv * 64 + lane, tx = tid % TX, ty = tid / TX;
+    const int x = X0 + tx, y = Y0 + ty, bx = tx + 2, by = ty + 2;
+    const double half = 0.5;
 
-    // The own column's z fluxes and rho, v, B are streamed two planes ahead
-    // of the plane being finished: at iteration r its z fluxes cover planes
-    // r-2..r+2 and its rho, v, B planes r..r+2, so the z difference and the
-    // z face above plane r are complete when plane r's x and y terms are.
-    // (The state of plane r+2 is read again when plane r+2 is finished;
-    // keeping it in registers for two planes would spill.)
-    double fzw[4][7];   // z fluxes (rho, m_x, m_y, m_z, e, B_x, B_y) of planes r-2..r+1
-    double pq[2][7];    // rho, v, B of planes r, r+1
-    double hzp[NF3];    // H_z of face (r-1)+1/2
+    if (prole) {
+        const bool colv = x < L.nx && y < L.ny;
+        const int xc = min(x, L.nx - 1), yc = min(y, L.ny - 1);   // column clamped into the cells
+        // the streamed column: the thread's own (x, y), clamped into the
+        // ghost layers like every box point, so that columns past the last
+        // cell hold the ghost values their neighbours difference
+        const int cx = min(x, L.nx + G - 1), cy = min(y, L.ny + G - 1);
+        const double dt = sc->dt, hdt = sc->hdt, dt6 = sc->dt6;
+        const double *usrc = STAGE == 4 ? a.A : a.U;
+        auto column = [&](int k, double (&s)[NF3]) __attribute__((always_inline)) {
+            const uint32_t o = L.off(cx, cy, k);
 #pragma unroll
-    for (int f = 0; f < NF3; ++f) hzp[f] = 0.0;
+            for (int f = 0; f < NF3; ++f) s[f] = ldo(a.S + f * fs, o);
+        };
+        auto operand = [&](int k, double (&u)[NF3]) __attribute__((always_inline)) {
+            const uint32_t o = L.off(xc, yc, k);
 #pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        pq[0][k] = pq[1][k] = 0.0;
+            for (int f = 0; f < NF3; ++f) u[f] = ldo(usrc + f * fs, o);
+        };
+        auto hand = [&](const Cell3 &c) __attribute__((always_inline)) {
+            lds.ex[0][tid] = c.rt;
+            lds.ex[1][tid] = c.ux; lds.ex[2][tid] = c.uy; lds.ex[3][tid] = c.uz;
+            lds.ex[4][tid] = c.bx; lds.ex[5][tid] = c.by; lds.ex[6][tid] = c.bz;
+        };
+        double fzw[4][7];                  // z fluxes of planes r-2..r+1
+        double s0[NF3], s1[NF3], s2[NF3];  // the column's states of planes r, r+1, r+2
+        double uo[NF3];                    // the combine's stored operand of plane r
+        column(zb - 2, s0);
+        column(zb - 1, s1);
+        zflux(cell3(s0, kc.gm1), fzw[0]);
+        zflux(cell3(s1, kc.gm1), fzw[1]);
+        column(zb, s0);
+        column(zb + 1, s1);
+        column(zb + 2, s2);
+        zflux(cell3(s0, kc.gm1), fzw[2]);
+        const Cell3 c1 = cell3(s1, kc.gm1);
+        zflux(c1, fzw[3]);
+        hand(c1);
+        if (STAGE > 1) operand(zb, uo);
+        Speeds3 sp;
+        for (int r = zb; r < ze; ++r) {
+            const Cell3 c = cell3(s0, kc.gm1);
+            lds.pr[0][by][bx] = c.rt;
+            lds.pr[1][by][bx] = c.ux; lds.pr[2][by][bx] = c.uy; lds.pr[3][by][bx] = c.uz;
+            lds.pr[4][by][bx] = c.bx; lds.pr[5][by][bx] = c.by; lds.pr[6][by][bx] = c.bz;
+            put_fluxes(lds, by, bx, c);
+            lds_barrier();
+            // state of plane r+3 (past the block's last plane: ghost planes,
+            // unused), consumed one plane later
+            double s3[NF3], fzn[7], K[NF3], un[NF3];
+            column(r + 3, s3);
+            const Cell3 c2 = cell3(s2, kc.gm1);
+            zflux(c2, fzn);
+            settle(fzn);
+            ideal_terms(lds, by, bx, kc, fzw, fzn, K);
+            settle(K);
+            lds_barrier();
 #pragma unroll
-        for (int m = 0; m < 4; ++m) fzw[m][k] = 0.0;
-    }
-    double cx_t = 0.0, cy_t = 0.0, cz_t = 0.0;
-    int bad_t = 0;
-    // the streamed column: the thread's own (x, y), clamped into the ghost
-    // layers like every box point, so that columns past the last cell hold
-    // the ghost values their neighbours difference
-    const int cx = min(x, L.nx + G - 1), cy = min(y, L.ny + G - 1);
-    const uint32_t sy = (uint32_t)L.pitch * 8u, sz = (uint32_t)(L.plane * 8);   // byte strides
-
-    // The own column's loads that a plane consumes after its tile work (its
-    // state two planes ahead, the G of H_z and, at stages 2-4, the combine's
-    // stored operand) are issued one plane early, as soon as the previous
-    // plane has consumed its own, into registers consumed in place: they
-    // land during that plane's x and y terms, and no barrier waits for them
-    // before the next plane's tile barrier.  Past the block's last plane
-    // they read ghost planes, unused.
-    const double *usrc = STAGE == 4 ? a.A : a.U;
-    double psn[NF3];                 // state of the own column, plane r+2
-    double puo[NF3];                 // the combine's stored operand of the own cell, plane r
-    double pgz[NQF];                 // G_z of the own column's face r+1/2
-    double pgc[4][4];                // G_x(v_z), G_x(B_z), G_y(v_z), G_y(B_z) around that face
-    auto prefetch = [&](int rr) __attribute__((always_inline)) {
-        const uint32_t o = L.off(cx, cy, rr + 2);
+            for (int f = 0; f < NF3; ++f) K[f] = K[f] + lds.ex[f][tid];
+            hand(c2);
+            if (colv) {
+                combine3<STAGE>(a, fs, L.off(x, y, r), s0, uo, K, dt, hdt, dt6, un);
+                if (STAGE == 4) sp.add(un, kc.gm1, kc.gamma);
+            }
+            if (STAGE > 1) operand(r + 1, uo);
 #pragma unroll
-        for (int f = 0; f < NF3; ++f) psn[f] = ldo(a.S + f * fs, o);
-        if (STAGE > 1 && HD) {
-            // columns past the last cell and planes before the first output
-            // plane read a cell of the block and discard it
-            const uint32_t ou = L.off(xc, yc, max(rr, zb));
+            for (int f = 0; f < NF3; ++f) { s0[f] = s1[f]; s1[f] = s2[f]; s2[f] = s3[f]; }
 #pragma unroll
-            for (int f = 0; f < NF3; ++f) puo[f] = ldo(usrc + f * fs, ou);
+            for (int k = 0; k < 7; ++k) {
+                fzw[0][k] = fzw[1][k]; fzw[1][k] = fzw[2][k]; fzw[2][k] = fzw[3][k]; fzw[3][k] = fzn[k];
+            }
         }
-        if (HD) {
-            const uint32_t c = L.off(xc, yc, max(rr, zb - 1));
+        if (STAGE == 4) sp.reduce(lds.red, wv, lane);
+    } else {
+        const bool cross = a.cross != 0;
+        const double *Gf = a.Gf;
+        auto garr = [&](int d, int q) { return Gf + (int64_t)(NQF * d + q) * fs; };
+        const uint32_t sy = (uint32_t)L.pitch * 8u, sz = (uint32_t)(L.plane * 8);   // byte strides
+        // columns past the last cell read a cell of the block and discard it
+        const int xc = min(x, L.nx - 1), yc = min(y, L.ny - 1);
+        dma_tile<NQF, TY + 2, TX + 4, false, NW> tgx(Gf, fs, L, 0, X0, Y0, zb, wv, lane);
+        dma_tile<NQF, TY + 1, TX + 4, false, NW> tgy(Gf, fs, L, 1, X0, Y0, zb, wv, lane);
+        dma_tile<4, TY + 2, TX + 4, true, NW> tgz(Gf, fs, L, 2, X0, Y0, zb - 1, wv, lane);
+        tgz.fill(&lds.gz[(zb - 1) & 1].v[0][0][0], wv, sz);
+        // apron point of this thread
+        const bool fr = tid < NFRAME;
+        int fbx = 0, fby = 0;
+        frame_point<TX, TY>(fr ? tid : 0, fbx, fby);
+        const int fgx = clampi(X0 - 2 + fbx, -G, L.nx + G - 1), fgy = clampi(Y0 - 2 + fby, -G, L.ny + G - 1);
+        double sf[NF3];   // its state of the next plane
+        auto apron = [&](int k) __attribute__((always_inline)) {
+            const uint32_t o = L.off(fgx, fgy, k);
 #pragma unroll
-            for (int q = 0; q < NQF; ++q) pgz[q] = ldo(garr(2, q), c);
+            for (int f = 0; f < NF3; ++f) sf[f] = ldo(a.S + f * fs, o);
+        };
+        if (fr) apron(zb);
+        // what the z face r+1/2 reads beyond the tiles of plane r: G_z of
+        // rho~, eps~ and v_z, and G_x, G_y of v_z and B_z of plane r+1 around
+        // it (x faces x-1, x, then y faces y-1, y); loaded one plane early
+        double pgz[3], pgc[4][2];
+        auto zface = [&](int k) __attribute__((always_inline)) {
+            const uint32_t c = L.off(xc, yc, k);
+            pgz[0] = ldo(garr(2, GR), c);
+            pgz[1] = ldo(garr(2, GE), c);
+            pgz[2] = ldo(garr(2, GVZ), c);
             if (cross) {
-                // x faces around the z face, then y faces: (-1, r), (0, r),
-                // (-1, r+1), (0, r+1) relative to the own column
-                const uint32_t c00 = c - 8u, c01 = c, c10 = c - 8u + sz, c11 = c + sz;
-                const uint32_t d00 = c - sy, d01 = c, d10 = c - sy + sz, d11 = c + sz;
-                pgc[0][0] = ldo(garr(0, GVZ), c00); pgc[0][1] = ldo(garr(0, GVZ), c01);
-                pgc[0][2] = ldo(garr(0, GVZ), c10); pgc[0][3] = ldo(garr(0, GVZ), c11);
-                pgc[1][0] = ldo(garr(0, GB2), c00); pgc[1][1] = ldo(garr(0, GB2), c01);
-                pgc[1][2] = ldo(garr(0, GB2), c10); pgc[1][3] = ldo(garr(0, GB2), c11);
-                pgc[2][0] = ldo(garr(1, GVZ), d00); pgc[2][1] = ldo(garr(1, GVZ), d01);
-                pgc[2][2] = ldo(garr(1, GVZ), d10); pgc[2][3] = ldo(garr(1, GVZ), d11);
-                pgc[3][0] = ldo(garr(1, GB2), d00); pgc[3][1] = ldo(garr(1, GB2), d01);
-                pgc[3][2] = ldo(garr(1, GB2), d10); pgc[3][3] = ldo(garr(1, GB2), d11);
+                pgc[0][0] = ldo(garr(0, GVZ), c - 8u + sz); pgc[0][1] = ldo(garr(0, GVZ), c + sz);
+                pgc[1][0] = ldo(garr(0, GB2), c - 8u + sz); pgc[1][1] = ldo(garr(0, GB2), c + sz);
+                pgc[2][0] = ldo(garr(1, GVZ), c - sy + sz); pgc[2][1] = ldo(garr(1, GVZ), c + sz);
+                pgc[3][0] = ldo(garr(1, GB2), c - sy + sz); pgc[3][1] = ldo(garr(1, GB2), c + sz);
             }
-        }
-    };
-    prefetch(zb - 4);
-
-    for (int r = zb - 4; r < ze; ++r) {
-        const bool body = r >= zb;   // plane r is an output plane of this block
-        if (HD) {
-            // ---- the face quantities of plane r that the x- and y-face
-            // fluxes read, into LDS while the state of the plane is loaded
-            // (G_z also for the plane before the first output plane); the
-            // previous plane's closing barrier has freed the tiles
-            constexpr int NW = TX * TY / 64, GW = StageLds3<TX, TY, HD>::GW;
-            if (body) {
-                dma_tile<NQF, TY + 2, GW, false, NW>(&lds.gx[0][0][0], Gf, fs, L, 0, X0, Y0, r, wv, lane);
-                dma_tile<NQF, TY + 1, GW, false, NW>(&lds.gy[0][0][0], Gf, fs, L, 1, X0, Y0, r, wv, lane);
-            }
-            if (r >= zb - 1)
-                dma_tile<4, TY + 2, GW, true, NW>(&lds.gz[r & 1].v[0][0][0], Gf, fs, L, 2, X0, Y0, r, wv, lane);
-        }
-        // ---- P1: plane r over the tile and its apron -> primitives, x and y fluxes in LDS
-        double so[NF3];   // own cell's stage input (the combine's pointwise operand)
-        if (body) {
-            // the own point first, then the apron frame
-            for (int p = tid; p < TX * TY + NFRAME; p += TX * TY) {
-                int bx, by;
-                if (p < TX * TY) {
-                    bx = tx + 2;
-                    by = ty + 2;
-                } else {
-                    const int i = p - TX * TY;
-                    if (i < 2 * BX) { by = i / BX; bx = i % BX; }
-                    else if (i < 4 * BX) { by = TY + 2 + (i - 2 * BX) / BX; bx = (i - 2 * BX) % BX; }
-                    else { const int j = i - 4 * BX, c4 = j % 4; by = 2 + j / 4; bx = c4 < 2 ? c4 : TX + c4; }
-                }
-                const int gx = clampi(X0 - 2 + bx, -G, L.nx + G - 1), gy = clampi(Y0 - 2 + by, -G, L.ny + G - 1);
-                const uint32_t o = L.off(gx, gy, r);
-                double s[NF3];
-#pragma unroll
-                for (int f = 0; f < NF3; ++f) s[f] = ldo(a.S + f * fs, o);
-                if (p < TX * TY) {
-#pragma unroll
-                    for (int f = 0; f < NF3; ++f) so[f] = s[f];
-                }
-                const double rt = s[FR], mx = s[FMX], my = s[FMY], mz = s[FMZ], et = s[FE];
-                const double bx_ = s[FBX], by_ = s[FBY], bz_ = s[FBZ];
-                const double ir = 1.0 / rt;
-                const double ux = mx * ir, uy = my * ir, uz = mz * ir;
-                const double kin = half * ((mx * ux + my * uy) + mz * uz);
-                const double b2 = (bx_ * bx_ + by_ * by_) + bz_ * bz_;
-                const double pk = gm1 * ((et - kin) - half * b2);
-                const double pt = pk + half * b2;
-                const double bv = (bx_ * ux + by_ * uy) + bz_ * uz;
-                const double ef = et + pt;
-                lds.pr[0][by][bx] = rt;
-                lds.pr[1][by][bx] = ux;
-                lds.pr[2][by][bx] = uy;
-                lds.pr[3][by][bx] = uz;
-                lds.pr[4][by][bx] = bx_;
-                lds.pr[5][by][bx] = by_;
-                lds.pr[6][by][bx] = bz_;
-                lds.fx[0][by][bx] = mx;
-                lds.fx[1][by][bx] = (ux * mx - bx_ * bx_) + pt;
-                lds.fx[2][by][bx] = ux * my - bx_ * by_;
-                lds.fx[3][by][bx] = ux * mz - bx_ * bz_;
-                lds.fx[4][by][bx] = ux * ef - bx_ * bv;
-                lds.fx[5][by][bx] = ux * by_ - bx_ * uy;
-                lds.fx[6][by][bx] = ux * bz_ - bx_ * uz;
-                lds.fy[0][by][bx] = my;
-                lds.fy[1][by][bx] = uy * mx - by_ * bx_;
-                lds.fy[2][by][bx] = (uy * my - by_ * by_) + pt;
-                lds.fy[3][by][bx] = uy * mz - by_ * bz_;
-                lds.fy[4][by][bx] = uy * ef - by_ * bv;
-                lds.fy[5][by][bx] = uy * bx_ - by_ * ux;
-                lds.fy[6][by][bx] = uy * bz_ - by_ * uz;
-            }
-        }
-        __syncthreads();
-
-        // ---- own column, plane r+2: state, primitives, z fluxes
-        double pn[7], fzn[7];
+        };
+        // H_z of face zb-1/2, everything from memory
+        FaceFlux hzp;
         {
-            const double *sn = psn;
-            const double rt = sn[FR], mx = sn[FMX], my = sn[FMY], mz = sn[FMZ], et = sn[FE];
-            const double bx_ = sn[FBX], by_ = sn[FBY], bz_ = sn[FBZ];
-            const double ir = 1.0 / rt;
-            const double ux = mx * ir, uy = my * ir, uz = mz * ir;
-            const double kin = half * ((mx * ux + my * uy) + mz * uz);
-            const double b2 = (bx_ * bx_ + by_ * by_) + bz_ * bz_;
-            const double pk = gm1 * ((et - kin) - half * b2);
-            const double pt = pk + half * b2;
-            const double bv = (bx_ * ux + by_ * uy) + bz_ * uz;
-            const double ef = et + pt;
-            pn[0] = rt; pn[1] = ux; pn[2] = uy; pn[3] = uz; pn[4] = bx_; pn[5] = by_; pn[6] = bz_;
-            fzn[0] = mz;
-            fzn[1] = uz * mx - bz_ * bx_;
-            fzn[2] = uz * my - bz_ * by_;
-            fzn[3] = (uz * mz - bz_ * bz_) + pt;
-            fzn[4] = uz * ef - bz_ * bv;
-            fzn[5] = uz * bx_ - bz_ * ux;
-            fzn[6] = uz * by_ - bz_ * uy;
-        }
-
-        // ---- P2: H_z on the face r+1/2 (planes r, r+1 of the own column)
-        FaceFlux hz;
+            const uint32_t c = L.off(xc, yc, zb - 1);
+            double sa[NF3], sb[NF3], g[NQF];
 #pragma unroll
-        for (int f = 0; f < NF3; ++f) hz.h[f] = 0.0;
-        if (HD && r >= zb - 1) {
+            for (int f = 0; f < NF3; ++f) { sa[f] = ldo(a.S + f * fs, c); sb[f] = ldo(a.S + f * fs, c + sz); }
+#pragma unroll
+            for (int q = 0; q < NQF; ++q) g[q] = ldo(garr(2, q), c);
             double v1 = 0.0, b1 = 0.0, v2 = 0.0, b2 = 0.0;
             if (cross) {
-                // means of the four x faces (G of v_z, B_z), then y faces
-                v1 = ((pgc[0][0] + pgc[0][1]) + (pgc[0][2] + pgc[0][3])) * 0.25;
-                b1 = ((pgc[1][0] + pgc[1][1]) + (pgc[1][2] + pgc[1][3])) * 0.25;
-                v2 = ((pgc[2][0] + pgc[2][1]) + (pgc[2][2] + pgc[2][3])) * 0.25;
-                b2 = ((pgc[3][0] + pgc[3][1]) + (pgc[3][2] + pgc[3][3])) * 0.25;
+                auto mean = [&](const double *A, uint32_t st) __attribute__((always_inline)) {
+                    return ((ldo(A, c - st) + ldo(A, c)) + (ldo(A, c - st + sz) + ldo(A, c + sz))) * 0.25;
+                };
+                v1 = mean(garr(0, GVZ), 8u);
+                b1 = mean(garr(0, GB2), 8u);
+                v2 = mean(garr(1, GVZ), sy);
+                b2 = mean(garr(1, GB2), sy);
             }
-            const double rf = half * (pq[0][0] + pq[1][0]);
-            double vf[3], bf[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                vf[k] = half * (pq[0][1 + k] + pq[1][1 + k]);
-                bf[k] = half * (pq[0][4 + k] + pq[1][4 + k]);
-            }
-            hz = face_flux<2>(pgz, v1, b1, v2, b2, rf, vf, bf);
+            const Cell3 ca = cell3(sa, kc.gm1), cb = cell3(sb, kc.gm1);
+            const double rf = half * (ca.rt + cb.rt);
+            const double vf[3] = {half * (ca.ux + cb.ux), half * (ca.uy + cb.uy), half * (ca.uz + cb.uz)};
+            const double bf[3] = {half * (ca.bx + cb.bx), half * (ca.by + cb.by), half * (ca.bz + cb.bz)};
+            hzp = face_flux<2>(g, v1, b1, v2, b2, rf, vf, bf);
         }
-        // the combine operand leaves the prefetch registers (with
-        // hyper-diffusion its loads are complete: the barrier above waited
-        // for the tile fill issued after them), which then take the next
-        // plane's loads for the whole of this plane's x and y terms
-        double uo[NF3];
-        if (STAGE > 1 && HD) {
-#pragma unroll
-            for (int f = 0; f < NF3; ++f) uo[f] = puo[f];
-        }
-        prefetch(r + 1);
-        __builtin_amdgcn_sched_barrier(0);
-
-        // ---- P3: x and y terms of plane r and its output
-        if (body && colv) {
-            const int bx = tx + 2, by = ty + 2;
-            double K[NF3];
-            {
-                double ax[7], ay[7];
-#pragma unroll
-                for (int k = 0; k < 7; ++k) {
-                    ax[k] = (eight * (lds.fx[k][by][bx + 1] - lds.fx[k][by][bx - 1]) -
-                             (lds.fx[k][by][bx + 2] - lds.fx[k][by][bx - 2])) * kc.i12[0];
-                    ay[k] = (eight * (lds.fy[k][by + 1][bx] - lds.fy[k][by - 1][bx]) -
-                             (lds.fy[k][by + 2][bx] - lds.fy[k][by - 2][bx])) * kc.i12[1];
-                }
-                double ab[NF3], ez[NF3];
-                const double zero = 0.0;
-                ab[FR] = ax[0] + ay[0];
-                ab[FMX] = ax[1] + ay[1];
-                ab[FMY] = ax[2] + ay[2];
-                ab[FMZ] = ax[3] + ay[3];
-                ab[FE] = ax[4] + ay[4];
-                ab[FBX] = zero + ay[5];
-                ab[FBY] = ax[5] + zero;
-                ab[FBZ] = ax[6] + ay[6];
-#pragma unroll
-                for (int f = 0; f < 7; ++f) ez[f] = (eight * (fzw[3][f] - fzw[1][f]) - (fzn[f] - fzw[0][f])) * kc.i12[2];
-                ez[FBZ] = zero;
-#pragma unroll
-                for (int f = 0; f < NF3; ++f) K[f] = -(ab[f] + ez[f]);
+        zface(zb);
+        for (int r = zb; r < ze; ++r) {
+            const int zc = r & 1, zp = zc ^ 1;   // G_z slots of planes r and r-1
+            tgx.fill(&lds.gx[0][0][0], wv, sz);
+            tgy.fill(&lds.gy[0][0][0], wv, sz);
+            tgz.fill(&lds.gz[zc].v[0][0][0], wv, sz);
+            if (fr) {
+                const Cell3 c = cell3(sf, kc.gm1);
+                lds.pr[0][fby][fbx] = c.rt;
+                lds.pr[1][fby][fbx] = c.ux; lds.pr[2][fby][fbx] = c.uy; lds.pr[3][fby][fbx] = c.uz;
+                lds.pr[4][fby][fbx] = c.bx; lds.pr[5][fby][fbx] = c.by; lds.pr[6][fby][fbx] = c.bz;
+                put_fluxes(lds, fby, fbx, c);
             }
-            if (HD) {
-                // H_x on the faces x-1/2 and x+1/2, then H_y on y-1/2 and
-                // y+1/2, one face at a time (a scheduling barrier after each
-                // keeps the G loads of later faces from being hoisted into
-                // the registers of earlier ones)
-                double ah[NF3], bh[NF3];
-                const int zc = r & 1, zp = zc ^ 1;   // G_z slots of planes r and r-1
-#pragma unroll 1
-                for (int side = 0; side < 2; ++side) {
-                    const int lb = bx - 1 + side;         // box column of the face's left cell xx = x - 1 + side
-                    const int i = tx + side + 1;          // staged column of xx
-                    double g[NQF];
-#pragma unroll
-                    for (int q = 0; q < NQF; ++q) g[q] = lds.gx[q][ty + 1][i];
-                    double v1 = 0.0, b1 = 0.0, v2 = 0.0, b2 = 0.0;
-                    if (cross) {
-                        // y faces around the x face (G of v_x, B_x): (xx, y-1), (xx, y),
-                        // (xx+1, y-1), (xx+1, y); then z faces: (xx, r-1), (xx, r),
-                        // (xx+1, r-1), (xx+1, r)
-                        v1 = ((lds.gy[GVX][ty][i] + lds.gy[GVX][ty + 1][i]) +
-                              (lds.gy[GVX][ty][i + 1] + lds.gy[GVX][ty + 1][i + 1])) * 0.25;
-                        b1 = ((lds.gy[GB1][ty][i] + lds.gy[GB1][ty + 1][i]) +
-                              (lds.gy[GB1][ty][i + 1] + lds.gy[GB1][ty + 1][i + 1])) * 0.25;
-                        v2 = ((lds.gz[zp].v[0][ty + 1][i] + lds.gz[zc].v[0][ty + 1][i]) +
-                              (lds.gz[zp].v[0][ty + 1][i + 1] + lds.gz[zc].v[0][ty + 1][i + 1])) * 0.25;
-                        b2 = ((lds.gz[zp].v[1][ty + 1][i] + lds.gz[zc].v[1][ty + 1][i]) +
-                              (lds.gz[zp].v[1][ty + 1][i + 1] + lds.gz[zc].v[1][ty + 1][i + 1])) * 0.25;
-                    }
-                    const double rf = half * (lds.pr[0][by][lb] + lds.pr[0][by][lb + 1]);
-                    double vf[3], bf[3];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        vf[k] = half * (lds.pr[1 + k][by][lb] + lds.pr[1 + k][by][lb + 1]);
-                        bf[k] = half * (lds.pr[4 + k][by][lb] + lds.pr[4 + k][by][lb + 1]);
-                    }
-                    const FaceFlux h = face_flux<0>(g, v1, b1, v2, b2, rf, vf, bf);
-#pragma unroll
-                    for (int f = 0; f < NF3; ++f) ah[f] = side == 0 ? h.h[f] : (h.h[f] - ah[f]) * kc.ih[0];
-                    __builtin_amdgcn_sched_barrier(0);
+            loads_done();   // the tiles
+            lds_barrier();
+            double T[NF3];
+            {   // H_z on the face r+1/2
+                const int j = ty + 1, i = tx + 2;
+                double g[NQF];
+                g[GR] = pgz[0]; g[GE] = pgz[1]; g[GVZ] = pgz[2];
+                g[GVX] = lds.gz[zc].v[0][j][i];
+                g[GB1] = lds.gz[zc].v[1][j][i];
+                g[GVY] = lds.gz[zc].v[2][j][i];
+                g[GB2] = lds.gz[zc].v[3][j][i];
+                double v1 = 0.0, b1 = 0.0, v2 = 0.0, b2 = 0.0;
+                if (cross) {
+                    // means of the four x faces (G of v_z, B_z), then y faces
+                    v1 = ((lds.gx[GVZ][j][i - 1] + lds.gx[GVZ][j][i]) + (pgc[0][0] + pgc[0][1])) * 0.25;
+                    b1 = ((lds.gx[GB2][j][i - 1] + lds.gx[GB2][j][i]) + (pgc[1][0] + pgc[1][1])) * 0.25;
+                    v2 = ((lds.gy[GVZ][j - 1][i] + lds.gy[GVZ][j][i]) + (pgc[2][0] + pgc[2][1])) * 0.25;
+                    b2 = ((lds.gy[GB2][j - 1][i] + lds.gy[GB2][j][i]) + (pgc[3][0] + pgc[3][1])) * 0.25;
                 }
-#pragma unroll 1
-                for (int side = 0; side < 2; ++side) {
-                    const int lb = by - 1 + side;         // box row of the face's lower cell yy = y - 1 + side
-                    const int j = ty + side;              // staged row of yy
-                    double g[NQF];
+                const double rf = half * (lds.pr[0][by][bx] + lds.ex[0][tid]);
+                double vf[3], bf[3];
 #pragma unroll
-                    for (int q = 0; q < NQF; ++q) g[q] = lds.gy[q][j][tx + 2];
-                    double v1 = 0.0, b1 = 0.0, v2 = 0.0, b2 = 0.0;
-                    if (cross) {
-                        // x faces around the y face (G of v_y, B_y): (x-1, yy), (x, yy),
-                        // (x-1, yy+1), (x, yy+1); then z faces: (yy, r-1), (yy, r),
-                        // (yy+1, r-1), (yy+1, r)
-                        v1 = ((lds.gx[GVY][j][tx + 1] + lds.gx[GVY][j][tx + 2]) +
-                              (lds.gx[GVY][j + 1][tx + 1] + lds.gx[GVY][j + 1][tx + 2])) * 0.25;
-                        b1 = ((lds.gx[GB1][j][tx + 1] + lds.gx[GB1][j][tx + 2]) +
-                              (lds.gx[GB1][j + 1][tx + 1] + lds.gx[GB1][j + 1][tx + 2])) * 0.25;
-                        v2 = ((lds.gz[zp].v[2][j][tx + 2] + lds.gz[zc].v[2][j][tx + 2]) +
-                              (lds.gz[zp].v[2][j + 1][tx + 2] + lds.gz[zc].v[2][j + 1][tx + 2])) * 0.25;
-                        b2 = ((lds.gz[zp].v[3][j][tx + 2] + lds.gz[zc].v[3][j][tx + 2]) +
-                              (lds.gz[zp].v[3][j + 1][tx + 2] + lds.gz[zc].v[3][j + 1][tx + 2])) * 0.25;
-                    }
-                    const double rf = half * (lds.pr[0][lb][bx] + lds.pr[0][lb + 1][bx]);
-                    double vf[3], bf[3];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        vf[k] = half * (lds.pr[1 + k][lb][bx] + lds.pr[1 + k][lb + 1][bx]);
-                        bf[k] = half * (lds.pr[4 + k][lb][bx] + lds.pr[4 + k][lb + 1][bx]);
-                    }
-                    const FaceFlux h = face_flux<1>(g, v1, b1, v2, b2, rf, vf, bf);
-#pragma unroll
-                    for (int f = 0; f < NF3; ++f) bh[f] = side == 0 ? h.h[f] : (h.h[f] - bh[f]) * kc.ih[1];
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int k = 0; k < 3; ++k) {
+                    vf[k] = half * (lds.pr[1 + k][by][bx] + lds.ex[1 + k][tid]);
+                    bf[k] = half * (lds.pr[4 + k][by][bx] + lds.ex[4 + k][tid]);
                 }
+                const FaceFlux hz = face_flux<2>(g, v1, b1, v2, b2, rf, vf, bf);
 #pragma unroll
-                for (int f = 0; f < NF3; ++f) K[f] = K[f] + ((ah[f] + bh[f]) + (hz.h[f] - hzp[f]) * kc.ih[2]);
+                for (int f = 0; f < NF3; ++f) T[f] = (hz.h[f] - hzp.h[f]) * kc.ih[2];
+                hzp = hz;
             }
-            const uint32_t oo = L.off(x, y, r);
-            auto uop = [&](int f) __attribute__((always_inline)) { return HD ? uo[f] : ldo(usrc + f * fs, oo); };
-            if (STAGE == 1) {
+            settle(T);
+            settle(hzp.h);
+            __builtin_amdgcn_sched_barrier(0);
+            zface(r + 1);
+            if (fr) apron(r + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            // H_x on the faces x-1/2 and x+1/2, then H_y on y-1/2 and y+1/2,
+            // one face at a time (a scheduling barrier after each keeps the
+            // LDS reads of later faces out of the registers of earlier ones)
+            double ah[NF3], bh[NF3];
 #pragma unroll
-                for (int f = 0; f < NF3; ++f) sto(a.out1 + f * fs, oo, so[f] + hdt * K[f]);
-            } else if (STAGE == 2) {
+            for (int side = 0; side < 2; ++side) {
+                const int lb = bx - 1 + side;         // box column of the face's left cell xx = x - 1 + side
+                const int i = tx + side + 1;          // staged column of xx
+                double g[NQF];
 #pragma unroll
-                for (int f = 0; f < NF3; ++f) {
-                    const double u = uop(f), sv = so[f];
-                    sto(a.out1 + f * fs, oo, u + hdt * K[f]);
-                    sto(a.out2 + f * fs, oo, (u + u) + ((sv - u) + dt * K[f]));
+                for (int q = 0; q < NQF; ++q) g[q] = lds.gx[q][ty + 1][i];
+                double v1 = 0.0, b1 = 0.0, v2 = 0.0, b2 = 0.0;
+                if (cross) {
+                    // y faces around the x face (G of v_x, B_x): (xx, y-1), (xx, y),
+                    // (xx+1, y-1), (xx+1, y); then z faces: (xx, r-1), (xx, r),
+                    // (xx+1, r-1), (xx+1, r)
+                    v1 = ((lds.gy[GVX][ty][i] + lds.gy[GVX][ty + 1][i]) +
+                          (lds.gy[GVX][ty][i + 1] + lds.gy[GVX][ty + 1][i + 1])) * 0.25;
+                    b1 = ((lds.gy[GB1][ty][i] + lds.gy[GB1][ty + 1][i]) +
+                          (lds.gy[GB1][ty][i + 1] + lds.gy[GB1][ty + 1][i + 1])) * 0.25;
+                    v2 = ((lds.gz[zp].v[0][ty + 1][i] + lds.gz[zc].v[0][ty + 1][i]) +
+                          (lds.gz[zp].v[0][ty + 1][i + 1] + lds.gz[zc].v[0][ty + 1][i + 1])) * 0.25;
+                    b2 = ((lds.gz[zp].v[1][ty + 1][i] + lds.gz[zc].v[1][ty + 1][i]) +
+                          (lds.gz[zp].v[1][ty + 1][i + 1] + lds.gz[zc].v[1][ty + 1][i + 1])) * 0.25;
                 }
-            } else if (STAGE == 3) {
+                const double rf = half * (lds.pr[0][by][lb] + lds.pr[0][by][lb + 1]);
+                double vf[3], bf[3];
 #pragma unroll
-                for (int f = 0; f < NF3; ++f) sto(a.out1 + f * fs, oo, uop(f) + dt * K[f]);
-            } else {
-                double un[NF3];
-#pragma unroll
-                for (int f = 0; f < NF3; ++f) {
-                    const double av = uop(f), sv = so[f];
-                    un[f] = (sv + (av - (sv + sv)) * kc.third) + dt6 * K[f];
-                    sto(a.out1 + f * fs, oo, un[f]);
+                for (int k = 0; k < 3; ++k) {
+                    vf[k] = half * (lds.pr[1 + k][by][lb] + lds.pr[1 + k][by][lb + 1]);
+                    bf[k] = half * (lds.pr[4 + k][by][lb] + lds.pr[4 + k][by][lb + 1]);
                 }
-                // wave speeds of the new state (the next step's dt and c_max)
-                const double ir = 1.0 / un[FR];
-                const double ux = un[FMX] * ir, uy = un[FMY] * ir, uz = un[FMZ] * ir;
-                const double kin = half * ((un[FMX] * ux + un[FMY] * uy) + un[FMZ] * uz);
-                const double b2 = (un[FBX] * un[FBX] + un[FBY] * un[FBY]) + un[FBZ] * un[FBZ];
-                const double pk = gm1 * ((un[FE] - kin) - half * b2);
-                const double cf = sqrt((kc.gamma * pk + b2) * ir);
-                bool fin = isfinite(cf);
+                const FaceFlux h = face_flux<0>(g, v1, b1, v2, b2, rf, vf, bf);
 #pragma unroll
-                for (int f = 0; f < NF3; ++f) fin = fin && isfinite(un[f]);
-                if (!(un[FR] > 0.0) || !(pk > 0.0) || !fin) {
-                    bad_t = 1;
-                } else {
-                    cx_t = fmax(cx_t, fabs(ux) + cf);
-                    cy_t = fmax(cy_t, fabs(uy) + cf);
-                    cz_t = fmax(cz_t, fabs(uz) + cf);
-                }
+                for (int f = 0; f < NF3; ++f) ah[f] = side == 0 ? h.h[f] : (h.h[f] - ah[f]) * kc.ih[0];
+                settle(ah);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        }
-        // ---- shift the windows
 #pragma unroll
-        for (int f = 0; f < NF3; ++f) hzp[f] = hz.h[f];
+            for (int side = 0; side < 2; ++side) {
+                const int lb = by - 1 + side;         // box row of the face's lower cell yy = y - 1 + side
+                const int j = ty + side;              // staged row of yy
+                double g[NQF];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) {
-            pq[0][k] = pq[1][k]; pq[1][k] = pn[k];
-            fzw[0][k] = fzw[1][k]; fzw[1][k] = fzw[2][k]; fzw[2][k] = fzw[3][k]; fzw[3][k] = fzn[k];
+                for (int q = 0; q < NQF; ++q) g[q] = lds.gy[q][j][tx + 2];
+                double v1 = 0.0, b1 = 0.0, v2 = 0.0, b2 = 0.0;
+                if (cross) {
+                    // x faces around the y face (G of v_y, B_y): (x-1, yy), (x, yy),
+                    // (x-1, yy+1), (x, yy+1); then z faces: (yy, r-1), (yy, r),
+                    // (yy+1, r-1), (yy+1, r)
+                    v1 = ((lds.gx[GVY][j][tx + 1] + lds.gx[GVY][j][tx + 2]) +
+                          (lds.gx[GVY][j + 1][tx + 1] + lds.gx[GVY][j + 1][tx + 2])) * 0.25;
+                    b1 = ((lds.gx[GB1][j][tx + 1] + lds.gx[GB1][j][tx + 2]) +
+                          (lds.gx[GB1][j + 1][tx + 1] + lds.gx[GB1][j + 1][tx + 2])) * 0.25;
+                    v2 = ((lds.gz[zp].v[2][j][tx + 2] + lds.gz[zc].v[2][j][tx + 2]) +
+                          (lds.gz[zp].v[2][j + 1][tx + 2] + lds.gz[zc].v[2][j + 1][tx + 2])) * 0.25;
+                    b2 = ((lds.gz[zp].v[3][j][tx + 2] + lds.gz[zc].v[3][j][tx + 2]) +
+                          (lds.gz[zp].v[3][j + 1][tx + 2] + lds.gz[zc].v[3][j + 1][tx + 2])) * 0.25;
+                }
+                const double rf = half * (lds.pr[0][lb][bx] + lds.pr[0][lb + 1][bx]);
+                double vf[3], bf[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    vf[k] = half * (lds.pr[1 + k][lb][bx] + lds.pr[1 + k][lb + 1][bx]);
+                    bf[k] = half * (lds.pr[4 + k][lb][bx] + lds.pr[4 + k][lb + 1][bx]);
+                }
+                const FaceFlux h = face_flux<1>(g, v1, b1, v2, b2, rf, vf, bf);
+#pragma unroll
+                for (int f = 0; f < NF3; ++f) bh[f] = side == 0 ? h.h[f] : (h.h[f] - bh[f]) * kc.ih[1];
+                settle(bh);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int f = 0; f < NF3; ++f) lds.ex[f][tid] = (ah[f] + bh[f]) + T[f];
+            lds_barrier();
         }
-        __syncthreads();
     }
 
     if (STAGE == 4) {
-        for (int off = 32; off > 0; off >>= 1) {
-            cx_t = fmax(cx_t, __shfl_xor(cx_t, off));
-            cy_t = fmax(cy_t, __shfl_xor(cy_t, off));
-            cz_t = fmax(cz_t, __shfl_xor(cz_t, off));
-            bad_t |= __shfl_xor(bad_t, off);
-        }
-        const int wv = tid >> 6;
-        if ((tid & 63) == 0) {
-            lds.red[0][wv] = cx_t; lds.red[1][wv] = cy_t; lds.red[2][wv] = cz_t; lds.red[3][wv] = (double)bad_t;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            double m0 = 0.0, m1 = 0.0, m2 = 0.0, bb = 0.0;
-            for (int k = 0; k < TX * TY / 64; ++k) {
-                m0 = fmax(m0, lds.red[0][k]); m1 = fmax(m1, lds.red[1][k]);
-                m2 = fmax(m2, lds.red[2][k]); bb = fmax(bb, lds.red[3][k]);
-            }
-            const int ns = sc->cur ^ 1;
-            sacx::raise_max(&sc->cacc[ns][0], m0);
-            sacx::raise_max(&sc->cacc[ns][1], m1);
-            sacx::raise_max(&sc->cacc[ns][2], m2);
-            if (bb > 0.0) atomicOr(&sc->nonphys, 1);
-        }
+        lds_barrier();
+        if (threadIdx.x == 0) raise_speeds(lds.red, sc);
     }
 }
 
@@ -1165,8 +1353,8 @@ void auto_planes(sacx3_ctx *c) {
     int cus = 0, per = 0, perf = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
     if (e == hipSuccess)
-        e = c->params.hd_on ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k3_stage<1, true, TXF, TYF>, NT, 0)
-                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k3_stage<1, false, TXF, TYF>, NT, 0);
+        e = c->params.hd_on ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k3_stage_hd<1, TXF, TYF>, 2 * NT, 0)
+                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k3_stage<1, TXF, TYF>, NT, 0);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&perf, k3_faces<TXF, TYF>, NT, 0);
     if (e != hipSuccess || cus < 1 || per < 1 || perf < 1) {
         (void)hipGetLastError();
@@ -1196,9 +1384,9 @@ int fill3(sacx3_ctx *c, double *S) {
 template <int STAGE>
 int launch_stage3(sacx3_ctx *c, const Stage3Args &a, int nblocks) {
     if (c->params.hd_on)
-        hipLaunchKernelGGL((k3_stage<STAGE, true, TXF, TYF>), dim3(nblocks), dim3(NT), 0, c->stream, a);
+        hipLaunchKernelGGL((k3_stage_hd<STAGE, TXF, TYF>), dim3(nblocks), dim3(2 * NT), 0, c->stream, a);
     else
-        hipLaunchKernelGGL((k3_stage<STAGE, false, TXF, TYF>), dim3(nblocks), dim3(NT), 0, c->stream, a);
+        hipLaunchKernelGGL((k3_stage<STAGE, TXF, TYF>), dim3(nblocks), dim3(NT), 0, c->stream, a);
     HIPCHK3(hipGetLastError());
     return SACX_OK;
 }

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 # tiles: one column short, full, one over, one cell; strips: one plane, two
-# (each parity of the first plane), a remainder, the automatic choice
+# (each parity of the first plane), a remainder, the automatic choice; sides
+# of 1, 2 (periodic: filled ghost layers) and 3 cells (read in place)
 @pytest.mark.parametrize("nx,ny,nz,planes,cross", [
     (31, 7, 5, 1, True),
     (32, 8, 6, 2, True),
@@ -21,6 +22,8 @@ pytestmark = pytest.mark.gpu
     (65, 1, 9, 0, False),
     (64, 16, 1, 0, True),
     (3, 24, 2, 1, False),
+    (4, 3, 5, 2, True),
+    (2, 9, 3, 0, True),
 ])
 @pytest.mark.parametrize("opened", [False, True])
 def test_tile_and_strip_edges_bit_exact(nx, ny, nz, planes, cross, opened):

@@ -750,7 +750,7 @@ __device__ __forceinline__ void loads_done() { asm volatile("s_waitcnt vmcnt(0)"
 // one wave per SIMD, whose waves waited in 42 % of their cycles; each plane's
 // state was also read twice (for the plane's x and y terms, and two planes
 // early for the z fluxes).  Two roles with a loop each fit two waves per SIMD
-// (219-223 VGPRs, 153 KB of LDS), and the P role has the registers to keep a
+// (219-241 VGPRs, 153 KB of LDS), and the P role has the registers to keep a
 // state until its plane comes.  256^3 FP64, per launch: 2.65-3.0 -> 1.67-2.0 ms;
 // two whole steps 35.78 -> 27.68 ms; five of 75 x 53 x 61: 2.52 -> 2.03 ms.
 // The order of the LDS reads is fixed in the source: read two at a time, each

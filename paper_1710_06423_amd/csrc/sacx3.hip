@@ -90,10 +90,10 @@ struct Layout3 {
 struct Dev3 {
     double t, dt, cmax, t_end, hdt, dt6;
     double kd2[3][4];                 // c2 * h_d * c_max per constant class
-    unsigned long long cacc[2][3];    // [slot][x, y, z]
     double last_c[3], last_cmax;
     long long steps;
     int cur, active, nonphys, pad;
+    sacx::SpeedWord acc[2][sacx::kAcc];   // [slot], the maximum over the words
 };
 
 // grid constants, computed once on the host in FP64
@@ -490,27 +490,26 @@ struct Speeds3 {
     // one result per wave into red (wave wv)
     template <int NW>
     __device__ __forceinline__ void reduce(double (&red)[4][NW], int wv, int lane) {
-        for (int off = 32; off > 0; off >>= 1) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) c[d] = fmax(c[d], __shfl_xor(c[d], off));
-            bad |= __shfl_xor(bad, off);
-        }
-        if (lane == 0) {
+        for (int d = 0; d < 3; ++d) c[d] = sacx::wave_max(c[d]);
+        const bool any = __any(bad) != 0;
+        if (lane == 63) {
 #pragma unroll
             for (int d = 0; d < 3; ++d) red[d][wv] = c[d];
-            red[3][wv] = (double)bad;
+            red[3][wv] = any ? 1.0 : 0.0;
         }
     }
 };
 
 template <int NW>
-__device__ __forceinline__ void raise_speeds(const double (&red)[4][NW], Dev3 *sc) {
-    double m[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < NW; ++k)
-        for (int d = 0; d < 4; ++d) m[d] = fmax(m[d], red[d][k]);
-    const int ns = sc->cur ^ 1;
-    for (int d = 0; d < 3; ++d) sacx::raise_max(&sc->cacc[ns][d], m[d]);
-    if (m[3] > 0.0) atomicOr(&sc->nonphys, 1);
+__device__ __forceinline__ void raise_speeds(const double (&red)[4][NW], Dev3 *sc, int slot) {
+    if (threadIdx.x >= 4) return;
+    double m = 0.0;
+    for (int k = 0; k < NW; ++k) m = fmax(m, red[threadIdx.x][k]);
+    if (threadIdx.x < 3)
+        atomicMax(&sc->acc[slot][sacx::acc_word()].v[threadIdx.x], (unsigned long long)__double_as_longlong(m));
+    else if (m > 0.0)
+        atomicOr(&sc->nonphys, 1);
 }
 
 // the RK4 combine of the own cell at byte offset o: so is the stage input,
@@ -620,7 +619,7 @@ __global__ __launch_bounds__(TX *TY, 1) void k3_stage(Stage3Args a) {
     if (STAGE == 4) {
         sp.reduce(lds.red, tid >> 6, tid & 63);
         __syncthreads();
-        if (tid == 0) raise_speeds(lds.red, sc);
+        raise_speeds(lds.red, sc, sc->cur ^ 1);
     }
 }
 
@@ -1069,7 +1068,7 @@ __global__ __launch_bounds__(2 * TX *TY, 1) void k3_stage_hd(Stage3Args a) {
 
     if (STAGE == 4) {
         lds_barrier();
-        if (threadIdx.x == 0) raise_speeds(lds.red, sc);
+        raise_speeds(lds.red, sc, sc->cur ^ 1);
     }
 }
 
@@ -1136,18 +1135,6 @@ struct MPtr8 {
     double *p[NF3];
 };
 
-__global__ void k3_import(double *U, int64_t fs, Layout3 L, Ptr8 src, int64_t pitch, int64_t ppitch) {
-    const int64_t n = (int64_t)L.nx * L.ny * L.nz;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(t % L.nx);
-        const int64_t jk = t / L.nx;
-        const int j = (int)(jk % L.ny), k = (int)(jk / L.ny);
-        const int64_t d = L.at(i, j, k), s = i + j * pitch + k * ppitch;
-#pragma unroll
-        for (int f = 0; f < NF3; ++f) U[d + f * fs] = src.p[f][s];
-    }
-}
-
 __global__ void k3_export(const double *U, int64_t fs, Layout3 L, MPtr8 dst, uint32_t mask, int64_t pitch,
                           int64_t ppitch) {
     const int64_t n = (int64_t)L.nx * L.ny * L.nz;
@@ -1162,57 +1149,28 @@ __global__ void k3_export(const double *U, int64_t fs, Layout3 L, MPtr8 dst, uin
     }
 }
 
-// wave speeds of a state into accumulator slot `slot` (non-physical flag set)
-__global__ void k3_wavespeed(const double *U, int64_t fs, Layout3 L, double gamma, Dev3 *sc, int slot) {
+// the caller's fields into the state, and in the same pass over them the
+// state's wave speeds into slot 0 (as two passes 256^3 took 0.38 + 0.22 ms)
+__global__ __launch_bounds__(256) void k3_import(double *U, int64_t fs, Layout3 L, Ptr8 src, int64_t pitch,
+                                                 int64_t ppitch, double gamma, Dev3 *sc) {
     __shared__ double red[4][4];
-    const double gm1 = gamma - 1.0, half = 0.5;
-    double c0 = 0.0, c1 = 0.0, c2 = 0.0;
-    int bad = 0;
+    Speeds3 sp;
     const int64_t n = (int64_t)L.nx * L.ny * L.nz;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
         const int i = (int)(t % L.nx);
         const int64_t jk = t / L.nx;
         const int j = (int)(jk % L.ny), k = (int)(jk / L.ny);
-        const int64_t o = L.at(i, j, k);
+        const int64_t d = L.at(i, j, k), o = i + j * pitch + k * ppitch;
         double u[NF3];
 #pragma unroll
-        for (int f = 0; f < NF3; ++f) u[f] = U[o + f * fs];
-        const double ir = 1.0 / u[FR];
-        const double ux = u[FMX] * ir, uy = u[FMY] * ir, uz = u[FMZ] * ir;
-        const double kin = half * ((u[FMX] * ux + u[FMY] * uy) + u[FMZ] * uz);
-        const double b2 = (u[FBX] * u[FBX] + u[FBY] * u[FBY]) + u[FBZ] * u[FBZ];
-        const double pk = gm1 * ((u[FE] - kin) - half * b2);
-        const double cf = sqrt((gamma * pk + b2) * ir);
-        bool fin = isfinite(cf);
+        for (int f = 0; f < NF3; ++f) u[f] = src.p[f][o];
 #pragma unroll
-        for (int f = 0; f < NF3; ++f) fin = fin && isfinite(u[f]);
-        if (!(u[FR] > 0.0) || !(pk > 0.0) || !fin) {
-            bad = 1;
-        } else {
-            c0 = fmax(c0, fabs(ux) + cf);
-            c1 = fmax(c1, fabs(uy) + cf);
-            c2 = fmax(c2, fabs(uz) + cf);
-        }
+        for (int f = 0; f < NF3; ++f) U[d + f * fs] = u[f];
+        sp.add(u, gamma - 1.0, gamma);
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        c0 = fmax(c0, __shfl_xor(c0, off));
-        c1 = fmax(c1, __shfl_xor(c1, off));
-        c2 = fmax(c2, __shfl_xor(c2, off));
-        bad |= __shfl_xor(bad, off);
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { red[0][w] = c0; red[1][w] = c1; red[2][w] = c2; red[3][w] = bad; }
+    sp.reduce(red, threadIdx.x >> 6, threadIdx.x & 63);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double m0 = 0.0, m1 = 0.0, m2 = 0.0, bb = 0.0;
-        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) {
-            m0 = fmax(m0, red[0][k]); m1 = fmax(m1, red[1][k]); m2 = fmax(m2, red[2][k]); bb = fmax(bb, red[3][k]);
-        }
-        sacx::raise_max(&sc->cacc[slot][0], m0);
-        sacx::raise_max(&sc->cacc[slot][1], m1);
-        sacx::raise_max(&sc->cacc[slot][2], m2);
-        if (bb > 0.0) atomicOr(&sc->nonphys, 1);
-    }
+    raise_speeds(red, sc, 0);
 }
 
 __global__ void k3_reset(Dev3 *sc, double t0) {
@@ -1225,19 +1183,28 @@ __global__ void k3_reset(Dev3 *sc, double t0) {
 // off) and open the next (`begin`): its dt from the reduced wave speeds
 // (minimum of h_d / c_d over the directions with more than one cell, taken x,
 // y, z, then the end-time clamp) and the per-step constants.
-__global__ void k3_step(Dev3 *sc, double t_end, Consts3 k, bool end, bool begin) {
-    if (end && sc->active) {
-        sc->t = sc->t + sc->dt;
-        sc->steps = sc->steps + 1;
-        sc->cur ^= 1;
+// One wave, its loads issued at once, as for the 2-D scheme.
+__global__ __launch_bounds__(64) void k3_step(Dev3 *sc, double t_end, Consts3 k, bool end, bool begin) {
+    const int lane = threadIdx.x;
+    const unsigned long long v = sacx::speeds_by_lane(sc->acc, lane);
+    const int active = sc->active, cur0 = sc->cur, nonphys = sc->nonphys;
+    const long long steps = sc->steps;
+    const double dt0 = sc->dt, t0 = sc->t;
+    end = end && active;
+    const int cur = end ? cur0 ^ 1 : cur0;
+    double c[3];
+    for (int d = 0; d < 3; ++d) c[d] = __longlong_as_double((long long)__shfl(v, 32 * cur + d));
+    if (begin) sacx::speeds_clear_by_lane(sc->acc[cur ^ 1], lane);
+    if (lane) return;
+    const double t = end ? t0 + dt0 : t0;
+    if (end) {
+        sc->t = t;
+        sc->steps = steps + 1;
+        sc->cur = cur;
     }
     if (!begin) return;
     sc->t_end = t_end;
-    if (sc->nonphys) { sc->active = 0; return; }
-    const double t = sc->t;
-    if (t_end > 0.0 && t_end - t <= 1e-12 * t_end) { sc->active = 0; return; }
-    double c[3];
-    for (int d = 0; d < 3; ++d) c[d] = __longlong_as_double((long long)sc->cacc[sc->cur][d]);
+    if (nonphys || (t_end > 0.0 && t_end - t <= 1e-12 * t_end)) { sc->active = 0; return; }
     double m = -1.0, cm = -1.0;
     for (int d = 0; d < 3; ++d) {
         if (!k.act[d]) continue;
@@ -1255,7 +1222,6 @@ __global__ void k3_step(Dev3 *sc, double t_end, Consts3 k, bool end, bool begin)
     sc->dt6 = dt / 6.0;
     for (int d = 0; d < 3; ++d)
         for (int q = 0; q < 4; ++q) sc->kd2[d][q] = k.c2[q] * k.h[d] * cm;
-    for (int d = 0; d < 3; ++d) sc->cacc[sc->cur ^ 1][d] = 0ull;
     sc->active = 1;
 }
 
@@ -1646,10 +1612,8 @@ int sacx3_init_state(sacx3_ctx *ctx, const double *const *d_fields, int64_t pitc
     for (int f = 0; f < NF3; ++f) src.p[f] = d_fields[f];
     const int64_t ncell = (int64_t)L.nx * L.ny * L.nz;
     hipLaunchKernelGGL(k3_reset, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t0);
-    hipLaunchKernelGGL(k3_import, dim3(blocks_for(ncell, 256)), dim3(256), 0, ctx->stream, ctx->U, ctx->fs, L, src,
-                       pitch, plane_pitch);
-    hipLaunchKernelGGL(k3_wavespeed, dim3(std::min(blocks_for(ncell, 256), 2048)), dim3(256), 0, ctx->stream,
-                       ctx->U, ctx->fs, L, ctx->kc.gamma, ctx->sc, 0);
+    hipLaunchKernelGGL(k3_import, dim3(std::min(blocks_for(ncell, 256), 8192)), dim3(256), 0, ctx->stream, ctx->U,
+                       ctx->fs, L, src, pitch, plane_pitch, ctx->kc.gamma, ctx->sc);
     HIPCHK3(hipGetLastError());
     ctx->initialized = true;
     return SACX_OK;
@@ -1672,7 +1636,7 @@ int sacx3_advance(sacx3_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_d
     for (int n0 = 0; n0 < nsteps; n0 += chunk) {
         const int n1 = std::min(nsteps, n0 + chunk);
         for (int n = n0; n < n1; ++n) {
-            hipLaunchKernelGGL(k3_step, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t_end, ctx->kc, n > n0, true);
+            hipLaunchKernelGGL(k3_step, dim3(1), dim3(64), 0, ctx->stream, ctx->sc, t_end, ctx->kc, n > n0, true);
             int rc;
             if ((rc = stage3(ctx, 1, ctx->U, nullptr, nullptr, ctx->B1, nullptr))) return rc;
             if ((rc = stage3(ctx, 2, ctx->B1, ctx->U, nullptr, ctx->B2, ctx->A))) return rc;
@@ -1680,7 +1644,7 @@ int sacx3_advance(sacx3_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_d
             if ((rc = stage3(ctx, 4, ctx->B1, nullptr, ctx->A, ctx->U, nullptr))) return rc;
             HIPCHK3(hipGetLastError());
         }
-        hipLaunchKernelGGL(k3_step, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t_end, ctx->kc, true, false);
+        hipLaunchKernelGGL(k3_step, dim3(1), dim3(64), 0, ctx->stream, ctx->sc, t_end, ctx->kc, true, false);
         HIPCHK3(hipGetLastError());
         if (sync && n1 < nsteps) {
             int act = 1;
@@ -1741,7 +1705,7 @@ int sacx3_diagnostics(sacx3_ctx *ctx, sacx3_diag *out) {
     out->dt = h.dt;
     double c[3], cm = -1.0;
     for (int d = 0; d < 3; ++d) {
-        const unsigned long long bits = h.cacc[h.cur][d];
+        const unsigned long long bits = sacx::speed_max(h.acc[h.cur], d);
         memcpy(&c[d], &bits, sizeof(double));
         out->c[d] = c[d];
         if (ctx->kc.act[d]) cm = cm < 0.0 ? c[d] : std::max(cm, c[d]);

@@ -3,6 +3,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 #include <stdint.h>
 
 #include "sacx.h"
@@ -39,6 +41,12 @@ struct Layout {
 
 // Device-resident step scalars.  c accumulators hold the IEEE bit patterns of
 // non-negative doubles, so an unsigned 64-bit max is the floating max.
+// words over which the blocks of a launch spread their wave-speed maxima
+constexpr int kAcc = 8;
+struct alignas(128) SpeedWord {
+    unsigned long long v[3];   // x, y, z
+};
+
 struct DevScalars {
     double t;            // current time
     double dt;           // time step of the step in progress / last taken
@@ -48,7 +56,6 @@ struct DevScalars {
     // every stage kernel as uniform values)
     double hdt, dt6;     // dt/2, dt/6
     double kx2[4], ky2[4];  // c2 * h_d * c_max per constant class
-    unsigned long long cacc[2][2];  // [slot][x, y] wave-speed maxima
     double last_cx, last_cy, last_cmax;
     long long steps;     // steps since init
     long long steps0;    // the same when the current advance call began
@@ -56,19 +63,77 @@ struct DevScalars {
     int active;          // 1 while the step in progress proceeds
     int nonphys;         // sticky: a non-physical state was reduced
     int prev_active;     // `active` of the step before the one in progress, of the same call
+    SpeedWord acc[2][kAcc];  // [slot] wave-speed maxima, as the maximum over the words
 };
 
-// Raise a wave-speed accumulator (the IEEE bits of a non-negative double) to
-// v.  Atomics on one word are carried out one after the other, about 11 ns
-// each: 4096 blocks x 4 waves x 2 maxima of an initial state took 380 us at
-// every grid size.  Each block sends one maximum; in a launch of more than
-// 256 blocks only one above what the accumulator already holds (a read that
-// lags behind sends one too many).  With fewer blocks the read's latency,
-// about 1 us at the end of every block, costs more than the atomics it saves.
-__device__ __forceinline__ void raise_max(unsigned long long *p, double v) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    if (gridDim.x * gridDim.y <= 256 || b > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(p, b);
+// the maximum over the words of a slot (IEEE bits of non-negative doubles
+// order like the doubles)
+__host__ __device__ inline unsigned long long speed_max(const SpeedWord (&slot)[kAcc], int d) {
+    unsigned long long m = 0ull;
+    for (int k = 0; k < kAcc; ++k) {
+        const unsigned long long v = slot[k].v[d];
+        m = v > m ? v : m;
+    }
+    return m;
+}
+
+// the slot's maxima are cx, cy and cz
+__device__ inline void speed_set(SpeedWord (&slot)[kAcc], unsigned long long cx = 0ull, unsigned long long cy = 0ull,
+                                 unsigned long long cz = 0ull) {
+    for (int k = 0; k < kAcc; ++k) {
+        slot[k].v[0] = k ? 0ull : cx;
+        slot[k].v[1] = k ? 0ull : cy;
+        slot[k].v[2] = k ? 0ull : cz;
+    }
+}
+
+// Maximum of non-negative values over a full wave, in lane 63.  By register
+// lanes (DPP), a few cycles a step; a shuffle goes through the LDS pipe, and
+// the eighteen dependent ones of two maxima and a flag were at the end of
+// every block.
+__device__ __forceinline__ double wave_max(double v) {
+    auto step = [](double x, auto ctrl) __attribute__((always_inline)) {
+        constexpr int C = decltype(ctrl)::value;
+        const int lo = __double2loint(x), hi = __double2hiint(x);
+        const int l2 = __builtin_amdgcn_update_dpp(lo, lo, C, 0xf, 0xf, false);
+        const int h2 = __builtin_amdgcn_update_dpp(hi, hi, C, 0xf, 0xf, false);
+        return fmax(x, __hiloint2double(h2, l2));
+    };
+    v = step(v, std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+    v = step(v, std::integral_constant<int, 0x112>{});
+    v = step(v, std::integral_constant<int, 0x114>{});
+    v = step(v, std::integral_constant<int, 0x118>{});
+    v = step(v, std::integral_constant<int, 0x142>{});   // row_bcast 15: lane 31 has rows 0-1, lane 63 rows 2-3
+    v = step(v, std::integral_constant<int, 0x143>{});   // row_bcast 31: lane 63 has all
+    return v;
+}
+
+// the word of this block
+__device__ __forceinline__ int acc_word() { return (int)((blockIdx.x + gridDim.x * blockIdx.y) % kAcc); }
+
+// Raise the maxima of a block into a slot.  Atomics on one word are carried
+// out one after the other, about 11 ns each: 4096 blocks x 4 waves x 2 maxima
+// of an initial state took 380 us at every grid size.  Each block sends one
+// maximum per direction, and blocks take turns over kAcc words: the 512 and
+// more blocks that end together no longer queue for one word, and no block
+// has to read the word first to spare it the atomic.
+template <int NW>
+__device__ __forceinline__ void raise_speeds(double cx, double cy, int bad, double (&red)[3][NW], DevScalars *sc,
+                                             int slot) {
+    cx = wave_max(cx);
+    cy = wave_max(cy);
+    const bool any = __any(bad) != 0;
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 63) { red[0][w] = cx; red[1][w] = cy; red[2][w] = any ? 1.0 : 0.0; }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double m = 0.0;
+        for (int k = 0; k < NW; ++k) m = fmax(m, red[threadIdx.x][k]);
+        if (threadIdx.x < 2)
+            atomicMax(&sc->acc[slot][acc_word()].v[threadIdx.x], (unsigned long long)__double_as_longlong(m));
+        else if (m > 0.0)
+            atomicOr(&sc->nonphys, 1);
+    }
 }
 
 // grid constants of the scheme, computed once on the host in FP64
@@ -89,15 +154,12 @@ struct StepConsts {
     int ax, ay;  // direction has more than one cell
 };
 
-// dt for the step about to start: CFL time step from the reduced wave speeds
-// with the end-time clamp, and the per-step constants derived from it
-__device__ inline void step_begin_dev(DevScalars *sc, double t_end, const StepConsts &k) {
+// dt for the step about to start at time t with wave-speed maxima cx, cy: CFL
+// time step with the end-time clamp, and the per-step constants derived from it
+__device__ inline void step_open(DevScalars *sc, double t_end, const StepConsts &k, double t, int nonphys, double cx,
+                                 double cy) {
     sc->t_end = t_end;
-    if (sc->nonphys) { sc->active = 0; return; }
-    const double t = sc->t;
-    if (t_end > 0.0 && t_end - t <= 1e-12 * t_end) { sc->active = 0; return; }
-    const double cx = __longlong_as_double((long long)sc->cacc[sc->cur][0]);
-    const double cy = __longlong_as_double((long long)sc->cacc[sc->cur][1]);
+    if (nonphys || (t_end > 0.0 && t_end - t <= 1e-12 * t_end)) { sc->active = 0; return; }
     const double dx = k.dx, dy = k.dy;
     double h;
     if (k.ax && k.ay) h = (dx / cx < dy / cy) ? dx / cx : dy / cy;
@@ -105,20 +167,44 @@ __device__ inline void step_begin_dev(DevScalars *sc, double t_end, const StepCo
     else h = dy / cy;
     double dt = k.cfl * h;
     if (t_end > 0.0) dt = (dt < t_end - t) ? dt : t_end - t;
+    const double cmax = (k.ax && k.ay) ? (cx > cy ? cx : cy) : (k.ax ? cx : cy);
     sc->dt = dt;
-    sc->cmax = (k.ax && k.ay) ? (cx > cy ? cx : cy) : (k.ax ? cx : cy);
+    sc->cmax = cmax;
     sc->last_cx = cx;
     sc->last_cy = cy;
-    sc->last_cmax = sc->cmax;
+    sc->last_cmax = cmax;
     sc->hdt = 0.5 * dt;
     sc->dt6 = dt / 6.0;
     for (int m = 0; m < 4; ++m) {
-        sc->kx2[m] = k.c2[m] * dx * sc->cmax;
-        sc->ky2[m] = k.c2[m] * dy * sc->cmax;
+        sc->kx2[m] = k.c2[m] * dx * cmax;
+        sc->ky2[m] = k.c2[m] * dy * cmax;
     }
-    sc->cacc[sc->cur ^ 1][0] = 0ull;
-    sc->cacc[sc->cur ^ 1][1] = 0ull;
     sc->active = 1;
+}
+
+// the same by one thread, from the current slot, with the other slot cleared
+__device__ inline void step_begin_dev(DevScalars *sc, double t_end, const StepConsts &k) {
+    const int cur = sc->cur;
+    step_open(sc, t_end, k, sc->t, sc->nonphys, __longlong_as_double((long long)speed_max(sc->acc[cur], 0)),
+              __longlong_as_double((long long)speed_max(sc->acc[cur], 1)));
+    speed_set(sc->acc[cur ^ 1]);
+}
+
+// Both slots' maxima by a wave: lane 32 s + d gets that of slot s, direction d.
+// One load per lane instead of a chain of them in one thread.
+__device__ __forceinline__ unsigned long long speeds_by_lane(const SpeedWord (&acc)[2][kAcc], int lane) {
+    static_assert(kAcc == 8, "a lane per slot, word and direction (of four)");
+    unsigned long long v = (lane & 3) < 3 ? acc[lane >> 5][(lane >> 2) & 7].v[lane & 3] : 0ull;
+#pragma unroll
+    for (int off = 4; off < 32; off <<= 1) {
+        const unsigned long long o = __shfl_xor(v, off);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+// and clear a slot
+__device__ __forceinline__ void speeds_clear_by_lane(SpeedWord (&slot)[kAcc], int lane) {
+    if (lane < 32 && (lane & 3) < 3) slot[lane >> 2].v[lane & 3] = 0ull;
 }
 
 __device__ inline void step_end_dev(DevScalars *sc) {

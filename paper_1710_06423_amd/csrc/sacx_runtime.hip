@@ -543,22 +543,8 @@ __device__ __forceinline__ void cell_speeds(const real (&u)[NF], real rb, real e
 
 // the maxima of a block of 256 threads into accumulator slot `slot`
 __device__ __forceinline__ void block_speeds(double cx, double cy, int bad, DevScalars *sc, int slot) {
-    __shared__ double red[2][4];
-    for (int off = 32; off > 0; off >>= 1) {
-        cx = fmax(cx, __shfl_xor(cx, off));
-        cy = fmax(cy, __shfl_xor(cy, off));
-        bad |= __shfl_xor(bad, off);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = cx;
-        red[1][threadIdx.x >> 6] = cy;
-        if (bad) atomicOr(&sc->nonphys, 1);
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        const double *r = red[threadIdx.x];
-        raise_max(&sc->cacc[slot][threadIdx.x], fmax(fmax(r[0], r[1]), fmax(r[2], r[3])));
-    }
+    __shared__ double red[3][4];
+    raise_speeds(cx, cy, bad, red, sc, slot);
 }
 
 // the caller's evolved fields into the state, and in the same pass over them
@@ -611,7 +597,8 @@ __global__ void k_reset_scalars(DevScalars *sc, double t0) {
     sc->dt = 0.0;
     sc->cmax = 0.0;
     sc->t_end = 0.0;
-    sc->cacc[0][0] = sc->cacc[0][1] = sc->cacc[1][0] = sc->cacc[1][1] = 0ull;
+    speed_set(sc->acc[0]);
+    speed_set(sc->acc[1]);
     sc->last_cx = sc->last_cy = sc->last_cmax = 0.0;
     sc->steps = 0;
     sc->steps0 = 0;
@@ -623,15 +610,29 @@ __global__ void k_reset_scalars(DevScalars *sc, double t0) {
 
 // dt for the step about to start (CFL time step with the end-time clamp);
 // `prev`: the step before it, of the same call, ends first (one launch for
-// both); otherwise the call begins here
-__global__ void k_step_begin(DevScalars *sc, double t_end, StepConsts k, int prev) {
-    if (prev) {
-        step_end_dev(sc);
-        sc->prev_active = sc->active;
-    } else {
-        sc->steps0 = sc->steps;
+// both); otherwise the call begins here.  One wave: it runs alone between two
+// steps, so its time is that of its chain of loads, and all are issued at once.
+__global__ __launch_bounds__(64) void k_step_begin(DevScalars *sc, double t_end, StepConsts k, int prev) {
+    const int lane = threadIdx.x;
+    const unsigned long long v = speeds_by_lane(sc->acc, lane);
+    const int active = sc->active, cur0 = sc->cur, nonphys = sc->nonphys;
+    const long long steps = sc->steps;
+    const double dt0 = sc->dt, t0 = sc->t;
+    const bool end = prev && active;
+    const int cur = end ? cur0 ^ 1 : cur0;
+    const double cx = __longlong_as_double((long long)__shfl(v, 32 * cur));
+    const double cy = __longlong_as_double((long long)__shfl(v, 32 * cur + 1));
+    speeds_clear_by_lane(sc->acc[cur ^ 1], lane);
+    if (lane) return;
+    const double t = end ? t0 + dt0 : t0;
+    if (prev) sc->prev_active = active;
+    else sc->steps0 = steps;
+    if (end) {
+        sc->t = t;
+        sc->steps = steps + 1;
+        sc->cur = cur;
     }
-    step_begin_dev(sc, t_end, k);
+    step_open(sc, t_end, k, t, nonphys, cx, cy);
 }
 
 __global__ void k_step_end(DevScalars *sc) { step_end_dev(sc); }
@@ -648,8 +649,7 @@ __device__ __forceinline__ void step_begin_global_dev(DevScalars *sc, double cx,
                         (!k.ay || cy > 0.0);
         if (!ok) sc->nonphys = 1;
     }
-    sc->cacc[sc->cur][0] = (unsigned long long)__double_as_longlong(cx);
-    sc->cacc[sc->cur][1] = (unsigned long long)__double_as_longlong(cy);
+    speed_set(sc->acc[sc->cur], (unsigned long long)__double_as_longlong(cx), (unsigned long long)__double_as_longlong(cy));
     step_begin_dev(sc, 0.0, k);
 }
 
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void k_domain_scalars(const BatchInst<real> *_
     for (int i = threadIdx.x; i < n; i += 256) {
         DevScalars *sc = inst[i].sc;
         if (prev) step_end_dev(sc);
-        const unsigned long long a = sc->cacc[sc->cur][0], b = sc->cacc[sc->cur][1];
+        const unsigned long long a = speed_max(sc->acc[sc->cur], 0), b = speed_max(sc->acc[sc->cur], 1);
         m0 = a > m0 ? a : m0;
         m1 = b > m1 ? b : m1;
     }
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(256) void k_domain_ghosts(const BatchInst<real> *__
 // maxima of the current state into a caller array (non-negative doubles
 // order as their bit patterns)
 __global__ void k_speeds_max(const DevScalars *sc, unsigned long long *dc) {
-    if (threadIdx.x < 2) atomicMax(&dc[threadIdx.x], sc->cacc[sc->cur][threadIdx.x]);
+    if (threadIdx.x < 2) atomicMax(&dc[threadIdx.x], speed_max(sc->acc[sc->cur], threadIdx.x));
 }
 
 // conservation sums: per-block partial sums of rows, then a fixed-order final sum
@@ -1443,7 +1443,7 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
         for (int n = n0; n < n1; ++n) {
             {
                 ProfScope ps(ctx, 5);
-                hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t_end, sk, n > 0);
+                hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, ctx->stream, ctx->sc, t_end, sk, n > 0);
             }
             int rc;
             if (ctx->sur_on) {
@@ -1546,8 +1546,8 @@ int sacx_diagnostics(sacx_ctx *ctx, sacx_diag *out) {
     HIPCHK(hipMemcpyAsync(&h, ctx->sc, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipMemcpyAsync(sums, ctx->sums, sizeof(sums), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    const double cx = __builtin_bit_cast(double, h.cacc[h.cur][0]);
-    const double cy = __builtin_bit_cast(double, h.cacc[h.cur][1]);
+    const double cx = __builtin_bit_cast(double, speed_max(h.acc[h.cur], 0));
+    const double cy = __builtin_bit_cast(double, speed_max(h.acc[h.cur], 1));
     out->t = h.t;
     out->dt = h.dt;
     out->c_x = cx;
@@ -1652,7 +1652,7 @@ int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int3
             hipLaunchKernelGGL(k_step_begin_global, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, c_max[0], c_max[1],
                                (const double *)nullptr, step_consts(ctx));
         else
-            hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, 0.0, step_consts(ctx), 0);
+            hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, ctx->stream, ctx->sc, 0.0, step_consts(ctx), 0);
         HIPCHK(hipGetLastError());
     }
     int rc;
@@ -1712,8 +1712,8 @@ int sacx_wave_speeds(sacx_ctx *ctx, double c_max[2]) {
     DevScalars h;
     HIPCHK(hipMemcpyAsync(&h, ctx->sc, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    c_max[0] = __builtin_bit_cast(double, h.cacc[h.cur][0]);
-    c_max[1] = __builtin_bit_cast(double, h.cacc[h.cur][1]);
+    c_max[0] = __builtin_bit_cast(double, speed_max(h.acc[h.cur], 0));
+    c_max[1] = __builtin_bit_cast(double, speed_max(h.acc[h.cur], 1));
     return SACX_OK;
 }
 

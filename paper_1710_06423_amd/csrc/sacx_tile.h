@@ -617,24 +617,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x,
 
     if (STAGE == 4) {
         // block reduction of the wave speeds, one atomic per block
-        auto &red = lds.red;
-        for (int off = 32; off > 0; off >>= 1) {
-            cx_t = fmax(cx_t, __shfl_xor(cx_t, off));
-            cy_t = fmax(cy_t, __shfl_xor(cy_t, off));
-            bad_t |= __shfl_xor(bad_t, off);
-        }
-        const int w = tid >> 6;
-        if ((tid & 63) == 0) { red[0][w] = cx_t; red[1][w] = cy_t; red[2][w] = (double)bad_t; }
-        __syncthreads();
-        if (tid == 0) {
-            double mx_ = 0.0, my_ = 0.0, bb = 0.0;
-            for (int k = 0; k < NT / 64; ++k) { mx_ = fmax(mx_, red[0][k]); my_ = fmax(my_, red[1][k]); bb = fmax(bb, red[2][k]); }
-            DevScalars *scw = a.sc;
-            const int nslot = scw->cur ^ 1;
-            raise_max(&scw->cacc[nslot][0], mx_);
-            raise_max(&scw->cacc[nslot][1], my_);
-            if (bb > 0.0) atomicOr(&scw->nonphys, 1);
-        }
+        raise_speeds(cx_t, cy_t, bad_t, lds.red, a.sc, a.sc->cur ^ 1);
     }
 }
 
@@ -827,24 +810,7 @@ __device__ __forceinline__ void stage_tile_1d(const StageArgs<real> &a, int tile
         }
     }
     if (STAGE == 4) {
-        auto &red = lds.red;
-        for (int off = 32; off > 0; off >>= 1) {
-            cx_t = fmax(cx_t, __shfl_xor(cx_t, off));
-            cy_t = fmax(cy_t, __shfl_xor(cy_t, off));
-            bad_t |= __shfl_xor(bad_t, off);
-        }
-        const int w = tid >> 6;
-        if ((tid & 63) == 0) { red[0][w] = cx_t; red[1][w] = cy_t; red[2][w] = (double)bad_t; }
-        __syncthreads();
-        if (tid == 0) {
-            double mx_ = 0.0, my_ = 0.0, bb = 0.0;
-            for (int k = 0; k < NT / 64; ++k) { mx_ = fmax(mx_, red[0][k]); my_ = fmax(my_, red[1][k]); bb = fmax(bb, red[2][k]); }
-            DevScalars *scw = a.sc;
-            const int nslot = scw->cur ^ 1;
-            raise_max(&scw->cacc[nslot][0], mx_);
-            raise_max(&scw->cacc[nslot][1], my_);
-            if (bb > 0.0) atomicOr(&scw->nonphys, 1);
-        }
+        raise_speeds(cx_t, cy_t, bad_t, lds.red, a.sc, a.sc->cur ^ 1);
     }
 }
 

@@ -487,26 +487,7 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
         }
     }
     if (STAGE == 4) {
-        for (int off = 32; off > 0; off >>= 1) {
-            cx_t = fmax(cx_t, __shfl_xor(cx_t, off));
-            cy_t = fmax(cy_t, __shfl_xor(cy_t, off));
-            bad_t |= __shfl_xor(bad_t, off);
-        }
-        if (t == 0) { lds.red[0][w] = cx_t; lds.red[1][w] = cy_t; lds.red[2][w] = (double)bad_t; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            DevScalars *scw = a.sc;
-            const int nslot = scw->cur ^ 1;
-            double m0 = 0.0, m1 = 0.0, bb = 0.0;
-            for (int k = 0; k < W; ++k) {
-                m0 = fmax(m0, lds.red[0][k]);
-                m1 = fmax(m1, lds.red[1][k]);
-                bb = fmax(bb, lds.red[2][k]);
-            }
-            raise_max(&scw->cacc[nslot][0], m0);
-            raise_max(&scw->cacc[nslot][1], m1);
-            if (bb > 0.0) atomicOr(&scw->nonphys, 1);
-        }
+        raise_speeds(cx_t, cy_t, bad_t, lds.red, a.sc, a.sc->cur ^ 1);
     }
 }
 

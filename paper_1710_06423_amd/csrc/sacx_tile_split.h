@@ -679,24 +679,7 @@ __device__ __forceinline__ void stage_tile_split(const StageArgs<real> &a, int t
     }
     if (STAGE == 4) {
         // block reduction of the wave speeds, one atomic per block
-        auto &red = lds.red;
-        for (int off = 32; off > 0; off >>= 1) {
-            cx_t = fmax(cx_t, __shfl_xor(cx_t, off));
-            cy_t = fmax(cy_t, __shfl_xor(cy_t, off));
-            bad_t |= __shfl_xor(bad_t, off);
-        }
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) { red[0][w] = cx_t; red[1][w] = cy_t; red[2][w] = (double)bad_t; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double mx_ = 0.0, my_ = 0.0, bb = 0.0;
-            for (int k = 0; k < 2 * NC / 64; ++k) { mx_ = fmax(mx_, red[0][k]); my_ = fmax(my_, red[1][k]); bb = fmax(bb, red[2][k]); }
-            DevScalars *scw = a.sc;
-            const int nslot = scw->cur ^ 1;
-            raise_max(&scw->cacc[nslot][0], mx_);
-            raise_max(&scw->cacc[nslot][1], my_);
-            if (bb > 0.0) atomicOr(&scw->nonphys, 1);
-        }
+        raise_speeds(cx_t, cy_t, bad_t, lds.red, a.sc, a.sc->cur ^ 1);
     }
 }
 

@@ -244,26 +244,7 @@ __global__ __launch_bounds__(NT) void k_tube_step(TubeArgs<real> a) {
             }
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        cx_t = fmax(cx_t, __shfl_xor(cx_t, off));
-        cy_t = fmax(cy_t, __shfl_xor(cy_t, off));
-        bad_t |= __shfl_xor(bad_t, off);
-    }
-    const int w = tid >> 6;
-    if ((tid & 63) == 0) { lds.red[0][w] = cx_t; lds.red[1][w] = cy_t; lds.red[2][w] = (double)bad_t; }
-    __syncthreads();
-    if (tid == 0) {
-        double m0 = 0.0, m1 = 0.0, bb = 0.0;
-        for (int k = 0; k < NT / 64; ++k) {
-            m0 = fmax(m0, lds.red[0][k]);
-            m1 = fmax(m1, lds.red[1][k]);
-            bb = fmax(bb, lds.red[2][k]);
-        }
-        const int nslot = sc->cur ^ 1;
-        raise_max(&sc->cacc[nslot][0], m0);
-        raise_max(&sc->cacc[nslot][1], m1);
-        if (bb > 0.0) atomicOr(&sc->nonphys, 1);
-    }
+    raise_speeds(cx_t, cy_t, bad_t, lds.red, sc, sc->cur ^ 1);
 }
 
 template <typename real>

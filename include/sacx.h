@@ -319,8 +319,11 @@ int sacx_domain_destroy(sacx_domain *d);
  * that needs at most 160 rows; else strips balanced to fit one round when
  * that needs at most 512 rows, else 256 rows (halved while there are fewer
  * than 1024 blocks).  Both are chosen again whenever threads or the tile kind
- * change.  Setting rows alone takes 128 columns in FP64 and 256 in FP32.  Results do not depend on the
- * shape (bit-identical); only speed does.  Used by the tile autotuner. */
+ * change.  Setting rows alone takes 128 columns in FP64 and 256 in FP32.
+ * Until either is set, launches need not have this shape: small and middle
+ * grids take blocks of 8 or 16 rows, steps without hyper-diffusion two stages
+ * per launch, tubes a whole step.  Results do not depend on the shape
+ * (bit-identical); only speed does.  Used by the tile autotuner. */
 int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows);
 int sacx_get_launch(const sacx_ctx *ctx, int32_t *threads, int32_t *rows);
 
@@ -337,10 +340,12 @@ int sacx_set_column_split(sacx_ctx *ctx, int32_t on);
  * group), used to split a run into useful computation and halo exchange as in
  * the paper's cost model T = T_comp + T_comm + T_idle (section 6).
  *  ms_stage[s] / n_stage[s]: the fused stage-s kernel (s = 0..3 for stages 1..4);
+ *                    a launch of two stages counts as the second of them, a
+ *                    tube's launch of a whole step as stage 1;
  *  ms_halo / n_halo: halo pack + unpack (or boundary fill) before each stage,
  *                    and each sacx_fill_boundaries, sacx_halo_pack and
  *                    sacx_halo_unpack call;
- *  ms_scalar / n_scalar: the one-thread time-step kernels;
+ *  ms_scalar / n_scalar: the time-step kernels;
  *  ms_surrogate / n_surrogate: surrogate refreshes (prediction and check).
  * sacx_profile_enable(ctx, 1) resets the accumulators and starts recording;
  * (ctx, 0) stops.  sacx_profile_read synchronises and returns the totals. */

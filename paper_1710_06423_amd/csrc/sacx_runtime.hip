@@ -79,6 +79,7 @@ struct sacx_ctx {
     int ty, nt;
     int split;         // FP64 hyper-diffusion tiles: two threads per column
     int box;           // rows of the box kernel's blocks (8, 16); 0: the marching kernels
+    int pair_rows;          // rows per block of the two-stage kernel
     bool nt_auto, ty_auto;  // columns / strip height chosen by auto_rows (until set explicitly)
     double dx, dy;
     SchemeConsts kc;
@@ -275,6 +276,18 @@ int box_for(bool fp32, bool hd, int64_t tiles8, int64_t tiles16, int cus, double
     return rows;
 }
 
+// Two stages per launch: without hyper-diffusion (with it a stage reaches 3
+// cells to each side and is not bound by memory), a background or exchange
+// sides, in the automatic launch shape, on grids whose periodic images are
+// one period away from 4 cells outside.  Faster at every size tried, 64^2
+// (29 -> 21 us per step) to 4000^2 (2524 -> 1400).
+bool stage_pairs(const sacx_ctx *c) {
+    if (c->params.hd_on || c->grid.background_on || c->sur_on || !c->nt_auto || !c->ty_auto) return false;
+    for (int k = 0; k < 4; ++k)
+        if (c->bc[k] == SACX_EXCHANGE) return false;
+    return c->L.nx >= 8 && c->L.ny >= 8;
+}
+
 int64_t box_tiles(const Layout &L, int rows) { return (int64_t)((L.nx + 57) / 58) * ((L.ny + rows - 1) / rows); }
 
 // the launch shape for the context's current settings: resident blocks from
@@ -287,6 +300,11 @@ void auto_rows(sacx_ctx *c) {
     const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
     c->box = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
+    // 24 rows per block re-read and recompute less, 8 make more blocks: even
+    // at 3 to 4 blocks of 8 rows per compute unit (700 x 500 FP64 60 us per
+    // step with 24, 54 with 8; 900 x 700 72 and 77)
+    const int64_t t8 = (int64_t)((c->L.nx + 55) / 56) * ((c->L.ny + 7) / 8);
+    c->pair_rows = t8 > 4 * (int64_t)(e == hipSuccess && cus > 0 ? cus : 256) ? 24 : 8;
     if (c->nt_auto) {
         c->nt = fp64 ? 128 : 256;
         double us = 0.0;
@@ -1053,6 +1071,25 @@ int tube_step(sacx_ctx *c, void *const *from, void *const *to, bool second) {
     return SACX_OK;
 }
 
+// a step without hyper-diffusion in two launches, from `from` to `to`
+template <typename real>
+int pair_step(sacx_ctx *c, void *const *from, void *const *to, bool second) {
+    for (int h = 0; h < 2; ++h) {
+        ProfScope ps(c, h ? 3 : 1);
+        StageArgs<real> a = stage_args<real>(c);
+        for (int f = 0; f < NF; ++f) {
+            a.S[f] = (const real *)(h ? c->B2[f] : from[f]);
+            a.U[f] = (const real *)from[f];
+            a.A[f] = (const real *)c->A[f];
+            a.out1[f] = (real *)(h ? to[f] : c->B2[f]);
+            a.out2[f] = (real *)c->A[f];
+        }
+        if (!fields_uniform(a)) return fail(SACX_EINVAL, "internal: stage buffers are not laid out at a uniform field stride");
+        HIPCHK(launch_pair<real>(h != 0, second, c->pair_rows, a, c->stream));
+    }
+    return SACX_OK;
+}
+
 int stage(sacx_ctx *c, int s, void *const *S, void *const *U, void *const *A, void *const *o1, void *const *o2) {
     if (narrow(c, 0) || narrow(c, 1)) {
         ProfScope ps(c, 4);
@@ -1434,7 +1471,9 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
     const StepConsts sk = step_consts(ctx);
     // a tube's steps take one launch each, but for the last of an odd number
     const bool tube = ctx->L.ny == 1 && ctx->L.nx >= 2 && !ctx->grid.background_on && !ctx->sur_on;
-    const int tube_steps = tube ? nsteps & ~1 : 0;
+    // and without hyper-diffusion two
+    const bool pairs = !tube && stage_pairs(ctx);
+    const int whole_steps = tube || pairs ? nsteps & ~1 : 0;
     // A synchronising call enqueues in chunks and stops early once the device
     // reports that stepping ended (end time reached or non-physical state).
     const int chunk = sync ? 128 : (nsteps > 0 ? nsteps : 1);
@@ -1453,10 +1492,17 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
                 }
                 ctx->sur_since += 1;
             }
-            if (n < tube_steps) {
-                // in pairs, U to B2 and back, so that a call ends with its state in U
-                ProfScope ps(ctx, 0);
+            if (n < whole_steps) {
+                // in pairs, U to another buffer and back, so that a call ends with its state in U
                 const bool second = n & 1;
+                if (pairs) {
+                    void *const *from = second ? ctx->B1 : ctx->U, *const *to = second ? ctx->U : ctx->B1;
+                    if ((rc = ctx->grid.precision == SACX_FP64 ? pair_step<double>(ctx, from, to, second)
+                                                               : pair_step<float>(ctx, from, to, second)))
+                        return rc;
+                    continue;
+                }
+                ProfScope ps(ctx, 0);
                 void *const *from = second ? ctx->B2 : ctx->U, *const *to = second ? ctx->U : ctx->B2;
                 if ((rc = ctx->grid.precision == SACX_FP64 ? tube_step<double>(ctx, from, to, second)
                                                            : tube_step<float>(ctx, from, to, second)))

@@ -1,4 +1,4 @@
-// sacx_box_kernel.h -- the box stage kernel and its launchers of the box stage kernel, as templates; each
+// sacx_box_kernel.h -- the box stage kernel and its launchers, as templates; each
 // precision is instantiated in a unit of its own with the contraction rule of
 // that precision's stage kernel.
 #pragma once
@@ -64,11 +64,14 @@ hipError_t launch_batch_box(const BatchArgs<real> &b, int rows, int stage, bool 
               : launch_batch_box_r<real, 8, 1, false>(b, stage, tiles, s);
 }
 
-// rows: 8 (one row per wave) or, FP32 with hyper-diffusion, 16 (two)
+// rows: 8 (one row per wave) or, with hyper-diffusion, 4 in FP64 (four waves)
+// and 16 in FP32 (two rows per wave)
 template <typename real>
 hipError_t launch_box(int stage, bool hd, int rows, const StageArgs<real> &a, hipStream_t s) {
     if constexpr (sizeof(real) == 4) {
         if (hd && rows == 16) return launch_box_r<real, 8, 2, true>(stage, a, s);
+    } else {
+        if (hd && rows == 4) return launch_box_r<real, 4, 1, true>(stage, a, s);
     }
     return hd ? launch_box_r<real, 8, 1, true>(stage, a, s) : launch_box_r<real, 8, 1, false>(stage, a, s);
 }

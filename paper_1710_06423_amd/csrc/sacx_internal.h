@@ -387,8 +387,8 @@ hipError_t launch_tube_step(bool hd, const TubeArgs<real> &a, hipStream_t s);
 // state buffer but the one that the step before wrote; rows: 8 or 24 per block
 template <typename real>
 hipError_t launch_pair(bool last, bool second, int rows, const StageArgs<real> &a, hipStream_t s);
-// the box kernel, 58 columns x `rows` rows per block (8, or 16 in FP32 with
-// hyper-diffusion); no background, plain coefficient
+// the box kernel, 58 columns x `rows` rows per block (8, or with hyper-diffusion
+// 4 in FP64 and 16 in FP32); no background, plain coefficient
 template <typename real>
 hipError_t launch_box(int stage, bool hd, int rows, const StageArgs<real> &a, hipStream_t s);
 template <typename real>

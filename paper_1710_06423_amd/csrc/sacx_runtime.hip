@@ -310,6 +310,12 @@ void auto_rows(sacx_ctx *c) {
         double us = 0.0;
         if (e == hipSuccess && cus >= 1 && shape_for_slots(c, cus, &c->nt, &c->ty, &us)) {
             if (!bg) c->box = box_for(!fp64, hd, box_tiles(c->L, 8), box_tiles(c->L, 16), cus, us);
+            // FP64 with half the rows while that makes no more blocks than
+            // compute units: a wave's work is issue-bound there and twice the
+            // units share it (64^2 40.1 -> 36.1 us per step, 300 x 136
+            // 43.1 -> 40.3; 400 x 200, with 350 blocks, 46.9 -> 51.0; FP32
+            // 30.6 -> 30.6 and slower)
+            if (c->box == 8 && fp64 && hd && box_tiles(c->L, 4) <= cus) c->box = 4;
             return;
         }
     }

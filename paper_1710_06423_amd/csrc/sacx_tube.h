@@ -7,7 +7,7 @@
 // at the step's start, so a block can take its cells through all four stages
 // by itself: it computes 12 more cells on each side (3 per stage) and keeps
 // the stage states in registers, sharing primitives and fluxes through LDS.
-// 800 points, 40 steps with their initial state and fields read: 0.58 ms
+// 800 points, 40 steps with their initial state and fields read: 0.54 ms
 // from 0.92.
 //
 // A block of NT threads owns NT - 24 cells.  The step reads U and writes the
@@ -247,13 +247,23 @@ __global__ __launch_bounds__(NT) void k_tube_step(TubeArgs<real> a) {
     raise_speeds(cx_t, cy_t, bad_t, lds.red, sc, sc->cur ^ 1);
 }
 
-template <typename real>
-hipError_t launch_tube_step(bool hd, const TubeArgs<real> &a, hipStream_t s) {
-    constexpr int NT = 256, TX = NT - 8 * G;
+template <typename real, int NT>
+static hipError_t launch_tube_nt(bool hd, const TubeArgs<real> &a, hipStream_t s) {
+    constexpr int TX = NT - 8 * G;
     const dim3 g((a.L.nx + TX - 1) / TX);
     if (hd) hipLaunchKernelGGL((k_tube_step<real, NT, true>), g, dim3(NT), 0, s, a);
     else hipLaunchKernelGGL((k_tube_step<real, NT, false>), g, dim3(NT), 0, s, a);
     return hipGetLastError();
+}
+
+// One wave per block (40 of its 64 cells written, no wait for other waves)
+// while that makes at most 256 blocks, a compute unit each: 800 cells 14.7 ->
+// 13.4 us per step in FP64 and 12.5 -> 11.6 in FP32, 3000 15.4 -> 13.3 and
+// 12.9 -> 11.7.  Longer tubes recompute less with four: 200000 cells 38 us and
+// 27 us, against 42 and 33.
+template <typename real>
+hipError_t launch_tube_step(bool hd, const TubeArgs<real> &a, hipStream_t s) {
+    return a.L.nx <= 256 * (64 - 8 * G) ? launch_tube_nt<real, 64>(hd, a, s) : launch_tube_nt<real, 256>(hd, a, s);
 }
 
 }  // namespace sacx

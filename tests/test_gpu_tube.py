@@ -1,6 +1,6 @@
 """A tube's whole steps in one launch each (pairs of steps of one call) against
 the oracle and against single steps, which run stage by stage: lengths around
-its blocks' 232 cells, both kinds of ends, and calls that stop inside a pair."""
+its blocks' 40 cells, and 232 from 10241 cells on, both kinds of ends, and calls that stop inside a pair."""
 
 import numpy as np
 import pytest
@@ -21,7 +21,7 @@ def _tube(n, bc, seed=3):
     return W.random_smooth(n, 1, seed=seed + n, bc=(bc[0], bc[1], 0, 0))
 
 
-@pytest.mark.parametrize("n", [2, 3, 5, 23, 231, 232, 233, 464, 801])
+@pytest.mark.parametrize("n", [2, 3, 5, 23, 39, 40, 41, 80, 231, 232, 233, 464, 801, 10240, 10241, 10440])
 @pytest.mark.parametrize("bc", [(0, 0), (1, 1)])
 @pytest.mark.parametrize("hd", [True, False])
 def test_tube_steps_match_oracle(oracle_lib, n, bc, hd):

@@ -68,6 +68,17 @@ __device__ __forceinline__ double lane_left(double v) {
                             __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, false));
 }
 
+// the value of the lane to the right (lane 63 keeps its own, unused)
+__device__ __forceinline__ float lane_right(float v) {
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x130, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double lane_right(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
+}
+
 // keeps the LDS reads of the next quantity out of the registers of this one
 // (FP64 with two rows per wave: without it 364-476 B of scratch per lane)
 template <typename real, int R>
@@ -141,6 +152,12 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
         for (int f = 0; f < NF; ++f) u[k].v[f] = a.S[0][o + f * fs];
     }
     real vx[NK], vy[NK], eps[NK], fyo[R][5];
+    // D_x F_x through register lanes in FP64, where LDS is as busy as the
+    // vector units (2 x 2 subdomains of 1024^2 in all 1291 -> 1268 us, 1024^2
+    // 2104 -> 2092); FP32 is bound by vector issue (2048^2 3700 -> 3715 us,
+    // 8 tubes and 8 boxes 2934 -> 3014) and goes through LDS
+    constexpr bool LANES = sizeof(real) == 8;
+    real dxo[R][5];
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
         if (!has[k]) continue;
@@ -166,11 +183,22 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
             lds.v[1][row[k] + 3][t] = vy[k];
         }
         if (k < R) {
-            lds.f.fx[CR][row[k]][t] = mx;
-            lds.f.fx[CMX][row[k]][t] = (vx[k] * mx - (bxt * bxt + two * bxt * bxb)) + pt;
-            lds.f.fx[CMY][row[k]][t] = vx[k] * my - (bxt * byt + bxt * byb + bxb * byt);
-            lds.f.fx[CE][row[k]][t] = ((vx[k] * ef - bxt * bvt) - bxt * bvb) - bxb * bvt;
-            lds.f.fx[CB][row[k]][t] = vx[k] * byT - bxT * vy[k];
+            real fx[5];
+            fx[CR] = mx;
+            fx[CMX] = (vx[k] * mx - (bxt * bxt + two * bxt * bxb)) + pt;
+            fx[CMY] = vx[k] * my - (bxt * byt + bxt * byb + bxb * byt);
+            fx[CE] = ((vx[k] * ef - bxt * bvt) - bxt * bvb) - bxb * bvt;
+            fx[CB] = vx[k] * byT - bxT * vy[k];
+#pragma unroll
+            for (int m = 0; m < 5; ++m) {
+                if constexpr (LANES) {
+                    const real l1 = lane_left(fx[m]), l2 = lane_left(l1), r1 = lane_right(fx[m]), r2 = lane_right(r1);
+                    dxo[k][m] = (eight * (r1 - l1) - (r2 - l2)) * i12dx;
+                    settle(dxo[k][m]);
+                } else {
+                    lds.f.fx[m][row[k]][t] = fx[m];
+                }
+            }
         }
         if (k < R || (row[k] >= -2 && row[k] <= TY + 1)) {
             real fy[5];
@@ -200,8 +228,13 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
 #pragma unroll
             for (int k = 0; k < R; ++k) {
                 const real dy = (eight * (fw[k + 3] - fw[k + 1]) - (fw[k + 4] - fw[k])) * i12dy;
-                const real *fx = lds.f.fx[m][j0 + k];
-                const real dx = (eight * (fx[tp1] - fx[tm1]) - (fx[tp2] - fx[tm2])) * i12dx;
+                real dx;
+                if constexpr (LANES) {
+                    dx = dxo[k][m];
+                } else {
+                    const real *fx = lds.f.fx[m][j0 + k];
+                    dx = (eight * (fx[tp1] - fx[tm1]) - (fx[tp2] - fx[tm2])) * i12dx;
+                }
                 if (m < CB) {
                     K[k][m] = -(dx + dy);
                     settle(K[k][m]);

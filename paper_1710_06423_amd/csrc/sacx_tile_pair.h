@@ -39,16 +39,6 @@ struct PairLds {
     double red[3][W];
 };
 
-// the value of the lane to the right (lane 63 keeps its own, unused)
-__device__ __forceinline__ float lane_right(float v) {
-    const int i = __float_as_int(v);
-    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x130, 0xf, 0xf, false));
-}
-__device__ __forceinline__ double lane_right(double v) {
-    const int lo = __double2loint(v), hi = __double2hiint(v);
-    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xf, 0xf, false),
-                            __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
-}
 // the value of one lane, the same in all
 __device__ __forceinline__ float lane_value(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));

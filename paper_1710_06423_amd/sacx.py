@@ -359,7 +359,10 @@ class Solver:
             return rc, done.value, t.value
 
     def read_fields(self, dtype: torch.dtype = torch.float64, mask: int = 0x3F) -> torch.Tensor:
-        out = torch.zeros((6, self.grid.ny, self.grid.nx), dtype=dtype, device=self.device)
+        # fields left out of the mask read as zero; with all of them every
+        # element is written (clearing 8000^2 in FP64 first took 0.45 ms)
+        alloc = torch.empty if mask == 0x3F and dtype in (torch.float64, torch.float32) else torch.zeros
+        out = alloc((6, self.grid.ny, self.grid.nx), dtype=dtype, device=self.device)
         prec = FP64 if dtype == torch.float64 else FP32
         with self._shared():
             _check(self.lib.sacx_read_fields(self.ctx, _ptrs([out[k] for k in range(6)]), self.grid.nx, mask, prec),

@@ -183,7 +183,9 @@ class Solver3:
 
     def read_fields(self, mask: int = 0xFF) -> torch.Tensor:
         g = self.grid
-        out = torch.zeros((8, g.nz, g.ny, g.nx), dtype=torch.float64, device=self.device)
+        # fields left out of the mask read as zero
+        alloc = torch.empty if mask == 0xFF else torch.zeros
+        out = alloc((8, g.nz, g.ny, g.nx), dtype=torch.float64, device=self.device)
         with self._shared():
             _s._check(self.lib.sacx3_read_fields(self.ctx, _s._ptrs([out[k] for k in range(8)]), g.nx, g.nx * g.ny,
                                                  int(mask)), "sacx3_read_fields")

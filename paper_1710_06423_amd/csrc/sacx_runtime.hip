@@ -2055,8 +2055,9 @@ void list_tiles(const sacx_ctx *c, int i, int nt, int rows, int box, std::vector
 // shape_for_slots chooses them for one grid: the cheapest (time per row) x
 // (rows + 9) over the widths and the numbers of blocks per compute unit, the
 // rows those that bring the tiles of all the contexts to that many blocks.
+// False where none fits one round of resident blocks.
 template <typename real>
-void shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int *nt, int *rows, int *box) {
+bool shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int *nt, int *rows, int *box) {
     const bool hd = ctx[0]->params.hd_on != 0;
     const int kind = sizeof(real) == 8 ? (hd ? KIND_SPLIT : KIND_F64_NOHD) : (hd ? KIND_F32 : KIND_F32_NOHD);
     double best = 0.0;
@@ -2095,6 +2096,7 @@ void shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int
     bool boxes = false;   // (tubes alone run in blocks of their own width)
     for (const sacx_ctx *c : ctx) boxes = boxes || c->L.ny > 1;
     *box = best == 0.0 || !boxes ? 0 : box_for(sizeof(real) == 4, hd, t8, t16, cus, best);
+    return best > 0.0;
 }
 
 // one context's entry of an instance table, for tiles of nt columns and `rows` rows
@@ -2486,6 +2488,7 @@ struct sacx_domain {
     char *tab;
     BatchItem *items;
     int ntiles, nt, box;
+    bool each;   // stage launches by subdomain, in each one's own launch shape
     bool split;
     bool built;
     unsigned long long gen_built;
@@ -2515,10 +2518,11 @@ int domain_build(sacx_domain *d, unsigned long long gen) {
         set = set || !c->nt_auto || !c->ty_auto;
     }
     int rows = 0, cus = 0;
+    bool one_round = false;
     d->box = 0;
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c0->device));
     if (set) d->nt = c0->nt;
-    else shape_for_many<real>(subs, cus, d->split, &d->nt, &rows, &d->box);
+    else one_round = shape_for_many<real>(subs, cus, d->split, &d->nt, &rows, &d->box);
     std::vector<BatchInst<real>> tab(n);
     std::vector<BatchItem> items;
     for (const sacx_ctx *c : subs)   // the one-thread tile was asked for
@@ -2531,6 +2535,14 @@ int domain_build(sacx_domain *d, unsigned long long gen) {
         list_tiles(c, i, d->nt, ty, d->box, &items);
     }
     d->ntiles = (int)items.size();
+    // A list of several rounds of blocks against launches by subdomain, each in
+    // the shape of its own grid, ms per step: FP64 2000^2 cells each 3.14 and
+    // 3.13, 2500^2 5.65 and 4.75, 4000^2 12.5 and 12.0, 2000 x 4000 13.4 and
+    // 12.4, but 1000 x 2000 3.16 and 3.31; FP32 4000^2 5.54 and 5.34, 2000 x
+    // 4000 5.60 and 5.53, but 2000^2 1.43 and 1.49.
+    int64_t cells = INT64_MAX;
+    for (const sacx_ctx *c : subs) cells = std::min(cells, (int64_t)c->L.nx * c->L.ny);
+    d->each = d->box == 0 && !one_round && cells >= (sizeof(real) == 8 ? 4000000 : 8000000);
     HIPCHK(hipMemcpyAsync(d->tab, tab.data(), sizeof(tab[0]) * n, hipMemcpyHostToDevice, c0->stream));
     HIPCHK(hipMemcpyAsync(d->items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice, c0->stream));
     // the host vectors go out of scope: finish the copies first
@@ -2540,7 +2552,7 @@ int domain_build(sacx_domain *d, unsigned long long gen) {
     return SACX_OK;
 }
 
-// nsteps steps, every launch over all subdomains
+// nsteps steps, every launch over all subdomains (but the stages of large ones)
 template <typename real>
 int domain_steps(sacx_domain *d, int nsteps) {
     sacx_ctx *c0 = (*d->subs)[0];
@@ -2567,6 +2579,15 @@ int domain_steps(sacx_domain *d, int nsteps) {
             if (exchange) {
                 ProfScope ps(c0, 4);
                 hipLaunchKernelGGL(k_domain_ghosts<real>, gg, dim3(256), 0, c0->stream, a.inst, st - 1, d->px, d->py);
+            }
+            if (d->each) {
+                for (sacx_ctx *c : *d->subs) {
+                    void *const *S[4] = {c->U, c->B1, c->B2, c->B1};
+                    void *const *O[4] = {c->B1, c->B2, c->B1, c->U};
+                    const int rc = stage(c, st, S[st - 1], c->U, c->A, O[st - 1], c->A);
+                    if (rc) return rc;
+                }
+                continue;
             }
             ProfScope ps(c0, st - 1);
             const int tiles = d->ntiles;

@@ -63,3 +63,23 @@ def test_eager_calls_between_replays():
     assert torch.equal(d.read_fields(), one.read_fields())
     d.close()
     one.close()
+
+
+@pytest.mark.parametrize("precision,shape,xc,yc", [
+    (0, (4003, 4001), [0, 2002, 4003], [0, 2000, 4001]),   # stages launched by subdomain
+    (0, (4003, 3900), [0, 2002, 4003], [0, 1950, 3900]),   # from one list, several rounds of blocks
+    (1, (5800, 2900), [0, 2900, 5800], [0, 2900]),
+])
+def test_large_subdomains_keep_the_bits(precision, shape, xc, yc):
+    torch = _torch()
+    from paper_1710_06423_amd import DecomposedSolver, Solver
+    prob = W.orszag_tang(shape[0], ny=shape[1])
+    print(f"case: {shape} cuts {xc} {yc} precision {precision}", flush=True)
+    one = Solver.from_problem(prob, precision=precision)
+    d = DecomposedSolver(prob, xc, yc, precision=precision)
+    d.advance(3)
+    one.advance(3)
+    assert torch.equal(d.read_fields(), one.read_fields())
+    assert d.diagnostics()[0][0]["t"] == one.diagnostics()["t"]
+    d.close()
+    one.close()

@@ -2055,7 +2055,7 @@ void list_tiles(const sacx_ctx *c, int i, int nt, int rows, int box, std::vector
 // shape_for_slots chooses them for one grid: the cheapest (time per row) x
 // (rows + 9) over the widths and the numbers of blocks per compute unit, the
 // rows those that bring the tiles of all the contexts to that many blocks.
-// False where none fits one round of resident blocks.
+// False where none of at most 256 rows fits one round of resident blocks.
 template <typename real>
 bool shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int *nt, int *rows, int *box) {
     const bool hd = ctx[0]->params.hd_on != 0;
@@ -2063,31 +2063,45 @@ bool shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int
     double best = 0.0;
     *rows = 256;
     *nt = sizeof(real) == 8 ? 128 : 256;
-    for (int w = 0; w < 3; ++w) {
-        const int cols = 64 << w, TX = cols - 2 * G;
-        int per = 0;
-        if (many_blocks_per_cu<real>(cols, hd, split, &per) != hipSuccess) { (void)hipGetLastError(); continue; }
-        for (int k = 1; k <= std::min(per, 8); ++k) {
-            const float us = kRowUs[kind][w][k - 1];
-            if (us == 0.0f) break;
-            auto tiles = [&](int ty) {
-                int64_t t = 0;
-                for (const sacx_ctx *c : ctx)
-                    if (c->L.ny > 1) t += (int64_t)((c->L.nx + TX - 1) / TX) * ((c->L.ny + ty - 1) / ty);
-                return t;
-            };
-            int lo = 1, hi = 257;   // the fewest rows whose tiles fit (257: none up to 256)
-            while (lo < hi) {
-                const int mid = (lo + hi) / 2;
-                if (tiles(mid) <= (int64_t)cus * k) hi = mid; else lo = mid + 1;
+    auto tiles = [&](int cols, int ty) {
+        const int TX = cols - 2 * G;
+        int64_t t = 0;
+        for (const sacx_ctx *c : ctx)
+            if (c->L.ny > 1) t += (int64_t)((c->L.nx + TX - 1) / TX) * ((c->L.ny + ty - 1) / ty);
+        return t;
+    };
+    // the cheapest shape of one round with at most `limit` rows
+    auto one_round = [&](int limit) {
+        for (int w = 0; w < 3; ++w) {
+            const int cols = 64 << w;
+            int per = 0;
+            if (many_blocks_per_cu<real>(cols, hd, split, &per) != hipSuccess) { (void)hipGetLastError(); continue; }
+            for (int k = 1; k <= std::min(per, 8); ++k) {
+                const float us = kRowUs[kind][w][k - 1];
+                if (us == 0.0f) break;
+                int lo = 1, hi = limit + 1;   // the fewest rows whose tiles fit (limit + 1: none)
+                while (lo < hi) {
+                    const int mid = (lo + hi) / 2;
+                    if (tiles(cols, mid) <= (int64_t)cus * k) hi = mid; else lo = mid + 1;
+                }
+                if (lo > limit) continue;
+                const double cost = us * (lo + 9.0);
+                if (best == 0.0 || cost < best) { best = cost; *nt = cols; *rows = lo; }
             }
-            if (lo > 256) continue;
-            const double cost = us * (lo + 9.0);
-            if (best == 0.0 || cost < best) { best = cost; *nt = cols; *rows = lo; }
         }
+        return best > 0.0;
+    };
+    if (!one_round(256)) {
+        // Strips of up to 512 rows in one round, against several rounds of
+        // 256: FP64 only where those are more than 1.3 rounds (two blocks per
+        // compute unit).  ms per step: FP64 4 x 2500^2 6.42 -> 5.23, 8 x 2000^2
+        // 8.97 -> 6.70, but 4 x 2000^2 (1.06 rounds) 3.39 -> 3.49; FP32 4 x 3000^2
+        // (1.13 rounds) 4.77 -> 3.35.
+        if (sizeof(real) == 4 || (double)tiles(*nt, 256) > 1.3 * 2.0 * cus) one_round(512);
+        *box = 0;
+        return false;
     }
-    // boxes instead where they are expected to be faster (past the shapes
-    // above a marching block takes 256 rows, which the boxes do not beat)
+    // boxes instead where they are expected to be faster
     int64_t t8 = 0, t16 = 0;
     for (const sacx_ctx *c : ctx) {
         t8 += c->L.ny > 1 ? box_tiles(c->L, 8) : (c->L.nx + kTubeCells - 1) / kTubeCells;
@@ -2095,8 +2109,8 @@ bool shape_for_many(const std::vector<sacx_ctx *> &ctx, int cus, bool split, int
     }
     bool boxes = false;   // (tubes alone run in blocks of their own width)
     for (const sacx_ctx *c : ctx) boxes = boxes || c->L.ny > 1;
-    *box = best == 0.0 || !boxes ? 0 : box_for(sizeof(real) == 4, hd, t8, t16, cus, best);
-    return best > 0.0;
+    *box = !boxes ? 0 : box_for(sizeof(real) == 4, hd, t8, t16, cus, best);
+    return true;
 }
 
 // one context's entry of an instance table, for tiles of nt columns and `rows` rows

@@ -38,3 +38,24 @@ def test_stage_launches_equal_the_persistent_launch(monkeypatch, precision, tile
         assert np.array_equal(out[0][i], out[1][i]), i
         assert np.array_equal(out[0][i], s.read_fields().cpu().numpy()), i
         s.close()
+
+
+@pytest.mark.parametrize("precision,sizes", [
+    (0, [(2600, 2400), (2500, 2600), (2400, 2500), (2700, 2500)]),   # one round of strips longer than 256 rows
+    (1, [(3000, 2900), (2900, 3000), (3000, 3000), (2800, 3000)]),
+])
+def test_large_instances_equal_single_runs(precision, sizes):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1710_06423_amd import Batch, Solver
+    print(f"case: {sizes} precision {precision}", flush=True)
+    probs = [W.orszag_tang(nx, ny=ny) for nx, ny in sizes]
+    b = Batch(probs, precision=precision)
+    b.advance(2)
+    for i, p in enumerate(probs):
+        s = Solver.from_problem(p, precision=precision)
+        s.advance(2)
+        assert torch.equal(b[i].read_fields(), s.read_fields())
+        s.close()
+    b.close()

@@ -9,11 +9,12 @@
  * coefficient is the ratio of third- to first-order differences scaled by the
  * maximum wave speed (plus a compression term), classic fourth-order
  * Runge-Kutta in time with a CFL time step.  One context is one GPU's
- * subdomain; its halo ("ghost") layers are exchanged through device-side
- * pack/unpack buffers (paper section 3, the halo exchange of Fig. 1 and the
- * exchange_halo listing), with periodic self-exchange or open
- * (zero-gradient) boundaries applied locally, or, for a domain split into
- * subdomain contexts, filled from the neighbours before every stage.
+ * subdomain; the cells beyond a periodic or open (zero-gradient) side are read
+ * where the boundary has their values, and for a domain split into subdomain
+ * contexts the halo ("ghost") layers are filled from the neighbours before
+ * every stage (paper section 3, the halo exchange of Fig. 1 and the
+ * exchange_halo listing; device-side pack/unpack calls for callers that
+ * exchange them themselves).
  *
  * Conventions shared by every call
  *  - Grid: cell centred, x_i = x0 + (i + 1/2) dx, dx = (x1 - x0) / nx (same
@@ -139,7 +140,7 @@ int sacx_destroy(sacx_ctx *ctx);
 /* Set the boundary kind of each side (paper section 5: periodic for
  * Orszag-Tang; open for the shock tube).  Periodic sides must come in pairs
  * (x-, x+ and y-, y+), else EINVAL.  A direction with one cell must be
- * periodic.  Takes effect at the next halo fill (the background's halos,
+ * periodic.  Takes effect at the next stage (the background's halos,
  * if any, are filled again at once).  While a learned coefficient is set
  * (sacx_hd_set_surrogate) only all-periodic boundaries are accepted (ESTATE
  * otherwise).  EXCHANGE sides: EUNSUP with a background or with fewer than

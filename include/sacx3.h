@@ -87,18 +87,18 @@ int sacx3_destroy(sacx3_ctx *ctx);
 
 /* Boundary kind of each of the six sides (paper section 5: periodic or open
  * boundaries).  Periodic sides come in pairs; a direction with one cell must
- * be periodic (EINVAL otherwise).  Takes effect at the next ghost fill. */
+ * be periodic (EINVAL otherwise).  Takes effect at the next step. */
 int sacx3_set_boundaries(sacx3_ctx *ctx, const int32_t bc[6]);
 
 /* Load a state (paper section 3: the initial configuration): 8 device
  * pointers to FP64 arrays in the field order above, row and plane pitch in
- * elements.  Copies the cells in, fills the ghost layers and reduces the
- * wave speeds for the first step; t = t0, step count reset.  Enqueued. */
+ * elements.  Copies the cells in and reduces the wave speeds for the
+ * first step; t = t0, step count reset.  Enqueued. */
 int sacx3_init_state(sacx3_ctx *ctx, const double *const *d_fields, int64_t pitch, int64_t plane_pitch,
                      double t0);
 
-/* Enqueue up to nsteps RK4 steps (paper section 2; one step is 4 stages, the
- * ghost layers refilled before each).  t_end <= 0: no end time; otherwise
+/* Enqueue up to nsteps RK4 steps (paper section 2; one step is 4 stages,
+ * which read the cells beyond each side where its boundary has their values).  t_end <= 0: no end time; otherwise
  * dt = min(dt, t_end - t) and stepping stops once t_end - t <= 1e-12 t_end.
  * A step whose start state is non-physical (rho <= 0, p <= 0 or not finite)
  * is not taken, nor any later one.  With steps_done or t_now non-NULL the

@@ -14,7 +14,7 @@
 //              primitives go to LDS (the x- and y-face coefficient ratios and
 //              the compression s take their neighbours there); the z-face
 //              ratio takes its six planes from a per-thread register window.
-//   k3_stage   L(S) and the RK4 stage combine: ideal fluxes differenced with
+//   k3_stage_hd   L(S) and the RK4 stage combine: ideal fluxes differenced with
 //              the fourth-order central difference (x and y fluxes through
 //              LDS, the z flux from a register window), the hyper-diffusive
 //              face fluxes H_d (hyper-viscous stress, hyper-resistive e.m.f.,
@@ -22,12 +22,13 @@
 //              then the storage-saving RK4 combine; stage 4 also reduces the
 //              wave speeds of the new state.  The G that the x- and y-face
 //              fluxes of a plane read are staged in LDS tiles by loads that
-//              write LDS directly, issued before the plane's state loads.
+//              write LDS directly.
 //
-// Splitting the stage in two moves the 21 face quantities through HBM (a
-// fused 3-D kernel would need the z windows of both launches in one thread):
-// as laid out, about 592 B per cell and stage against the 192 B of the
-// stage's own state accesses.
+// Splitting the stage in two moves the 21 face quantities through HBM: at
+// 512^3 336 B per cell for k3_faces and 504-629 B for the stage launch, against
+// the 192 B of the stage's own state accesses.  Without hyper-diffusion
+// k3_stage is the only launch of a stage; with it the stage launch is
+// k3_stage_hd.
 //
 // Arithmetic: every value is the IEEE operation sequence of the scheme's
 // definition in its storage-saving arrangement (divisions by grid constants
@@ -1074,7 +1075,7 @@ __global__ __launch_bounds__(2 * TX *TY, 1) void k3_stage_hd(Stage3Args a) {
 
 // ---------------------------------------------------------------- small kernels
 
-// ghost fills: x over the cell rows and planes, then y over the padded x
+// ghost fills (for periodic directions of 1 or 2 cells): x over the cell rows and planes, then y over the padded x
 // width, then z over the padded x and y extents (edges and corners filled);
 // periodic images or zero-gradient copies
 __global__ void k3_fill_x(double *S, int64_t fs, Layout3 L, int pm, int pp, const Dev3 *sc) {

@@ -1,5 +1,5 @@
-// sacx_batch.hip -- FP64 instantiation of the batched persistent launch (built
-// without contraction, like the FP64 stage kernel).
+// sacx_batch.hip -- FP64 instantiation of the batched launches (built without
+// contraction, like the FP64 stage kernel).
 #include "sacx_batch_kernel.h"
 
 namespace sacx {

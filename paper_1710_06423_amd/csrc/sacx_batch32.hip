@@ -1,5 +1,5 @@
-// sacx_batch32.hip -- FP32 instantiation of the batched persistent launch
-// (built with multiply-add contraction, like the FP32 stage kernel).
+// sacx_batch32.hip -- FP32 instantiation of the batched launches (built with
+// multiply-add contraction, like the FP32 stage kernel).
 #include "sacx_batch_kernel.h"
 
 namespace sacx {

@@ -1,6 +1,5 @@
 // sacx_batch_kernel.h -- the batched launches of many subdomains (one per stage,
-// or one persistent launch), as
-// templates; each precision is instantiated in its own translation unit with
+// or one persistent launch), as templates; each precision is instantiated in its own translation unit with
 // the same floating-point contraction as that precision's stage kernel, so an
 // instance evolves in a batch exactly as it does alone.
 #pragma once

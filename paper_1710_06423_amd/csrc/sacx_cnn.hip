@@ -13,7 +13,7 @@
 // (one 16-byte load per lane: 8 consecutive channels of one pixel, NHWC).
 // The backward data pass is the same kernel with the transposed weights and
 // negated tap offsets; the weight gradient reduces over pixels, with both
-// operands transposed through LDS so that K runs over 32 pixels.  Reductions
+// operands read from LDS transposed so that K runs over 32 pixels.  Reductions
 // over pixels (weight and bias gradients, the loss) go through per-block
 // partial sums and a fixed-order second pass, so results are deterministic.
 //

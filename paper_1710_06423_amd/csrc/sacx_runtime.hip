@@ -12,18 +12,22 @@
 // with L = 0 bit-for-bit unchanged, and moves 12 field values per cell and
 // step (stencil reads 4, pointwise reads 3, writes 5).
 //
-// Before every stage the halo of the stage input is refilled (paper section 3,
-// exchange_halo): periodic directions pack both boundary strips into device
-// exchange buffers and unpack them into the opposite ghost layers (the
-// self-exchange of a subdomain that is its own neighbour); open directions copy
-// the edge cell outward.  x goes first, then y over the padded width, so the
-// corners are filled.
+// Cells beyond a periodic or an open side are read where the boundary has
+// their values (SideMap), by the stage kernels themselves.  Ghost layers are
+// filled only for exchange sides (paper section 3, exchange_halo: the caller's
+// or the domain's hand-over between subdomains, x first, then y over the padded
+// width, so the corners travel) and for periodic directions of fewer than 3
+// cells.
+//
+// A call's steps take, by what is expected to be fastest, one launch per stage
+// (marching strips or boxes), one per two stages (without hyper-diffusion) or
+// one per step (tubes); the results are the same bits.
 //
 // The time step is computed on the device: stage 4 reduces max(|v_d| + c_f)
-// of the new state into the next slot of a double-buffered accumulator, a
-// one-thread kernel turns it into dt (with the end-time clamp) before the
-// next step, and another advances t after it.  Nothing synchronises with the
-// host inside sacx_advance.
+// of the new state into the next slot of a double-buffered accumulator, and
+// one small launch between two steps advances t and turns the maxima into the
+// next dt (with the end-time clamp).  Nothing synchronises with the host inside
+// sacx_advance.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

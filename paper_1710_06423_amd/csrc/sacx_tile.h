@@ -1,5 +1,5 @@
 // sacx_tile.h -- device code of one tile of the fused RK stage (shared by the
-// per-subdomain stage kernel and the batched persistent kernel), and the
+// per-subdomain stage kernel and the batched kernels), and the
 // hyper-diffusion coefficient ratio.
 //
 // One launch evaluates L(S) (ideal split-variable MHD fluxes differenced with

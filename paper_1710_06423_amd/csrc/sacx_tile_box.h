@@ -7,8 +7,8 @@
 // time.  Here the rows of a block run side by side, a wave for each R of them,
 // so a stage is four barriers whatever the grid: 7-8 us for one block per
 // compute unit in FP64.  Per step, against the best marching shape: 300 x 136
-// 43 us from 77, 512^2 88 from 137, 1024^2 212 from 261, 2048^2 827 from 796
-// (FP64); 32 from 72, 56 from 97, 115 from 158, 369 from 395 (FP32).  What
+// 41 us from 77, 512^2 88 from 137, 1024^2 206 from 261, 2048^2 827 from 796
+// (FP64); 31 from 72, 55 from 97, 115 from 158, 368 from 395 (FP32).  What
 // bounds it at size is the apron (14 rows loaded for 8, about 1.9 times the
 // primitives) and LDS traffic (about 170 reads and writes per cell).
 //

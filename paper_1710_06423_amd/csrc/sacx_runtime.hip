@@ -2820,13 +2820,14 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
     // One launch per stage (and one for its ghosts) over all subdomains: the
     // subdomains' own launches ran one after the other, each too small for
     // the chip, with 8 pack and unpack launches per stage in a 2 x 2 split.
-    // Not for narrow periodic directions, whose ghosts need fills, and not
-    // while the stream is captured: a graph must not read tables that a later
-    // call may replace.
+    // Not for narrow periodic directions, whose ghosts need fills, not for the
+    // one subdomain of a domain with a background, which the list kernels do
+    // not read, and not while the stream is captured: a graph must not read
+    // tables that a later call may replace.
     bool together = true;
     unsigned long long gen = 0;
     for (const sacx_ctx *c : *d->subs) {
-        together = together && !narrow(c, 0) && (c->L.ny == 1 || !narrow(c, 1));
+        together = together && !c->grid.background_on && !narrow(c, 0) && (c->L.ny == 1 || !narrow(c, 1));
         gen += c->gen;
     }
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

@@ -217,8 +217,9 @@ __device__ inline void step_end_dev(DevScalars *sc) {
 // Where the cells outside one direction are read: cell i (from -G to n + G - 1)
 // is stored at clamp(i, lo, hi), moved by `below` where i < 0 and by `above`
 // where i >= n: the periodic image, the edge cell of an open side, or the
-// ghost cell itself (exchange sides, and periodic directions of fewer than G
-// cells, whose ghosts are filled before the stage).  The stage kernels read
+// ghost cell itself (exchange sides, periodic directions of fewer than G
+// cells, whose ghosts are filled before the stage, and every side in a
+// stage-level call, whose ghosts the caller completes).  The stage kernels read
 // through this, so that no launch has to fill ghost layers before them: the
 // four launches of a fill took 15-19 us per stage at every grid size up to
 // 2048^2, where a stage itself takes 25-120 us.

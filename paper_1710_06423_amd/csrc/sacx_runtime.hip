@@ -14,10 +14,11 @@
 //
 // Cells beyond a periodic or an open side are read where the boundary has
 // their values (SideMap), by the stage kernels themselves.  Ghost layers are
-// filled only for exchange sides (paper section 3, exchange_halo: the caller's
-// or the domain's hand-over between subdomains, x first, then y over the padded
-// width, so the corners travel) and for periodic directions of fewer than 3
-// cells.
+// filled only for exchange sides (paper section 3, exchange_halo: the
+// domain's hand-over between subdomains, x first, then y over the padded
+// width, so the corners travel), for periodic directions of fewer than 3
+// cells, and for the stage-level calls, whose stages read the ghost cells that
+// the caller completed.
 //
 // A call's steps take, by what is expected to be fastest, one launch per stage
 // (marching strips or boxes), one per two stages (without hyper-diffusion) or
@@ -105,6 +106,9 @@ struct sacx_ctx {
     int64_t sur_refreshes, sur_tiles_checked;
     // decomposed stepping (sacx_stage): the next RK4 stage, 0 between steps
     int stage_next;
+    // the ghost cells of U, and of the background, are still to be filled for
+    // the stage-level calls (the library's own steps read through the maps)
+    bool ghosts_due, bg_due;
     // bumped by every change a batch's instance table copies (boundaries,
     // spacing), so that the batch rebuilds its table
     unsigned long long gen;
@@ -376,7 +380,7 @@ __global__ void k_unpack_x(FPtr<real> S, int nf, Layout L, const real *b0, const
 }
 
 // y strips over the padded width: buffer [f][g][i + G], i in [-G, nx + G),
-// cells outside x read through the x sides' map (exchange sides: the ghosts)
+// cells outside x read as mx says
 template <typename real>
 __global__ void k_pack_y(FPtr<real> S, int nf, Layout L, SideMap mx, real *b0, real *b1, int sides,
                          const DevScalars *sc) {
@@ -797,6 +801,8 @@ __global__ void k_sums_final(const double *partials, int npart, double *out, dou
 // how a context's stored cells are read outside each direction
 SideMap x_map(const sacx_ctx *c) { return side_map(c->L.nx, c->bc[0], c->bc[1]); }
 SideMap y_map(const sacx_ctx *c) { return side_map(c->L.ny, c->bc[2], c->bc[3]); }
+// or where they are stored: the ghost cells themselves
+SideMap stored_map(int n) { return side_map(n, SACX_EXCHANGE, SACX_EXCHANGE); }
 
 // event marks: class 0..3 = stage kernels, 4 = halo, 5 = scalar kernels
 int prof_event(sacx_ctx *c) {
@@ -855,7 +861,8 @@ void fill_dir_t(sacx_ctx *c, void *const *fields, int nf, bool gated, int dir) {
             hipLaunchKernelGGL(k_unpack_x<real>, g, dim3(T), 0, c->stream, S, nf, L, (const real *)h[1],
                                (const real *)h[0], 2, sc);
         } else {
-            hipLaunchKernelGGL(k_pack_y<real>, g, dim3(T), 0, c->stream, S, nf, L, x_map(c), (real *)h[0], (real *)h[1], 2, sc);
+            hipLaunchKernelGGL(k_pack_y<real>, g, dim3(T), 0, c->stream, S, nf, L, stored_map(L.nx), (real *)h[0],
+                               (real *)h[1], 2, sc);
             hipLaunchKernelGGL(k_unpack_y<real>, g, dim3(T), 0, c->stream, S, nf, L, (const real *)h[1],
                                (const real *)h[0], 2, sc);
         }
@@ -898,8 +905,8 @@ int fill_narrow(sacx_ctx *c, void *const *fields, int nf, bool gated) {
     return rc ? rc : fill_narrow(c, fields, nf, gated, 1);
 }
 
-// the ghost cells of the state U (the stage kernels do not need them: the
-// kernels of the learned coefficient read them)
+// the ghost cells of the state U (the kernels of the learned coefficient and
+// the stage-level calls read them)
 template <typename real>
 int fill_halo_t(sacx_ctx *c) {
     if (has_exchange(c) || narrow(c, 0) || narrow(c, 1)) {
@@ -916,6 +923,25 @@ int fill_halo_t(sacx_ctx *c) {
 
 int fill_halo(sacx_ctx *c) {
     return c->grid.precision == SACX_FP64 ? fill_halo_t<double>(c) : fill_halo_t<float>(c);
+}
+
+// before a stage-level call: the ghost cells that a loaded state and a
+// background have are filled where no such call needed them yet
+int ghosts_ready(sacx_ctx *c) {
+    if (c->ghosts_due) {
+        const int rc = fill_halo(c);
+        if (rc) return rc;
+        c->ghosts_due = false;
+    }
+    if (c->bg_due) {
+        for (int dir = 0; dir < 2; ++dir) {
+            if (c->grid.precision == SACX_FP64) fill_dir_t<double>(c, c->BG, NBG, false, dir);
+            else fill_dir_t<float>(c, c->BG, NBG, false, dir);
+        }
+        HIPCHK(hipGetLastError());
+        c->bg_due = false;
+    }
+    return SACX_OK;
 }
 
 // the state the next stage differences: U between steps, then w1, w2, w3
@@ -966,12 +992,12 @@ StepConsts step_consts(const sacx_ctx *c) {
 }
 
 template <typename real>
-StageArgs<real> stage_args(sacx_ctx *c) {
+StageArgs<real> stage_args(sacx_ctx *c, bool stored = false) {
     StageArgs<real> a;
     std::memset(&a, 0, sizeof(a));
     a.L = c->L;
-    a.mx = x_map(c);
-    a.my = y_map(c);
+    a.mx = stored ? stored_map(c->L.nx) : x_map(c);
+    a.my = stored ? stored_map(c->L.ny) : y_map(c);
     a.ty = c->ty;
     a.nt = c->nt;
     a.split = c->split;
@@ -1040,10 +1066,11 @@ bool fields_uniform(const StageArgs<real> &a) {
     return true;
 }
 
+// stored: the cells outside are the ghost cells as they are
 template <typename real>
 int run_stage(sacx_ctx *c, int stage, void *const *S, void *const *U, void *const *A, void *const *o1,
-              void *const *o2) {
-    StageArgs<real> a = stage_args<real>(c);
+              void *const *o2, bool stored = false) {
+    StageArgs<real> a = stage_args<real>(c, stored);
     for (int f = 0; f < NF; ++f) {
         a.S[f] = (const real *)S[f];
         a.U[f] = (const real *)(U ? U[f] : S[f]);
@@ -1372,6 +1399,7 @@ int sacx_set_boundaries(sacx_ctx *ctx, const int32_t bc[4]) {
         // the static background's ghosts follow the new boundaries
         DeviceGuard dg(ctx->device);
         if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
+        ctx->bg_due = true;
         return fill_narrow(ctx, ctx->BG, NBG, false);
     }
     return SACX_OK;
@@ -1387,6 +1415,8 @@ static int finish_init(sacx_ctx *ctx) {
     int rc = fill_narrow(ctx, ctx->U, NF, false);
     if (rc) return rc;
     ctx->stage_next = 0;
+    ctx->ghosts_due = true;
+    ctx->bg_due = ctx->grid.background_on != 0;
     ctx->initialized = true;
     return SACX_OK;
 }
@@ -1533,6 +1563,7 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
         }
     }
     if (nsteps > 0) {
+        ctx->ghosts_due = true;
         ProfScope ps(ctx, 5);
         hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, ctx->stream, ctx->sc);
         HIPCHK(hipGetLastError());
@@ -1624,7 +1655,9 @@ int sacx_halo_buffer_size(const sacx_ctx *ctx, int32_t side, size_t *bytes) {
     return SACX_OK;
 }
 
-static int halo_io(sacx_ctx *ctx, int32_t side, void *buf, bool pack) {
+// stored: the corners of a packed y strip are the ghost cells as they are;
+// otherwise the cells that the x sides' boundary has there
+static int halo_io(sacx_ctx *ctx, int32_t side, void *buf, bool pack, bool stored) {
     if (!ctx || !buf) return fail(SACX_EINVAL, "ctx/buffer must not be NULL");
     if (side < 0 || side > 3) return fail(SACX_EINVAL, "side must be 0..3");
     if (!ctx->initialized) return fail(SACX_ESTATE, "sacx_init_state has not been called");
@@ -1633,6 +1666,11 @@ static int halo_io(sacx_ctx *ctx, int32_t side, void *buf, bool pack) {
         return fail(SACX_EUNSUP, "halo exchange needs at least %d cells across", G);
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
+    if (stored) {
+        const int rc = ghosts_ready(ctx);
+        if (rc) return rc;
+    }
+    const SideMap mx = stored ? stored_map(L.nx) : x_map(ctx);
     ProfScope ps(ctx, 4);
     const int T = 256;
     const int s = side & 1;
@@ -1650,10 +1688,10 @@ static int halo_io(sacx_ctx *ctx, int32_t side, void *buf, bool pack) {
     } else {
         dim3 g((L.nx + 2 * G + T - 1) / T, NF, 1);
         if (f64) {
-            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, x_map(ctx), (double *)buf, (double *)buf, 10 + s, (const DevScalars *)nullptr);
+            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, mx, (double *)buf, (double *)buf, 10 + s, (const DevScalars *)nullptr);
             else hipLaunchKernelGGL(k_unpack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, (const double *)buf, (const double *)buf, 10 + s, (const DevScalars *)nullptr);
         } else {
-            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, x_map(ctx), (float *)buf, (float *)buf, 10 + s, (const DevScalars *)nullptr);
+            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, mx, (float *)buf, (float *)buf, 10 + s, (const DevScalars *)nullptr);
             else hipLaunchKernelGGL(k_unpack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, (const float *)buf, (const float *)buf, 10 + s, (const DevScalars *)nullptr);
         }
     }
@@ -1661,10 +1699,10 @@ static int halo_io(sacx_ctx *ctx, int32_t side, void *buf, bool pack) {
     return SACX_OK;
 }
 
-int sacx_halo_pack(sacx_ctx *ctx, int32_t side, void *d_buf) { return halo_io(ctx, side, d_buf, true); }
+int sacx_halo_pack(sacx_ctx *ctx, int32_t side, void *d_buf) { return halo_io(ctx, side, d_buf, true, true); }
 
 int sacx_halo_unpack(sacx_ctx *ctx, int32_t side, const void *d_buf) {
-    return halo_io(ctx, side, const_cast<void *>(d_buf), false);
+    return halo_io(ctx, side, const_cast<void *>(d_buf), false, true);
 }
 
 // ------------------------------------------------------------------ decomposed stepping
@@ -1682,7 +1720,8 @@ int sacx_fill_boundaries(sacx_ctx *ctx, int32_t direction) {
     return SACX_OK;
 }
 
-int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int32_t *stage_done) {
+// stored: the stage reads the ghost cells as they are; otherwise the sides' maps
+static int stage_call(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int32_t *stage_done, bool stored) {
     if (!ctx) return fail(SACX_EINVAL, "ctx must not be NULL");
     if (c_max_on_device != 0 && c_max_on_device != 1) return fail(SACX_EINVAL, "c_max_on_device must be 0 or 1");
     if (c_max_on_device && !c_max) return fail(SACX_EINVAL, "a device c_max must not be NULL");
@@ -1698,6 +1737,8 @@ int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int3
     }
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
+    int rc;
+    if (stored && (rc = ghosts_ready(ctx))) return rc;
     const int s = ctx->stage_next + 1;
     if (s == 1) {
         ProfScope ps(ctx, 5);
@@ -1711,20 +1752,14 @@ int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int3
             hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, ctx->stream, ctx->sc, 0.0, step_consts(ctx), 0);
         HIPCHK(hipGetLastError());
     }
-    int rc;
     {
         ProfScope ps(ctx, s - 1);
-        const bool f64 = ctx->grid.precision == SACX_FP64;
-        switch (s) {
-            case 1: rc = f64 ? run_stage<double>(ctx, 1, ctx->U, nullptr, nullptr, ctx->B1, nullptr)
-                             : run_stage<float>(ctx, 1, ctx->U, nullptr, nullptr, ctx->B1, nullptr); break;
-            case 2: rc = f64 ? run_stage<double>(ctx, 2, ctx->B1, ctx->U, nullptr, ctx->B2, ctx->A)
-                             : run_stage<float>(ctx, 2, ctx->B1, ctx->U, nullptr, ctx->B2, ctx->A); break;
-            case 3: rc = f64 ? run_stage<double>(ctx, 3, ctx->B2, ctx->U, nullptr, ctx->B1, nullptr)
-                             : run_stage<float>(ctx, 3, ctx->B2, ctx->U, nullptr, ctx->B1, nullptr); break;
-            default: rc = f64 ? run_stage<double>(ctx, 4, ctx->B1, nullptr, ctx->A, ctx->U, nullptr)
-                              : run_stage<float>(ctx, 4, ctx->B1, nullptr, ctx->A, ctx->U, nullptr); break;
-        }
+        void *const *S[4] = {ctx->U, ctx->B1, ctx->B2, ctx->B1};
+        void *const *O1[4] = {ctx->B1, ctx->B2, ctx->B1, ctx->U};
+        void *const *U = s == 2 || s == 3 ? ctx->U : nullptr, *const *A = s == 4 ? ctx->A : nullptr;
+        void *const *O2 = s == 2 ? ctx->A : nullptr;
+        rc = ctx->grid.precision == SACX_FP64 ? run_stage<double>(ctx, s, S[s - 1], U, A, O1[s - 1], O2, stored)
+                                              : run_stage<float>(ctx, s, S[s - 1], U, A, O1[s - 1], O2, stored);
     }
     if (rc) return rc;
     if (s == 4) {
@@ -1735,6 +1770,10 @@ int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int3
     ctx->stage_next = s & 3;
     if (stage_done) *stage_done = s;
     return SACX_OK;
+}
+
+int sacx_stage(sacx_ctx *ctx, const double *c_max, int32_t c_max_on_device, int32_t *stage_done) {
+    return stage_call(ctx, c_max, c_max_on_device, stage_done, true);
 }
 
 int sacx_set_spacing(sacx_ctx *ctx, double dx, double dy) {
@@ -2388,6 +2427,7 @@ int sacx_batch_advance(sacx_batch *b, int32_t nsteps, int32_t sync) {
         if (has_exchange(c)) return fail(SACX_ESTATE, "a batched instance cannot have exchange boundaries");
         if (c->stage_next) return fail(SACX_ESTATE, "a batched instance has a step begun with sacx_stage in progress");
         gsum += c->gen;
+        c->ghosts_due = c->ghosts_due || nsteps > 0;
     }
     DeviceGuard dg(b->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the batch device");
@@ -2506,6 +2546,7 @@ struct sacx_domain {
     char *tab;
     BatchItem *items;
     int ntiles, nt, box;
+    bool mixed;  // some subdomain's y neighbour has x sides of other kinds
     bool each;   // stage launches by subdomain, in each one's own launch shape
     bool split;
     bool built;
@@ -2721,7 +2762,9 @@ int sacx_domain_create(int32_t px, int32_t py, sacx_ctx *const *subs, void *d_bu
                 size_t sb = 0;
                 sacx_halo_buffer_size(subs[i], side, &sb);
                 (*d->buf)[i][side] = p;
-                (*d->nbr)[i][side] = domain_neighbour(px, py, a, b, side);
+                const int nb = domain_neighbour(px, py, a, b, side);
+                (*d->nbr)[i][side] = nb;
+                if (side >= 2 && (subs[nb]->bc[0] != subs[i]->bc[0] || subs[nb]->bc[1] != subs[i]->bc[1])) d->mixed = true;
                 p += round_up(sb, kDomainAlign);
             }
         }
@@ -2742,7 +2785,8 @@ int sacx_domain_destroy(sacx_domain *d) {
 // both strips of one direction of a context's stage input in one launch
 // (the two-sided form of the pack / unpack kernels): b0 for the low side,
 // b1 for the high side
-static int halo_io_both(sacx_ctx *ctx, int dir, void *b0, void *b1, bool pack) {
+static int halo_io_both(sacx_ctx *ctx, int dir, void *b0, void *b1, bool pack, bool stored) {
+    const SideMap mx = stored ? stored_map(ctx->L.nx) : x_map(ctx);
     ProfScope ps(ctx, 4);
     const Layout &L = ctx->L;
     const int T = 256;
@@ -2761,10 +2805,10 @@ static int halo_io_both(sacx_ctx *ctx, int dir, void *b0, void *b1, bool pack) {
         }
     } else {
         if (f64) {
-            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, x_map(ctx), (double *)b0, (double *)b1, 2, none);
+            if (pack) hipLaunchKernelGGL(k_pack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, mx, (double *)b0, (double *)b1, 2, none);
             else hipLaunchKernelGGL(k_unpack_y<double>, g, dim3(T), 0, ctx->stream, fptr<double>(S, NF), NF, L, (const double *)b0, (const double *)b1, 2, none);
         } else {
-            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, x_map(ctx), (float *)b0, (float *)b1, 2, none);
+            if (pack) hipLaunchKernelGGL(k_pack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, mx, (float *)b0, (float *)b1, 2, none);
             else hipLaunchKernelGGL(k_unpack_y<float>, g, dim3(T), 0, ctx->stream, fptr<float>(S, NF), NF, L, (const float *)b0, (const float *)b1, 2, none);
         }
     }
@@ -2782,9 +2826,9 @@ static int domain_exchange(sacx_domain *d, int dir) {
         sacx_ctx *c = (*d->subs)[i];
         void *const *b = (*d->buf)[i].data();
         int rc = SACX_OK;
-        if (b[lo] && b[hi]) rc = halo_io_both(c, dir, b[lo], b[hi], true);
-        else if (b[lo]) rc = sacx_halo_pack(c, lo, b[lo]);
-        else if (b[hi]) rc = sacx_halo_pack(c, hi, b[hi]);
+        if (b[lo] && b[hi]) rc = halo_io_both(c, dir, b[lo], b[hi], true, d->mixed);
+        else if (b[lo]) rc = halo_io(c, lo, b[lo], true, d->mixed);
+        else if (b[hi]) rc = halo_io(c, hi, b[hi], true, d->mixed);
         if (rc) return rc;
     }
     for (int i = 0; i < n; ++i) {
@@ -2794,9 +2838,9 @@ static int domain_exchange(sacx_domain *d, int dir) {
         void *from_lo = b[lo] ? (*d->buf)[(*d->nbr)[i][lo]][hi] : nullptr;
         void *from_hi = b[hi] ? (*d->buf)[(*d->nbr)[i][hi]][lo] : nullptr;
         int rc = SACX_OK;
-        if (from_lo && from_hi) rc = halo_io_both(c, dir, from_lo, from_hi, false);
-        else if (from_lo) rc = sacx_halo_unpack(c, lo, from_lo);
-        else if (from_hi) rc = sacx_halo_unpack(c, hi, from_hi);
+        if (from_lo && from_hi) rc = halo_io_both(c, dir, from_lo, from_hi, false, d->mixed);
+        else if (from_lo) rc = halo_io(c, lo, from_lo, false, d->mixed);
+        else if (from_hi) rc = halo_io(c, hi, from_hi, false, d->mixed);
         if (rc) return rc;
     }
     return SACX_OK;
@@ -2820,13 +2864,15 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
     // One launch per stage (and one for its ghosts) over all subdomains: the
     // subdomains' own launches ran one after the other, each too small for
     // the chip, with 8 pack and unpack launches per stage in a 2 x 2 split.
-    // Not for narrow periodic directions, whose ghosts need fills, not for the
+    // Not where y neighbours have x sides of different kinds (the corners of a
+    // subdomain are then what its neighbour has beyond its own sides), not for narrow periodic directions, whose ghosts need fills, not for the
     // one subdomain of a domain with a background, which the list kernels do
     // not read, and not while the stream is captured: a graph must not read
     // tables that a later call may replace.
-    bool together = true;
+    bool together = !d->mixed;
     unsigned long long gen = 0;
-    for (const sacx_ctx *c : *d->subs) {
+    for (sacx_ctx *c : *d->subs) {
+        c->ghosts_due = c->ghosts_due || nsteps > 0;
         together = together && !c->grid.background_on && !narrow(c, 0) && (c->L.ny == 1 || !narrow(c, 1));
         gen += c->gen;
     }
@@ -2849,16 +2895,18 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
         for (int i = 0; i < n; ++i)
             if ((rc = sacx_wave_speeds_max((*d->subs)[i], d->cmax))) return rc;
         for (int s = 0; s < 4; ++s) {
-            // (periodic and open sides need no fill, narrow directions apart)
+            // without mixed kinds the periodic and open sides need no fill,
+            // narrow directions apart
             for (int dir = 0; dir < 2; ++dir) {
                 for (int i = 0; i < n; ++i) {
                     sacx_ctx *c = (*d->subs)[i];
-                    if ((rc = fill_narrow(c, stage_input(c), NF, false, dir))) return rc;
+                    if ((rc = d->mixed ? sacx_fill_boundaries(c, dir) : fill_narrow(c, stage_input(c), NF, false, dir)))
+                        return rc;
                 }
                 if ((rc = domain_exchange(d, dir))) return rc;
             }
             for (int i = 0; i < n; ++i)
-                if ((rc = sacx_stage((*d->subs)[i], d->cmax, 1, nullptr))) return rc;
+                if ((rc = stage_call((*d->subs)[i], d->cmax, 1, nullptr, d->mixed))) return rc;
         }
     }
     return SACX_OK;

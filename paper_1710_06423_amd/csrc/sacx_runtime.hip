@@ -2211,8 +2211,6 @@ int batch_build(sacx_batch *b) {
     std::vector<int64_t> icost(n, 0);
     for (int i = 0; i < n; ++i) {
         sacx_ctx *c = (*b->ctx)[i];
-        if (c->sur_on)
-            return fail(SACX_EUNSUP, "instance %d has a learned coefficient set: the batch kernel uses the plain one", i);
         BatchInst<real> &I = tab[i];
         int rc = table_entry<real>(c, b->nt, (*b->rows)[i], &I);
         if (rc) return rc;
@@ -2426,9 +2424,10 @@ int sacx_batch_advance(sacx_batch *b, int32_t nsteps, int32_t sync) {
         if (!c->initialized) return fail(SACX_ESTATE, "every batch instance needs sacx_init_state first");
         if (has_exchange(c)) return fail(SACX_ESTATE, "a batched instance cannot have exchange boundaries");
         if (c->stage_next) return fail(SACX_ESTATE, "a batched instance has a step begun with sacx_stage in progress");
+        if (c->sur_on) return fail(SACX_EUNSUP, "a batched instance has a learned coefficient set: the batch uses the plain one");
         gsum += c->gen;
-        c->ghosts_due = c->ghosts_due || nsteps > 0;
     }
+    for (sacx_ctx *c : *b->ctx) c->ghosts_due = c->ghosts_due || nsteps > 0;
     DeviceGuard dg(b->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the batch device");
     // One launch per stage over the tiles of every instance, against the
@@ -2442,6 +2441,7 @@ int sacx_batch_advance(sacx_batch *b, int32_t nsteps, int32_t sync) {
     const bool stages = env == nullptr;
     if (b->dirty || gsum != b->gen_built || stages != b->stages) {
         b->stages = stages;
+        b->dirty = true;   // until the tables are complete
         int rc = b->precision == SACX_FP64 ? batch_build<double>(b) : batch_build<float>(b);
         if (rc) return rc;
         b->gen_built = gsum;

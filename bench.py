@@ -292,9 +292,11 @@ def sub_batch(args):
     cells = sum(p.nx * p.ny for p in probs)
     b = Batch(probs, precision=FP32)
     t, r, _ = tune_batch(b, use_cache=False, log=lambda *a: None)
+    tiles = b.tiles
     b.close()
     b = Batch(probs, precision=FP32)
-    b.set_tiles(t, [r] * len(probs))
+    if tiles:
+        b.set_tiles(*tiles)
     steps = 100
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -333,7 +335,8 @@ def sub_batch(args):
             "%.3e" % max(oracle.rel_l2(got[k], want[k]) for k in range(6)))
     b.close()
     return {"mcell_updates_s": round(value, 1), "ms_per_step": round(ms / steps, 4),
-            "instances": len(probs), "cells": cells, "steps": steps, "tiles": {"threads": t, "rows2d": r},
+            "instances": len(probs), "cells": cells, "steps": steps,
+            "tiles": {"threads": t, "rows2d": r} if tiles else "automatic",
             "dtype": "f32 bulk, f64 dt and sums",
             "one_at_a_time_fp64_mcell_updates_s": round(seq, 1), "speedup_vs_one_at_a_time_fp64": round(value / seq, 2),
             "max_rel_l2_vs_one_at_a_time_fp64": float("%.3e" % worst), "sampled_max_rel_l2_vs_oracle": errs}
@@ -716,10 +719,12 @@ def run_batch(args):
     log(f"[bench] batch of {len(probs)} instances, {cells} cells")
     b = Batch(probs, precision=FP32)
     t, r, trials = tune_batch(b, use_cache=False, log=log)
-    log(f"[bench] tiles: {t} threads, {r} rows")
+    tiles = b.tiles
+    log(f"[bench] tiles: {t} threads, {r} rows" if tiles else "[bench] tiles: automatic")
     b.close()
     b2 = Batch(probs, precision=FP32)
-    b2.set_tiles(t, [r] * len(probs))
+    if tiles:
+        b2.set_tiles(*tiles)
     if args.warmup:
         b2.advance(args.warmup)
     torch.cuda.synchronize()
@@ -754,7 +759,7 @@ def run_batch(args):
     b2.close()
     out = base_record(args, value, ms / args.steps, "f32", {
         "workload": "batch64_briowu32_orszagtang32_fp32", "instances": len(probs), "cells": cells,
-        "tiles": {"threads": t, "rows2d": r},
+        "tiles": {"threads": t, "rows2d": r} if tiles else "automatic",
     })
     out["roofline"] = None
     out["cpu_baseline"] = None

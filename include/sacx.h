@@ -322,10 +322,13 @@ int sacx_domain_destroy(sacx_domain *d);
  * than 1024 blocks).  Both are chosen again whenever threads or the tile kind
  * change.  Setting rows alone takes 128 columns in FP64 and 256 in FP32.
  * Until either is set, launches need not have this shape: small and middle
- * grids take blocks of 8 or 16 rows, steps without hyper-diffusion two stages
- * per launch, tubes a whole step.  Results do not depend on the shape
- * (bit-identical); only speed does.  Used by the tile autotuner. */
+ * grids take blocks of 4, 8 or 16 rows, steps without hyper-diffusion two
+ * stages per launch, tubes a whole step.  sacx_set_launch_auto returns to
+ * that state (the tile kind of sacx_set_column_split stays).  Results do not
+ * depend on the shape (bit-identical); only speed does.  Used by the tile
+ * autotuner. */
 int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows);
+int sacx_set_launch_auto(sacx_ctx *ctx);
 int sacx_get_launch(const sacx_ctx *ctx, int32_t *threads, int32_t *rows);
 
 /* Tile kind of FP64 two-dimensional contexts with hyper-diffusion and the
@@ -394,9 +397,12 @@ int sacx_batch_context(sacx_batch *b, int32_t i, sacx_ctx **out);
 /* Tile shapes: threads per block for the whole launch (64/128/256; 0 keeps)
  * and output rows per tile strip for each instance (rows[n], 1..4096; NULL
  * keeps).  Until the first call both are chosen from the device and the
- * instances' sizes.  One-dimensional instances always use one-row tiles.
- * Results do not depend on the shapes.  Used by the tile autotuner. */
+ * instances' sizes, and boxes of 8 or 16 rows taken where they are faster;
+ * sacx_batch_set_tiles_auto returns to that state.  One-dimensional instances
+ * always use one-row tiles.  Results do not depend on the shapes.  Used by the
+ * tile autotuner. */
 int sacx_batch_set_tiles(sacx_batch *b, int32_t threads, const int32_t *rows);
+int sacx_batch_set_tiles_auto(sacx_batch *b);
 
 /* Advance every instance by nsteps RK4 steps (each with its own dt).  With the
  * environment variable SACX_BATCH_SPIN_LIMIT set, by a persistent cooperative

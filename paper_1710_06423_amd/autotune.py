@@ -1,15 +1,18 @@
 """Tile autotuner for the batched launch (and the per-subdomain kernel).
 
-Times a few steps of the real workload for each candidate tile shape and
-keeps the fastest: threads per block for the launch, and output rows per tile
-strip for each instance class (2-D boxes; 1-D tubes always use one-row
-tiles).  Results depend only on speed, never on values (every shape gives the
+Times a few steps of the real workload with the automatic launches and for
+each candidate tile shape (threads per block, and output rows per tile strip
+of the 2-D instances; 1-D tubes always use one-row tiles), and leaves the
+fastest in force.  The automatic launches are not among the shapes that can be
+set (boxes, two stages or a whole step per launch): where no strip beats them
+they stay.  Only speed depends on the shape, never values (every one gives the
 same bits), so tuning on the live state is safe.  A JSON cache keyed by the
-workload signature avoids re-tuning.
+workload, the device and the built library avoids re-tuning.
 """
 
 from __future__ import annotations
 
+import hashlib
 import json
 import os
 import time
@@ -17,7 +20,7 @@ from typing import Dict, Iterable, List, Optional, Sequence, Tuple
 
 import torch
 
-from .sacx import FP32, FP64, Batch, Solver
+from .sacx import FP32, FP64, LIB_PATH, Batch, Solver
 
 CACHE = os.path.join(os.environ.get("XDG_CACHE_HOME", os.path.expanduser("~/.cache")), "sacx", "autotune.json")
 
@@ -58,36 +61,86 @@ def batch_signature(batch: Batch) -> str:
                                ",".join("%dx%d" % (g[i].nx, g[i].ny) for i in range(batch.n)))
 
 
+def _cache_key(batch: Batch) -> str:
+    """The workload, the device and the library: shapes timed with another
+    build are not taken over."""
+    with open(LIB_PATH, "rb") as fh:
+        lib = hashlib.sha256(fh.read()).hexdigest()[:16]
+    return "%s|%s|%s" % (batch_signature(batch), torch.cuda.get_device_name(batch.device), lib)
+
+
+def _strip_wins(time_auto, time_strip, rounds: int = 3) -> bool:
+    """The two in turn; a strip has to win by more than such short timings scatter."""
+    auto, strip = [], []
+    for _ in range(rounds):
+        auto.append(time_auto())
+        strip.append(time_strip())
+    return min(strip) < 0.98 * min(auto)
+
+
 def tune_batch(batch: Batch, threads: Sequence[int] = (128, 256), rows2d: Sequence[int] = (16, 32, 64, 128),
                steps: int = 2, use_cache: bool = True, log=None) -> Tuple[int, int, List[Tuple[int, int, float]]]:
-    """Pick (threads, rows for 2-D instances) for a batch; advances the batch
-    by (1 + steps) x number of candidates steps while measuring."""
-    key = batch_signature(batch)
+    """Time the automatic launches and every (threads, rows for 2-D instances)
+    of a batch and leave the fastest in force (batch.tiles: None where the
+    automatic launches stay).  Returns the fastest shape that can be set and
+    the trials, the automatic launches among them as (0, 0, ms).  Advances the
+    batch by (1 + steps) x (number of candidates + 1) steps while measuring, and
+    six times 1 + steps more where a strip comes in front."""
+    key = _cache_key(batch) if use_cache else ""
     cache = _load_cache() if use_cache else {}
+
+    def apply(t, r):
+        if t:
+            batch.set_tiles(t, [r] * batch.n)
+        else:
+            batch.set_tiles_auto()
+
     if key in cache:
         t, r = cache[key]["threads"], cache[key]["rows2d"]
-        batch.set_tiles(t, [r] * batch.n)
+        if cache[key]["automatic"]:
+            apply(0, 0)
+        else:
+            apply(t, r)
         return t, r, []
+
+    def timed(t, r):
+        apply(t, r)
+        batch.advance(1, sync=True)                     # table build + warm-up
+        return _time(lambda: batch.advance(steps, sync=False), 1) / steps
+
     trials = []
-    for t in threads:
-        for r in rows2d:
-            batch.set_tiles(t, [r] * batch.n)
-            batch.advance(1, sync=True)                     # table build + warm-up
-            ms = _time(lambda: batch.advance(steps, sync=False), 1) / steps
-            trials.append((t, r, ms))
-            if log:
-                log(f"[autotune] threads={t} rows={r}: {ms:.3f} ms/step")
-    t, r, _ = min(trials, key=lambda x: x[2])
-    batch.set_tiles(t, [r] * batch.n)
+    for t, r in [(0, 0)] + [(t, r) for t in threads for r in rows2d]:
+        ms = timed(t, r)
+        trials.append((t, r, ms))
+        if log:
+            log(f"[autotune] threads={t} rows={r}: {ms:.3f} ms/step" if t else f"[autotune] automatic: {ms:.3f} ms/step")
+    t, r, ms = min(trials[1:], key=lambda x: x[2])
+    automatic = not (ms < trials[0][2] and _strip_wins(lambda: timed(0, 0), lambda: timed(t, r)))
+    apply(*((0, 0) if automatic else (t, r)))
     if use_cache:
-        cache[key] = {"threads": t, "rows2d": r, "trials": trials}
+        cache[key] = {"threads": t, "rows2d": r, "automatic": automatic, "trials": trials}
         _save_cache(cache)
     return t, r, trials
 
 
 def tune_solver(s: Solver, threads: Sequence[int] = (64, 128, 256), rows: Sequence[int] = (32, 64, 128, 256),
                 log=None) -> Tuple[int, int]:
-    """Pick the launch shape of one subdomain by timing single steps."""
+    """Time the automatic launches and every launch shape of one subdomain, and
+    leave the fastest in force.  Returns the fastest shape that can be set.
+    Steps are timed two to a call: the automatic launches of some grids take
+    steps in pairs."""
+
+    def timed(t, r):
+        if t:
+            s.set_launch(t, r)
+        else:
+            s.set_launch_auto()
+        s.advance(2)
+        return _time(lambda: s.advance(2, sync=False), 2) / 2
+
+    auto = timed(0, 0)
+    if log:
+        log(f"[autotune] automatic: {auto:.3f} ms/step")
     best = None
     for t in threads:
         for r in rows:
@@ -95,11 +148,13 @@ def tune_solver(s: Solver, threads: Sequence[int] = (64, 128, 256), rows: Sequen
                 s.set_launch(t, r)
             except Exception:
                 continue
-            s.advance(1)
-            ms = _time(lambda: s.advance(1, sync=False), 2)
+            ms = timed(t, r)
             if log:
                 log(f"[autotune] threads={t} rows={r}: {ms:.3f} ms/step")
             if best is None or ms < best[2]:
                 best = (t, r, ms)
-    s.set_launch(best[0], best[1])
+    if best[2] < auto and _strip_wins(lambda: timed(0, 0), lambda: timed(best[0], best[1])):
+        s.set_launch(best[0], best[1])
+    else:
+        s.set_launch_auto()
     return best[0], best[1]

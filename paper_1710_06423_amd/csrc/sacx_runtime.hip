@@ -1312,6 +1312,15 @@ int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows) {
     return SACX_OK;
 }
 
+int sacx_set_launch_auto(sacx_ctx *ctx) {
+    if (!ctx) return fail(SACX_EINVAL, "ctx must not be NULL");
+    ctx->gen += 1;
+    ctx->nt_auto = ctx->ty_auto = true;
+    DeviceGuard dg(ctx->device);
+    auto_rows(ctx);
+    return SACX_OK;
+}
+
 int sacx_set_column_split(sacx_ctx *ctx, int32_t on) {
     if (!ctx) return fail(SACX_EINVAL, "ctx must not be NULL");
     if (on != 0 && on != 1) return fail(SACX_EINVAL, "on must be 0 or 1 (got %d)", on);
@@ -2366,7 +2375,6 @@ int sacx_batch_create(int32_t n, const sacx_grid *grids, const sacx_params *para
     b->items = (BatchItem *)(ws + P.off_items);
     b->qinst = (int *)(ws + P.off_qinst);
     b->items_cap = (int)batch_items_bound(n, grids);
-    b->nt = b->precision == SACX_FP64 ? 128 : 256;
     hipLaunchKernelGGL(k_zero_ints, dim3(8), dim3(256), 0, b->stream, b->sync, BATCH_SYNC0 + 2 * n);
     if (hipGetLastError() != hipSuccess) {
         sacx_batch_destroy(b);
@@ -2386,10 +2394,9 @@ int sacx_batch_create(int32_t n, const sacx_grid *grids, const sacx_params *para
             rc = sacx_set_boundaries(c, bc + 4 * i);
             if (rc) { sacx_batch_destroy(b); return rc; }
         }
-        b->rows->push_back(grids[i].ny == 1 ? 1 : std::min(64, grids[i].ny));
+        b->rows->push_back(0);
     }
-    b->shape_auto = true;
-    b->dirty = true;
+    sacx_batch_set_tiles_auto(b);
     *out = b;
     return SACX_OK;
 }
@@ -2398,6 +2405,20 @@ int sacx_batch_context(sacx_batch *b, int32_t i, sacx_ctx **out) {
     if (!b || !out) return fail(SACX_EINVAL, "batch/out must not be NULL");
     if (i < 0 || i >= b->n) return fail(SACX_EINVAL, "instance %d out of range", i);
     *out = (*b->ctx)[i];
+    return SACX_OK;
+}
+
+// the shapes of the persistent launch; the stage launches choose theirs when
+// their tables are built
+int sacx_batch_set_tiles_auto(sacx_batch *b) {
+    if (!b) return fail(SACX_EINVAL, "batch must not be NULL");
+    b->nt = b->precision == SACX_FP64 ? 128 : 256;
+    for (int i = 0; i < b->n; ++i) {
+        const int ny = (*b->ctx)[i]->grid.ny;
+        (*b->rows)[i] = ny == 1 ? 1 : std::min(64, ny);
+    }
+    b->shape_auto = true;
+    b->dirty = true;
     return SACX_OK;
 }
 

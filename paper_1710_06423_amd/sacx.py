@@ -39,9 +39,10 @@ EXPORTED = (
     "sacx_diagnostics", "sacx_halo_buffer_size", "sacx_halo_pack", "sacx_halo_unpack",
     "sacx_fill_boundaries", "sacx_stage", "sacx_wave_speeds", "sacx_wave_speeds_max", "sacx_set_spacing",
     "sacx_domain_buffer_size", "sacx_domain_create", "sacx_domain_advance", "sacx_domain_destroy",
-    "sacx_profile_enable", "sacx_profile_read", "sacx_set_launch", "sacx_get_launch", "sacx_set_column_split",
+    "sacx_profile_enable", "sacx_profile_read", "sacx_set_launch", "sacx_set_launch_auto", "sacx_get_launch",
+    "sacx_set_column_split",
     "sacx_batch_workspace_size", "sacx_batch_create", "sacx_batch_destroy", "sacx_batch_context",
-    "sacx_batch_set_tiles", "sacx_batch_advance",
+    "sacx_batch_set_tiles", "sacx_batch_set_tiles_auto", "sacx_batch_advance",
     "sacx_cnn_buffer_sizes", "sacx_cnn_pack", "sacx_cnn_forward", "sacx_cnn_backward",
     "sacx_cnn_backward_noalloc", "sacx_cnn_adam",
     "sacx_cnn_inputs", "sacx_hd_ratio_fields", "sacx_surrogate_workspace_size", "sacx_hd_set_surrogate",
@@ -160,6 +161,7 @@ def load_library():
     lib.sacx_profile_enable.argtypes = [P, ctypes.c_int32]
     lib.sacx_profile_read.argtypes = [P, ctypes.POINTER(Profile)]
     lib.sacx_set_launch.argtypes = [P, ctypes.c_int32, ctypes.c_int32]
+    lib.sacx_set_launch_auto.argtypes = [P]
     lib.sacx_get_launch.argtypes = [P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
     lib.sacx_set_column_split.argtypes = [P, ctypes.c_int32]
     lib.sacx_batch_workspace_size.argtypes = [ctypes.c_int32, ctypes.POINTER(Grid), ctypes.POINTER(Params),
@@ -169,6 +171,7 @@ def load_library():
     lib.sacx_batch_destroy.argtypes = [P]
     lib.sacx_batch_context.argtypes = [P, ctypes.c_int32, ctypes.POINTER(P)]
     lib.sacx_batch_set_tiles.argtypes = [P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+    lib.sacx_batch_set_tiles_auto.argtypes = [P]
     lib.sacx_batch_advance.argtypes = [P, ctypes.c_int32, ctypes.c_int32]
     I32, SZ = ctypes.c_int32, ctypes.c_size_t
     lib.sacx_cnn_buffer_sizes.argtypes = [I32, I32, I32, ctypes.POINTER(CnnSizes)]
@@ -524,6 +527,10 @@ class Solver:
     def set_launch(self, threads: int = 0, rows: int = 0):
         _check(self.lib.sacx_set_launch(self.ctx, int(threads), int(rows)), "sacx_set_launch")
 
+    def set_launch_auto(self):
+        """Back to the automatic launches, the state before any set_launch."""
+        _check(self.lib.sacx_set_launch_auto(self.ctx), "sacx_set_launch_auto")
+
     def set_column_split(self, on: bool):
         """Two threads per column (x and y roles) for FP64 hyper-diffusion
         tiles (default), or one; bit-identical results."""
@@ -565,6 +572,7 @@ class Batch:
                                               ctypes.byref(self.b)), "sacx_batch_create")
         _live.add(self)
         self.n = n
+        self.tiles = None   # (threads, rows) as set by set_tiles; None: the automatic launches
         self.views = []
         for i in range(n):
             c = ctypes.c_void_p(None)
@@ -585,6 +593,13 @@ class Batch:
     def set_tiles(self, threads: int = 0, rows=None):
         arr = None if rows is None else (ctypes.c_int32 * self.n)(*[int(r) for r in rows])
         _check(self.lib.sacx_batch_set_tiles(self.b, int(threads), arr), "sacx_batch_set_tiles")
+        if threads or rows is not None:
+            self.tiles = (threads, rows)
+
+    def set_tiles_auto(self):
+        """Back to the automatic launches, the state before any set_tiles."""
+        _check(self.lib.sacx_batch_set_tiles_auto(self.b), "sacx_batch_set_tiles_auto")
+        self.tiles = None
 
     def advance(self, nsteps: int, sync: bool = True):
         with torch.cuda.device(self.device):

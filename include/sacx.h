@@ -351,6 +351,8 @@ int sacx_set_column_split(sacx_ctx *ctx, int32_t on);
  *                    sacx_halo_unpack call;
  *  ms_scalar / n_scalar: the time-step kernels;
  *  ms_surrogate / n_surrogate: surrogate refreshes (prediction and check).
+ * A subdomain of a sacx_domain counts the launches over all subdomains, each
+ * with its share of the time by cells.
  * sacx_profile_enable(ctx, 1) resets the accumulators and starts recording;
  * (ctx, 0) stops.  sacx_profile_read synchronises and returns the totals. */
 typedef struct sacx_profile {

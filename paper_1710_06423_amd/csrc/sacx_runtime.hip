@@ -64,6 +64,14 @@ int sacx::set_error(int code, const char *fmt, ...) {
 
 // ------------------------------------------------------------------ context
 
+// a launch group between two events of a context's pool; class 0..3 = stage
+// kernels, 4 = halo, 5 = scalar kernels, 6 = surrogate refresh; share: the part
+// of its time that is the context's own
+struct ProfMark {
+    int cls, start, stop;
+    double share;
+};
+
 struct sacx_ctx {
     sacx_grid grid;
     sacx_params params;
@@ -91,8 +99,9 @@ struct sacx_ctx {
     // profiling: event pairs recorded around launch groups, resolved at read
     bool prof_on;
     std::vector<hipEvent_t> *ev_pool;
-    std::vector<std::pair<int, std::pair<int, int>>> *ev_marks;  // (class, (start, stop) pool index)
+    std::vector<ProfMark> *ev_marks;
     int ev_used;
+    int prof_start;    // the start event of a launch group shared with other contexts
     sacx_profile prof;
     // learned hyper-diffusion coefficient (off unless sacx_hd_set_surrogate)
     bool sur_on;
@@ -804,7 +813,6 @@ SideMap y_map(const sacx_ctx *c) { return side_map(c->L.ny, c->bc[2], c->bc[3]);
 // or where they are stored: the ghost cells themselves
 SideMap stored_map(int n) { return side_map(n, SACX_EXCHANGE, SACX_EXCHANGE); }
 
-// event marks: class 0..3 = stage kernels, 4 = halo, 5 = scalar kernels
 int prof_event(sacx_ctx *c) {
     if (c->ev_used == (int)c->ev_pool->size()) {
         hipEvent_t e;
@@ -825,7 +833,27 @@ struct ProfScope {
     ~ProfScope() {
         if (c->prof_on && start >= 0) {
             int stop = prof_event(c);
-            if (stop >= 0) c->ev_marks->push_back({cls, {start, stop}});
+            if (stop >= 0) c->ev_marks->push_back({cls, start, stop, 1.0});
+        }
+    }
+};
+
+// a launch group over several contexts: each profiled one takes its share of
+// the time, by cells
+struct SharedProfScope {
+    const std::vector<sacx_ctx *> &ctx;
+    int cls;
+    SharedProfScope(const std::vector<sacx_ctx *> &ctx_, int cls_) : ctx(ctx_), cls(cls_) {
+        for (sacx_ctx *c : ctx)
+            if (c->prof_on) c->prof_start = prof_event(c);
+    }
+    ~SharedProfScope() {
+        double all = 0.0;
+        for (const sacx_ctx *c : ctx) all += (double)c->L.nx * c->L.ny;
+        for (sacx_ctx *c : ctx) {
+            if (!c->prof_on || c->prof_start < 0) continue;
+            const int stop = prof_event(c);
+            if (stop >= 0) c->ev_marks->push_back({cls, c->prof_start, stop, (double)c->L.nx * c->L.ny / all});
         }
     }
 };
@@ -1257,7 +1285,7 @@ int sacx_create(const sacx_grid *grid, const sacx_params *params, void *d_ws, si
     c->sur_r = nullptr;
     c->sur_k = nullptr;
     c->ev_pool = new (std::nothrow) std::vector<hipEvent_t>();
-    c->ev_marks = new (std::nothrow) std::vector<std::pair<int, std::pair<int, int>>>();
+    c->ev_marks = new (std::nothrow) std::vector<ProfMark>();
     if (!c->ev_pool || !c->ev_marks) {
         delete c->ev_pool;
         delete c->ev_marks;
@@ -1355,16 +1383,17 @@ int sacx_profile_read(sacx_ctx *ctx, sacx_profile *out) {
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the context device");
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    for (const auto &m : *ctx->ev_marks) {
-        float ms = 0.f;
-        HIPCHK(hipEventElapsedTime(&ms, (*ctx->ev_pool)[m.second.first], (*ctx->ev_pool)[m.second.second]));
-        if (m.first < 4) {
-            ctx->prof.ms_stage[m.first] += ms;
-            ctx->prof.n_stage[m.first] += 1;
-        } else if (m.first == 4) {
+    for (const ProfMark &m : *ctx->ev_marks) {
+        float whole = 0.f;
+        HIPCHK(hipEventElapsedTime(&whole, (*ctx->ev_pool)[m.start], (*ctx->ev_pool)[m.stop]));
+        const double ms = whole * m.share;
+        if (m.cls < 4) {
+            ctx->prof.ms_stage[m.cls] += ms;
+            ctx->prof.n_stage[m.cls] += 1;
+        } else if (m.cls == 4) {
             ctx->prof.ms_halo += ms;
             ctx->prof.n_halo += 1;
-        } else if (m.first == 6) {
+        } else if (m.cls == 6) {
             ctx->prof.ms_surrogate += ms;
             ctx->prof.n_surrogate += 1;
         } else {
@@ -2651,13 +2680,13 @@ int domain_steps(sacx_domain *d, int nsteps) {
     const dim3 gg((unsigned)std::min<int64_t>((ghosts + 255) / 256, 1024), NF, n);
     for (int s = 0; s <= nsteps; ++s) {
         {
-            ProfScope ps(c0, 5);
+            SharedProfScope ps(*d->subs, 5);
             hipLaunchKernelGGL(k_domain_scalars<real>, dim3(1), dim3(256), 0, c0->stream, a.inst, n, s > 0, s < nsteps,
                                d->cmax);
         }
         for (int st = 1; st <= 4 && s < nsteps; ++st) {
             if (exchange) {
-                ProfScope ps(c0, 4);
+                SharedProfScope ps(*d->subs, 4);
                 hipLaunchKernelGGL(k_domain_ghosts<real>, gg, dim3(256), 0, c0->stream, a.inst, st - 1, d->px, d->py);
             }
             if (d->each) {
@@ -2669,7 +2698,7 @@ int domain_steps(sacx_domain *d, int nsteps) {
                 }
                 continue;
             }
-            ProfScope ps(c0, st - 1);
+            SharedProfScope ps(*d->subs, st - 1);
             const int tiles = d->ntiles;
             if (d->box) {
                 HIPCHK(launch_batch_box<real>(a, d->box, st, c0->params.hd_on != 0, tiles, c0->stream));

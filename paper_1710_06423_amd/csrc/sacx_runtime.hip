@@ -2036,7 +2036,8 @@ struct sacx_batch {
     char *tab;          // BatchInst array
     int *sync;          // abort flag, queue counters, per-instance completion counters
     BatchItem *items;
-    int *qinst;         // instances of each XCD queue
+    int *qinst;         // instances of each XCD queue; of stage launches, those with narrow y
+    int nnarrow, narrow_nx;   // how many those are, and their most columns
     int qoff[kBatchQueues], qlen[kBatchQueues], ioff[kBatchQueues + 1];
     int items_cap;
     int nitems;
@@ -2102,6 +2103,23 @@ int batch_plan(int n, const sacx_grid *grids, const sacx_params *params, BatchPl
     for (int i = 0; i < n; ++i) { P->inst_off[i] = off; off += round_up(P->inst_bytes[i], kAlign); }
     P->total = off;
     return SACX_OK;
+}
+
+// the ghost rows of a stage's input of batched instances whose periodic y has
+// fewer than G rows (one launch for all of them: as one per instance, 41 of them
+// made 169 launches a step)
+template <typename real>
+__global__ __launch_bounds__(256) void k_batch_narrow(const BatchInst<real> *__restrict__ inst,
+                                                      const int *__restrict__ which, int stage) {
+    const BatchInst<real> &I = inst[which[blockIdx.x]];
+    if (!I.sc->active) return;
+    const Layout L = I.L;
+    real *S = const_cast<real *>(I.st[stage].S[blockIdx.y]);
+    for (int i = blockIdx.z * 256 + threadIdx.x; i < L.nx; i += gridDim.z * 256)
+        for (int g = 1; g <= G; ++g) {
+            S[eidx(L, i, -g)] = S[eidx(L, i, (G * L.ny - g) % L.ny)];
+            S[eidx(L, i, L.ny - 1 + g)] = S[eidx(L, i, (g - 1) % L.ny)];
+        }
 }
 
 __global__ void k_zero_ints(int *p, int n) {
@@ -2288,7 +2306,15 @@ int batch_build(sacx_batch *b) {
         for (int tube = 0; tube < 2; ++tube)
             for (int i = 0; i < n; ++i)
                 if (tab[i].oned == tube) list_tiles((*b->ctx)[i], i, b->nt, (*b->rows)[i], b->box, &flat);
-        qinst.assign(n, 0);
+        b->narrow_nx = 0;
+        for (int i = 0; i < n; ++i) {
+            const sacx_ctx *c = (*b->ctx)[i];
+            if (tab[i].oned || !narrow(c, 1)) continue;
+            qinst.push_back(i);
+            b->narrow_nx = std::max(b->narrow_nx, c->L.nx);
+        }
+        b->nnarrow = (int)qinst.size();
+        qinst.resize(n, 0);
     }
     for (int k = 0; k < kBatchQueues && !b->stages; ++k) {
         b->qoff[k] = (int)flat.size();
@@ -2340,10 +2366,10 @@ int batch_stages(sacx_batch *b, int nsteps) {
     for (int s = 0; s < nsteps; ++s) {
         HIPCHK(launch_batch_scalars<real>(a, s > 0, true, flag, b->stream));
         for (int st = 1; st <= 4; ++st) {
-            for (sacx_ctx *c : *b->ctx) {
-                int rc = fill_narrow(c, st == 1 ? c->U : (st == 3 ? c->B2 : c->B1), NF, true);
-                if (rc) return rc;
-            }
+            // (x has at least G cells)
+            if (b->nnarrow)
+                hipLaunchKernelGGL(k_batch_narrow<real>, dim3(b->nnarrow, NF, std::min((b->narrow_nx + 255) / 256, 64)),
+                                   dim3(256), 0, b->stream, a.inst, (const int *)b->qinst, st - 1);
             HIPCHK(b->box ? launch_batch_box<real>(a, b->box, st, true, b->nitems, b->stream)
                           : launch_batch_stage<real>(a, b->nt, st, true, b->nitems, b->stream));
         }

@@ -2246,30 +2246,17 @@ int table_entry(sacx_ctx *c, int nt, int rows, BatchInst<real> *out) {
     return SACX_OK;
 }
 
+// the work lists of the persistent launch: per XCD queue its instances, most
+// expensive first, each its fill pieces then its tiles
 template <typename real>
-int batch_build(sacx_batch *b) {
-    const int n = b->n;
-    int cus = 0;
-    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
-    b->box = 0;
-    if (b->shape_auto && b->stages) {
-        int rows = 0;
-        shape_for_many<real>(*b->ctx, cus, false, &b->nt, &rows, &b->box);
-        for (int i = 0; i < n; ++i) {
-            const int ny = (*b->ctx)[i]->grid.ny;
-            (*b->rows)[i] = ny == 1 ? 1 : std::min(rows, ny);
-        }
-    }
-    const int TX = b->nt - 2 * G;
-    std::vector<BatchInst<real>> tab(n);
+void queue_tiles(sacx_batch *b, std::vector<BatchInst<real>> *tab, std::vector<BatchItem> *flat, std::vector<int> *qinst) {
+    const int n = b->n, TX = b->nt - 2 * G;
     struct Costed { int64_t cost; BatchItem it; };
     std::vector<std::vector<Costed>> tiles(n);
     std::vector<int64_t> icost(n, 0);
     for (int i = 0; i < n; ++i) {
-        sacx_ctx *c = (*b->ctx)[i];
-        BatchInst<real> &I = tab[i];
-        int rc = table_entry<real>(c, b->nt, (*b->rows)[i], &I);
-        if (rc) return rc;
+        const sacx_ctx *c = (*b->ctx)[i];
+        BatchInst<real> &I = (*tab)[i];
         const int xt = (c->L.nx + TX - 1) / TX;
         if (I.oned) {
             for (int x = 0; x < xt; ++x) tiles[i].push_back({1, {i, x, 0, BATCH_TILE}});
@@ -2286,9 +2273,7 @@ int batch_build(sacx_batch *b) {
         I.nfill = batch_fill_pieces(c->grid);
         for (const Costed &t : tiles[i]) icost[i] += t.cost;
     }
-    // instances to the XCD queues, most expensive first to the least loaded
-    // queue; each queue's list: its instances most expensive first, each its
-    // fill pieces then its tiles
+    // instances to the queues, most expensive first to the least loaded
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return icost[p] > icost[q]; });
@@ -2298,6 +2283,38 @@ int batch_build(sacx_batch *b) {
         const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
         group[k].push_back(i);
         load[k] += icost[i];
+    }
+    for (int k = 0; k < kBatchQueues; ++k) {
+        b->qoff[k] = (int)flat->size();
+        b->ioff[k] = (int)qinst->size();
+        for (int i : group[k]) {
+            qinst->push_back(i);
+            for (int p = 0; p < (*tab)[i].nfill; ++p) flat->push_back({i, p, 0, BATCH_FILL});
+            for (const Costed &t : tiles[i]) flat->push_back(t.it);
+        }
+        b->qlen[k] = (int)flat->size() - b->qoff[k];
+    }
+    b->ioff[kBatchQueues] = (int)qinst->size();
+}
+
+template <typename real>
+int batch_build(sacx_batch *b) {
+    const int n = b->n;
+    int cus = 0;
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
+    b->box = 0;
+    if (b->shape_auto && b->stages) {
+        int rows = 0;
+        shape_for_many<real>(*b->ctx, cus, false, &b->nt, &rows, &b->box);
+        for (int i = 0; i < n; ++i) {
+            const int ny = (*b->ctx)[i]->grid.ny;
+            (*b->rows)[i] = ny == 1 ? 1 : std::min(rows, ny);
+        }
+    }
+    std::vector<BatchInst<real>> tab(n);
+    for (int i = 0; i < n; ++i) {
+        int rc = table_entry<real>((*b->ctx)[i], b->nt, (*b->rows)[i], &tab[i]);
+        if (rc) return rc;
     }
     std::vector<BatchItem> flat;
     std::vector<int> qinst;
@@ -2315,18 +2332,13 @@ int batch_build(sacx_batch *b) {
         }
         b->nnarrow = (int)qinst.size();
         qinst.resize(n, 0);
+    } else {
+        queue_tiles(b, &tab, &flat, &qinst);
+        int per_cu = 0;
+        HIPCHK(batch_blocks_per_cu<real>(b->nt, &per_cu));
+        if (per_cu < 1) return fail(SACX_EUNSUP, "batched kernel does not fit on a compute unit with %d threads", b->nt);
+        b->blocks = per_cu * cus;
     }
-    for (int k = 0; k < kBatchQueues && !b->stages; ++k) {
-        b->qoff[k] = (int)flat.size();
-        b->ioff[k] = (int)qinst.size();
-        for (int i : group[k]) {
-            qinst.push_back(i);
-            for (int k2 = 0; k2 < tab[i].nfill; ++k2) flat.push_back({i, k2, 0, BATCH_FILL});
-            for (const Costed &t : tiles[i]) flat.push_back(t.it);
-        }
-        b->qlen[k] = (int)flat.size() - b->qoff[k];
-    }
-    b->ioff[kBatchQueues] = (int)qinst.size();
     if ((int64_t)flat.size() > b->items_cap) return fail(SACX_ENOSPC, "batch work list exceeds its bound");
     b->nitems = (int)flat.size();
     HIPCHK(hipMemcpyAsync(b->qinst, qinst.data(), sizeof(int) * n, hipMemcpyHostToDevice, b->stream));
@@ -2334,10 +2346,6 @@ int batch_build(sacx_batch *b) {
     HIPCHK(hipMemcpyAsync(b->items, flat.data(), sizeof(BatchItem) * flat.size(), hipMemcpyHostToDevice, b->stream));
     // host vectors go out of scope: finish the copies first
     HIPCHK(hipStreamSynchronize(b->stream));
-    int per_cu = 0;
-    HIPCHK(batch_blocks_per_cu<real>(b->nt, &per_cu));
-    if (per_cu < 1) return fail(SACX_EUNSUP, "batched kernel does not fit on a compute unit with %d threads", b->nt);
-    b->blocks = per_cu * cus;
     b->dirty = false;
     return SACX_OK;
 }

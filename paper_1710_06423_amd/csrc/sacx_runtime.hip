@@ -37,6 +37,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <string>
 #include <array>
@@ -60,6 +61,16 @@ int sacx::set_error(int code, const char *fmt, ...) {
     return code;
 }
 #define fail sacx::set_error
+
+// work that allocates host memory, for an entry point that no exception may leave
+template <typename F>
+static int allocating(F &&work) {
+    try {
+        return work();
+    } catch (const std::exception &e) {   // bad_alloc, or a vector's length_error
+        return fail(SACX_EINVAL, "out of host memory (%s)", e.what());
+    }
+}
 
 
 // ------------------------------------------------------------------ context
@@ -2393,7 +2404,7 @@ extern "C" {
 int sacx_batch_workspace_size(int32_t n, const sacx_grid *grids, const sacx_params *params, size_t *bytes) {
     if (!bytes) return fail(SACX_EINVAL, "bytes must not be NULL");
     BatchPlan P;
-    int rc = batch_plan(n, grids, params, &P);
+    int rc = allocating([&] { return batch_plan(n, grids, params, &P); });
     if (rc) return rc;
     *bytes = P.total;
     return SACX_OK;
@@ -2418,7 +2429,7 @@ int sacx_batch_create(int32_t n, const sacx_grid *grids, const sacx_params *para
     if (!out) return fail(SACX_EINVAL, "out must not be NULL");
     *out = nullptr;
     BatchPlan P;
-    int rc = batch_plan(n, grids, params, &P);
+    int rc = allocating([&] { return batch_plan(n, grids, params, &P); });
     if (rc) return rc;
     if (!d_ws || ((uintptr_t)d_ws) % kAlign) return fail(SACX_EINVAL, "workspace must be non-NULL and 256-byte aligned");
     if (ws_bytes < P.total) return fail(SACX_ENOSPC, "workspace has %zu bytes, %zu needed", ws_bytes, P.total);
@@ -2428,6 +2439,8 @@ int sacx_batch_create(int32_t n, const sacx_grid *grids, const sacx_params *para
     b->ctx = new (std::nothrow) std::vector<sacx_ctx *>();
     b->rows = new (std::nothrow) std::vector<int>();
     if (!b->ctx || !b->rows) { sacx_batch_destroy(b); return fail(SACX_EINVAL, "out of host memory"); }
+    rc = allocating([&] { b->ctx->reserve(n); b->rows->assign(n, 0); return SACX_OK; });
+    if (rc) { sacx_batch_destroy(b); return rc; }
     b->n = n;
     b->precision = grids[0].precision;
     b->stream = (hipStream_t)hip_stream;
@@ -2457,7 +2470,6 @@ int sacx_batch_create(int32_t n, const sacx_grid *grids, const sacx_params *para
             rc = sacx_set_boundaries(c, bc + 4 * i);
             if (rc) { sacx_batch_destroy(b); return rc; }
         }
-        b->rows->push_back(0);
     }
     sacx_batch_set_tiles_auto(b);
     *out = b;
@@ -2526,7 +2538,7 @@ int sacx_batch_advance(sacx_batch *b, int32_t nsteps, int32_t sync) {
     if (b->dirty || gsum != b->gen_built || stages != b->stages) {
         b->stages = stages;
         b->dirty = true;   // until the tables are complete
-        int rc = b->precision == SACX_FP64 ? batch_build<double>(b) : batch_build<float>(b);
+        int rc = allocating([&] { return b->precision == SACX_FP64 ? batch_build<double>(b) : batch_build<float>(b); });
         if (rc) return rc;
         b->gen_built = gsum;
     }
@@ -2820,13 +2832,16 @@ int sacx_domain_create(int32_t px, int32_t py, sacx_ctx *const *subs, void *d_bu
     d->px = px;
     d->py = py;
     d->built = false;
-    d->subs = new (std::nothrow) std::vector<sacx_ctx *>(subs, subs + (size_t)px * py);
-    d->buf = new (std::nothrow) std::vector<std::array<void *, 4>>((size_t)px * py);
-    d->nbr = new (std::nothrow) std::vector<std::array<int, 4>>((size_t)px * py);
-    d->bc = new (std::nothrow) std::vector<std::array<int, 4>>((size_t)px * py);
-    if (!d->subs || !d->buf || !d->nbr || !d->bc) {
+    rc = allocating([&] {
+        d->subs = new std::vector<sacx_ctx *>(subs, subs + (size_t)px * py);
+        d->buf = new std::vector<std::array<void *, 4>>((size_t)px * py);
+        d->nbr = new std::vector<std::array<int, 4>>((size_t)px * py);
+        d->bc = new std::vector<std::array<int, 4>>((size_t)px * py);
+        return SACX_OK;
+    });
+    if (rc) {
         sacx_domain_destroy(d);
-        return fail(SACX_EINVAL, "out of host memory");
+        return rc;
     }
     char *p = (char *)d_buf;
     d->cmax = (double *)p;
@@ -2966,7 +2981,7 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
         if (cap == hipStreamCaptureStatusNone) {
             const bool f64 = c0->grid.precision == SACX_FP64;
             if (!d->built || d->gen_built != gen) {
-                const int rc = f64 ? domain_build<double>(d, gen) : domain_build<float>(d, gen);
+                const int rc = allocating([&] { return f64 ? domain_build<double>(d, gen) : domain_build<float>(d, gen); });
                 if (rc) return rc;
             }
             return f64 ? domain_steps<double>(d, nsteps) : domain_steps<float>(d, nsteps);

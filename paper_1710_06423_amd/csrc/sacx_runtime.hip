@@ -316,6 +316,24 @@ bool stage_pairs(const sacx_ctx *c) {
     return c->L.nx >= 8 && c->L.ny >= 8;
 }
 
+// Rows per block of the two-stage kernel: 24 re-read and recompute less, 8 make
+// more blocks.  A compute unit holds one block of 24 rows or two of 8; the time
+// is the rounds of 24-row blocks against a round's time of 8-row blocks (0.72 of
+// the other in FP64, 0.84 in FP32) times the mean of their whole rounds and
+// their number in rounds (their last round ends early where it is part-filled).
+// Over sizes from 64^2 to 4000^2 this takes the slower one by more than 2 % at 10
+// of 178 in FP64 (12 % at 2000 x 500, at most 4 % elsewhere) and at 6 of 153 in
+// FP32 (at most 4 %).  us per step with 8 and with 24 rows, FP64:
+// 300 x 136 19, 27; 392 x 600 38, 32; 700 x 500 47, 55; 900 x 700 68, 67; 1000 x 800
+// 83, 88; 1501 x 997 148, 150; 2000^2 387, 377; 4000^2 1493, 1369; FP32: 300 x 136
+// 16, 19; 700 x 500 30, 32; 900 x 700 42, 39; 1501 x 997 78, 76; 4000^2 808, 728.
+int pair_rows_for(const Layout &L, bool fp64, int cus) {
+    const int64_t xt = (L.nx + 55) / 56, t8 = xt * ((L.ny + 7) / 8), t24 = xt * ((L.ny + 23) / 24);
+    const double r8 = 0.5 * ((double)((t8 + 2 * cus - 1) / (2 * cus)) + (double)t8 / (2 * cus));
+    const double r24 = (double)((t24 + cus - 1) / cus);
+    return r24 < (fp64 ? 0.72 : 0.84) * r8 ? 24 : 8;
+}
+
 int64_t box_tiles(const Layout &L, int rows) { return (int64_t)((L.nx + 57) / 58) * ((L.ny + rows - 1) / rows); }
 
 // the launch shape for the context's current settings: resident blocks from
@@ -328,11 +346,7 @@ void auto_rows(sacx_ctx *c) {
     const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
     c->box = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
-    // 24 rows per block re-read and recompute less, 8 make more blocks: even
-    // at 3 to 4 blocks of 8 rows per compute unit (700 x 500 FP64 60 us per
-    // step with 24, 54 with 8; 900 x 700 72 and 77)
-    const int64_t t8 = (int64_t)((c->L.nx + 55) / 56) * ((c->L.ny + 7) / 8);
-    c->pair_rows = t8 > 4 * (int64_t)(e == hipSuccess && cus > 0 ? cus : 256) ? 24 : 8;
+    c->pair_rows = pair_rows_for(c->L, fp64, e == hipSuccess && cus > 0 ? cus : 256);
     if (c->nt_auto) {
         c->nt = fp64 ? 128 : 256;
         double us = 0.0;

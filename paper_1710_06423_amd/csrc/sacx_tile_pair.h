@@ -21,11 +21,11 @@
 //
 // The arithmetic is that of the stage kernels, operation for operation.
 //
-// Measured, us per step (one stage per launch; this with 8 and with 24 rows
-// written per block): FP64 300 x 136 30.0, 22.3, 30.3; 900 x 700 105, 77, 72;
-// 1501 x 997 197, 154, 158; 4000^2 2524, 1538, 1400.  FP32 300 x 136 24.5,
-// 18.0, 22.0; 1501 x 997 114, 86, 82; 4000^2 1069, 863, 764.  Three rows per
-// wave took 128 registers and 100-156 B of scratch in FP64 (4000^2: 1928).
+// Measured, us per step, one stage per launch: FP64 300 x 136 30.0, 900 x 700
+// 105, 1501 x 997 197, 4000^2 2524; FP32 300 x 136 24.5, 1501 x 997 114, 4000^2
+// 1069.  This with 8 and with 24 rows written per block: FP64 19.0, 26.6; 68, 67;
+// 148, 150; 1493, 1369.  FP32 16.3, 18.8; 78, 76; 808, 728.  Three rows per wave
+// took 128 registers and 100-156 B of scratch in FP64 (4000^2: 1928).
 #pragma once
 
 #include "sacx_tile_box.h"

@@ -8,6 +8,6 @@ namespace sacx {
 template hipError_t launch_box<double>(int, bool, int, const StageArgs<double> &, hipStream_t);
 template hipError_t launch_batch_box<double>(const BatchArgs<double> &, int, int, bool, int, hipStream_t);
 template hipError_t launch_pair<double>(bool, bool, int, const StageArgs<double> &, hipStream_t);
-template hipError_t launch_tube_step<double>(bool, const TubeArgs<double> &, hipStream_t);
+template hipError_t launch_tube_step<double>(bool, int, const TubeArgs<double> &, hipStream_t);
 
 }  // namespace sacx

@@ -8,6 +8,6 @@ namespace sacx {
 template hipError_t launch_box<float>(int, bool, int, const StageArgs<float> &, hipStream_t);
 template hipError_t launch_batch_box<float>(const BatchArgs<float> &, int, int, bool, int, hipStream_t);
 template hipError_t launch_pair<float>(bool, bool, int, const StageArgs<float> &, hipStream_t);
-template hipError_t launch_tube_step<float>(bool, const TubeArgs<float> &, hipStream_t);
+template hipError_t launch_tube_step<float>(bool, int, const TubeArgs<float> &, hipStream_t);
 
 }  // namespace sacx

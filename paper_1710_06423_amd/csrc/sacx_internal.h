@@ -381,7 +381,7 @@ struct BatchArgs {
 template <typename real>
 hipError_t launch_stage(int stage, bool hd, bool bg, const StageArgs<real> &a, hipStream_t s);
 template <typename real>
-hipError_t launch_tube_step(bool hd, const TubeArgs<real> &a, hipStream_t s);
+hipError_t launch_tube_step(bool hd, int cus, const TubeArgs<real> &a, hipStream_t s);
 // stages 1 and 2 (from S = U to out1 and out2 = A) or, `last`, 3 and 4 (from S,
 // U and A to out1) of the scheme without hyper-diffusion; no background, no
 // exchange sides, at least 8 cells in both directions.  `second`: U is not the

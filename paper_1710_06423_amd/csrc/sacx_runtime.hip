@@ -103,6 +103,7 @@ struct sacx_ctx {
     int ty, nt;
     int split;         // FP64 hyper-diffusion tiles: two threads per column
     int box;           // rows of the box kernel's blocks (8, 16); 0: the marching kernels
+    int cus;                // compute units of the device
     int pair_rows;          // rows per block of the two-stage kernel
     bool nt_auto, ty_auto;  // columns / strip height chosen by auto_rows (until set explicitly)
     double dx, dy;
@@ -346,7 +347,8 @@ void auto_rows(sacx_ctx *c) {
     const bool hd = c->params.hd_on != 0, bg = c->grid.background_on != 0;
     c->box = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
-    c->pair_rows = pair_rows_for(c->L, fp64, e == hipSuccess && cus > 0 ? cus : 256);
+    c->cus = e == hipSuccess && cus > 0 ? cus : 256;
+    c->pair_rows = pair_rows_for(c->L, fp64, c->cus);
     if (c->nt_auto) {
         c->nt = fp64 ? 128 : 256;
         double us = 0.0;
@@ -1157,7 +1159,7 @@ int tube_step(sacx_ctx *c, void *const *from, void *const *to, bool second) {
     a.k = c->kc;
     a.sc = c->sc;
     a.second = second;
-    HIPCHK(launch_tube_step<real>(c->params.hd_on != 0, a, c->stream));
+    HIPCHK(launch_tube_step<real>(c->params.hd_on != 0, c->cus, a, c->stream));
     return SACX_OK;
 }
 

@@ -257,13 +257,13 @@ static hipError_t launch_tube_nt(bool hd, const TubeArgs<real> &a, hipStream_t s
 }
 
 // One wave per block (40 of its 64 cells written, no wait for other waves)
-// while that makes at most 256 blocks, a compute unit each: 800 cells 14.7 ->
+// while that makes at most a block per compute unit (of 256): 800 cells 14.7 ->
 // 13.4 us per step in FP64 and 12.5 -> 11.6 in FP32, 3000 15.4 -> 13.3 and
 // 12.9 -> 11.7.  Longer tubes recompute less with four: 200000 cells 38 us and
 // 27 us, against 42 and 33.
 template <typename real>
-hipError_t launch_tube_step(bool hd, const TubeArgs<real> &a, hipStream_t s) {
-    return a.L.nx <= 256 * (64 - 8 * G) ? launch_tube_nt<real, 64>(hd, a, s) : launch_tube_nt<real, 256>(hd, a, s);
+hipError_t launch_tube_step(bool hd, int cus, const TubeArgs<real> &a, hipStream_t s) {
+    return a.L.nx <= (int64_t)cus * (64 - 8 * G) ? launch_tube_nt<real, 64>(hd, a, s) : launch_tube_nt<real, 256>(hd, a, s);
 }
 
 }  // namespace sacx

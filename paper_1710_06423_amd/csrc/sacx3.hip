@@ -367,7 +367,7 @@ __device__ __forceinline__ void zflux(const Cell3 &c, double (&f)[7]) {
     f[6] = c.uz * c.by - c.bz * c.uy;
 }
 
-// rho, v, B of a plane's tile and apron, and its x and y fluxes
+// the x and y fluxes of a plane's tile and apron
 template <int TX, int TY>
 struct PlaneLds3 {
     double fx[7][TY + 4][TX + 4];   // x fluxes of rho, m_x, m_y, m_z, e, B_y, B_z

@@ -102,7 +102,7 @@ struct sacx_ctx {
     bool initialized;
     int ty, nt;
     int split;         // FP64 hyper-diffusion tiles: two threads per column
-    int box;           // rows of the box kernel's blocks (8, 16); 0: the marching kernels
+    int box;           // rows of the box kernel's blocks (4, 8, 16); 0: the marching kernels
     int cus;                // compute units of the device
     int pair_rows;          // rows per block of the two-stage kernel
     bool nt_auto, ty_auto;  // columns / strip height chosen by auto_rows (until set explicitly)
@@ -1470,7 +1470,7 @@ int sacx_set_boundaries(sacx_ctx *ctx, const int32_t bc[4]) {
     return SACX_OK;
 }
 
-// the step scalars of a new state, and the ghosts it needs once its fields are in place
+// the step scalars of a new state; finish_init fills the narrow ghosts once its fields are in place
 static void begin_init(sacx_ctx *ctx, double t0) {
     hipLaunchKernelGGL(k_reset_scalars, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t0);
 }

@@ -79,19 +79,9 @@ __device__ __forceinline__ double lane_right(double v) {
                             __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
 }
 
-// keeps the LDS reads of the next quantity out of the registers of this one
-// (FP64 with two rows per wave: without it 364-476 B of scratch per lane)
-template <typename real, int R>
-__device__ __forceinline__ void fence() {
-    if constexpr (sizeof(real) == 8 && R > 1) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
 // computes v here: the compiler would otherwise sink the arithmetic into the
-// block that uses it, four barriers later, and hold all its operands instead
-// (FP64 with two rows per wave: 364-476 B of scratch per lane)
+// block that uses it, up to four barriers later, and hold all its operands
+// instead
 template <typename real>
 __device__ __forceinline__ void settle(real &v) {
     asm volatile("" : "+v"(v));
@@ -245,7 +235,6 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
                     settle(K[k][5]);
                 }
             }
-            fence<real, R>();
         }
     }
     if (kc.grav) {
@@ -333,7 +322,6 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
             for (int q = 0; q < 5; ++q) {
                 gx[k][q] = xface(q, j0 + k, sf);
                 settle(gx[k][q]);
-                fence<real, R>();
             }
             g.gx[0][j0 + k + 1][t] = gx[k][QVY];
             g.gx[1][j0 + k + 1][t] = gx[k][QB];
@@ -360,7 +348,6 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
                 gy[k][q] = nu * (qw[k + 3] - qw[k + 2]) * idy;
                 settle(gy[k][q]);
             }
-            fence<real, R>();
         }
 #pragma unroll
         for (int k = 0; k < R; ++k) {
@@ -383,7 +370,6 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
                 if (q == QVX) g.gy[0][0][t] = gq;
                 else if (q == QB) g.gy[1][0][t] = gq;
                 else g.gb[q == QR ? 0 : (q == QE ? 1 : 2)][0][t] = gq;
-                fence<real, R>();
             }
         }
         __syncthreads();
@@ -464,7 +450,6 @@ __device__ __forceinline__ void stage_tile_box(const StageArgs<real> &a, int til
             for (int m = 0; m < 5; ++m) hyp[m] = hyn[m];
 #pragma unroll
             for (int f = 0; f < 6; ++f) settle(K[k][f]);
-            fence<real, R>();
         }
     }
 

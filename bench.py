@@ -436,6 +436,17 @@ def sub_surrogate(args, log_every=1000):
                          "generate_s": round(gen_s, 1), "iterations": 6000, "train_s": round(train_s, 1)}}
 
 
+def stage_accesses(n_stage, background):
+    """Values per cell that a profiled run's stage launches cannot do without:
+    12 field accesses x 6 fields per step of four stage launches; a background
+    adds its 4 fields, read once per launch.  A step of two launches, two
+    stages each (without hyper-diffusion), counts as stages 2 and 4 alone: 7
+    field accesses."""
+    single = n_stage[0]
+    pairs = n_stage[1] - single
+    return single * (12 * 6 + (16 if background else 0)) + pairs * 7 * 6
+
+
 def run_single(args):
     import torch
     import workloads as W
@@ -487,16 +498,12 @@ def run_single(args):
 
     cells = n * n
     value = cells * args.steps / (ms / 1e3) / 1e6
-    # dominant kernel: the fused stage kernel (four stage instantiations).
-    # algorithmic bytes: 12 field accesses x 6 fields x w per cell and step,
-    # i.e. 18 w bytes per cell per stage launch on average; a background adds
-    # its 4 fields, read once per stage launch.  Without hyper-diffusion a
-    # launch takes two stages: 7 field accesses per step.
+    # dominant kernel: the fused stage kernel (four stage instantiations)
     n_launch = sum(prof["n_stage"])
-    acc = 7 * 6 if n_launch == 2 * args.steps else 12 * 6 + (16 if strat else 0)
+    moved = stage_accesses(prof["n_stage"], strat) * w   # bytes per cell of the whole run
     stage_ms = sum(prof["ms_stage"])
     avg_launch_s = stage_ms / n_launch / 1e3
-    bytes_per_launch = acc * w * cells * args.steps / n_launch
+    bytes_per_launch = moved * cells / n_launch
     achieved = bytes_per_launch / avg_launch_s / 1e9
     per_stage = [prof["ms_stage"][k] / max(prof["n_stage"][k], 1) for k in range(4)]
     t_comp = stage_ms
@@ -511,7 +518,7 @@ def run_single(args):
         "nx": n, "ny": n, "precision": args.precision, "hyper_diffusion": hd, "cfl": 0.3,
         "halo": ("3-cell; x periodic, y open (zero-gradient), read in place by the stage kernels" if strat
                  else "3-cell, periodic, read in place by the stage kernels"),
-        "bytes_per_cell_update": acc * w,
+        "bytes_per_cell_update": moved // args.steps if moved % args.steps == 0 else round(moved / args.steps, 3),
     })
     if strat:
         out["config"].update({"background": "isothermal hydrostatic, scale height 0.25, uniform field (0.1, 0.4)",

@@ -870,11 +870,16 @@ struct ProfScope {
 struct SharedProfScope {
     const std::vector<sacx_ctx *> &ctx;
     int cls;
+    bool any = false;
     SharedProfScope(const std::vector<sacx_ctx *> &ctx_, int cls_) : ctx(ctx_), cls(cls_) {
-        for (sacx_ctx *c : ctx)
-            if (c->prof_on) c->prof_start = prof_event(c);
+        for (sacx_ctx *c : ctx) {
+            if (!c->prof_on) continue;
+            c->prof_start = prof_event(c);
+            any = true;
+        }
     }
     ~SharedProfScope() {
+        if (!any) return;
         double all = 0.0;
         for (const sacx_ctx *c : ctx) all += (double)c->L.nx * c->L.ny;
         for (sacx_ctx *c : ctx) {

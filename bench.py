@@ -20,7 +20,7 @@ them.
 
 Other modes (one JSON line each):
   --mode batch      64 mixed Brio-Wu / Orszag-Tang instances, one launch per
-                    stage for all of them (FP32, autotuned tiles), against the
+                    stage for all of them (FP32, as the tuner leaves them), against the
                     same instances run one at a time;
   --mode surrogate  the learned hyper-diffusion coefficient: trained on
                     solver-generated Orszag-Tang data, evaluated on an
@@ -279,7 +279,7 @@ def sub_fp32(args, ref_fields, t_ref):
 
 
 def sub_batch(args):
-    """64 mixed instances in one launch per stage (FP32, autotuned tiles),
+    """64 mixed instances in one launch per stage (FP32, as the tuner leaves them),
     100 steps; beside it the same instances run one at a time in FP64 (rate,
     and every instance's error against its FP64 run), and sampled instances
     against the FP64 oracle."""

@@ -326,7 +326,9 @@ int sacx_domain_destroy(sacx_domain *d);
  * stages per launch, tubes a whole step.  sacx_set_launch_auto returns to
  * that state (the tile kind of sacx_set_column_split stays).  Results do not
  * depend on the shape (bit-identical); only speed does.  Used by the tile
- * autotuner. */
+ * autotuner.  sacx_get_launch: the columns and rows of the blocks launched now
+ * (setting those by hand takes strips of that shape, not the automatic
+ * launches). */
 int sacx_set_launch(sacx_ctx *ctx, int32_t threads, int32_t rows);
 int sacx_set_launch_auto(sacx_ctx *ctx);
 int sacx_get_launch(const sacx_ctx *ctx, int32_t *threads, int32_t *rows);

@@ -182,7 +182,7 @@ struct TileLds {
 
 // One tile of the stage: columns [tx*TX, tx*TX + TX), rows of strip ty.
 // Called by the per-subdomain kernel (one tile per block) and by the batched
-// persistent kernel (tiles of many subdomains from a work queue).
+// kernels (tiles of many subdomains, from a list or a work queue).
 template <typename real, int NT, int STAGE, bool HD, bool BG, bool SUR = false>
 __device__ __forceinline__ void stage_tile(const StageArgs<real> &a, int tile_x, int tile_y, TileLds<real, NT> &lds) {
     constexpr int TX = NT - 2 * G;

@@ -95,6 +95,7 @@ struct sacx_ctx {
     size_t ws_bytes;
     DevScalars *sc;
     double *sums;      // 6 doubles
+    int *unfilled;     // 1 while the ghost cells of a loaded state are not filled
     double *partials;  // npart x 6
     int npart;
     void *U[NF], *B1[NF], *B2[NF], *A[NF], *BG[NBG];
@@ -127,8 +128,9 @@ struct sacx_ctx {
     int64_t sur_refreshes, sur_tiles_checked;
     // decomposed stepping (sacx_stage): the next RK4 stage, 0 between steps
     int stage_next;
-    // the ghost cells of U, and of the background, are still to be filled for
-    // the stage-level calls (the library's own steps read through the maps)
+    // the ghost cells of a loaded state, and of the background, may still have
+    // to be filled for the stage-level calls (the library's own steps read
+    // through the maps)
     bool ghosts_due, bg_due;
     // bumped by every change a batch's instance table copies (boundaries,
     // spacing), so that the batch rebuilds its table
@@ -491,13 +493,23 @@ __global__ void k_fill_y(FPtr<real> S, int nf, Layout L, int periodic, int skip,
     }
 }
 
-// every ghost cell of both directions in one launch, each read straight from
-// the cell it copies (corners included); for contexts whose every side is read through its map
+// The ghost cells of both directions in one launch, for any kinds of sides, as
+// fills of x over the interior rows and then of y over the padded width leave
+// them: beyond exchange sides they stay as they are.  With a flag only while
+// that is set: a captured graph that has this launch must not fill a loaded
+// state a second time, over what the caller completed between its replays.
 template <typename real>
-__global__ void k_fill_ghosts(FPtr<real> S, Layout L, SideMap mx, SideMap my) {
+__global__ void k_fill_ghosts(FPtr<real> S, Layout L, int4 bc, const int *unfilled) {
+    if (unfilled && !*unfilled) return;
     const int W = L.nx + 2 * G;
     const int64_t ny_part = (int64_t)2 * G * W, n = ny_part + (int64_t)2 * G * L.ny;
     const int f = blockIdx.y;
+    // the cell that one beyond the sides of a direction images (beyond an exchange side itself)
+    auto image = [](int i, int cells, int lo, int hi) {
+        const int kind = i < 0 ? lo : hi;
+        if ((i >= 0 && i < cells) || kind == SACX_EXCHANGE) return i;
+        return kind == SACX_PERIODIC ? (i % cells + cells) % cells : (i < 0 ? 0 : cells - 1);
+    };
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
         int i, j;
         if (k < ny_part) {
@@ -510,9 +522,14 @@ __global__ void k_fill_ghosts(FPtr<real> S, Layout L, SideMap mx, SideMap my) {
             j = (int)(k2 / (2 * G));
             i = g < G ? g - G : L.nx + g - G;
         }
-        S.p[f][eidx(L, i, j)] = S.p[f][eidx(L, mx.at(i), my.at(j))];
+        const int si = image(i, L.nx, bc.x, bc.y), sj = image(j, L.ny, bc.z, bc.w);
+        const bool outside = si < 0 || si >= L.nx;   // beyond an exchange side of x
+        if (sj < 0 || sj >= L.ny || (outside && sj == j)) continue;
+        S.p[f][eidx(L, i, j)] = S.p[f][eidx(L, si, sj)];
     }
 }
+
+__global__ void k_set_int(int *p, int v) { *p = v; }
 
 // caller arrays <-> internal storage
 template <typename T>
@@ -660,7 +677,8 @@ __global__ __launch_bounds__(256) void k_wavespeed(FPtr<real> U, Layout L, doubl
     block_speeds(cx, cy, bad, sc, 0);
 }
 
-__global__ void k_reset_scalars(DevScalars *sc, double t0) {
+__global__ void k_reset_scalars(DevScalars *sc, double t0, int *unfilled) {
+    *unfilled = 1;
     sc->t = t0;
     sc->dt = 0.0;
     sc->cmax = 0.0;
@@ -965,33 +983,35 @@ int fill_narrow(sacx_ctx *c, void *const *fields, int nf, bool gated) {
     return rc ? rc : fill_narrow(c, fields, nf, gated, 1);
 }
 
-// the ghost cells of the state U (the kernels of the learned coefficient and
-// the stage-level calls read them)
-template <typename real>
-int fill_halo_t(sacx_ctx *c) {
-    if (has_exchange(c) || narrow(c, 0) || narrow(c, 1)) {
-        fill_dir_t<real>(c, c->U, NF, false, 0);
-        fill_dir_t<real>(c, c->U, NF, false, 1);
-    } else {
-        const int64_t n = (int64_t)2 * G * (c->L.nx + 2 * G + c->L.ny);
-        hipLaunchKernelGGL(k_fill_ghosts<real>, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096), NF), dim3(256),
-                           0, c->stream, fptr<real>(c->U, NF), c->L, x_map(c), y_map(c));
-    }
+// the ghost cells of the state U (the kernels of the learned coefficient and a
+// first stage-level call read them); unfilled: only where that is set
+int fill_halo(sacx_ctx *c, const int *unfilled = nullptr) {
+    const int64_t n = (int64_t)2 * G * (c->L.nx + 2 * G + c->L.ny);
+    const dim3 g((unsigned)std::min<int64_t>((n + 255) / 256, 4096), NF);
+    const int4 bc = make_int4(c->bc[0], c->bc[1], c->bc[2], c->bc[3]);
+    if (c->grid.precision == SACX_FP64)
+        hipLaunchKernelGGL(k_fill_ghosts<double>, g, dim3(256), 0, c->stream, fptr<double>(c->U, NF), c->L, bc, unfilled);
+    else
+        hipLaunchKernelGGL(k_fill_ghosts<float>, g, dim3(256), 0, c->stream, fptr<float>(c->U, NF), c->L, bc, unfilled);
     HIPCHK(hipGetLastError());
     return SACX_OK;
 }
 
-int fill_halo(sacx_ctx *c) {
-    return c->grid.precision == SACX_FP64 ? fill_halo_t<double>(c) : fill_halo_t<float>(c);
-}
-
-// before a stage-level call: the ghost cells that a loaded state and a
-// background have are filled where no such call needed them yet
+// Before a stage-level call: the ghost cells that a loaded state and a
+// background have are filled where no such call needed them yet (filled by the
+// pass that loads the state, 8000^2 took 0.9 % longer and four subdomains of
+// 512^2 2.6 %).  A capture holds the launches too and does not count as done.
 int ghosts_ready(sacx_ctx *c) {
+    if (!c->ghosts_due && !c->bg_due) return SACX_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing(c->stream, &cap));
+    const bool captured = cap != hipStreamCaptureStatusNone;
     if (c->ghosts_due) {
-        const int rc = fill_halo(c);
+        const int rc = fill_halo(c, c->unfilled);
         if (rc) return rc;
-        c->ghosts_due = false;
+        hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, c->stream, c->unfilled, 0);
+        HIPCHK(hipGetLastError());
+        c->ghosts_due = captured;
     }
     if (c->bg_due) {
         for (int dir = 0; dir < 2; ++dir) {
@@ -999,7 +1019,7 @@ int ghosts_ready(sacx_ctx *c) {
             else fill_dir_t<float>(c, c->BG, NBG, false, dir);
         }
         HIPCHK(hipGetLastError());
-        c->bg_due = false;
+        c->bg_due = captured;
     }
     return SACX_OK;
 }
@@ -1294,6 +1314,7 @@ int sacx_create(const sacx_grid *grid, const sacx_params *params, void *d_ws, si
     c->ws_bytes = ws_bytes;
     c->sc = (DevScalars *)(c->ws + P.off_sc);
     c->sums = (double *)(c->ws + P.off_sums);
+    c->unfilled = (int *)(c->sums + NF);
     c->partials = (double *)(c->ws + P.off_part);
     c->npart = (int)std::min<int64_t>(kPartials, grid->ny);
     char *st = c->ws + P.off_state;
@@ -1477,7 +1498,7 @@ int sacx_set_boundaries(sacx_ctx *ctx, const int32_t bc[4]) {
 
 // the step scalars of a new state; finish_init fills the narrow ghosts once its fields are in place
 static void begin_init(sacx_ctx *ctx, double t0) {
-    hipLaunchKernelGGL(k_reset_scalars, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t0);
+    hipLaunchKernelGGL(k_reset_scalars, dim3(1), dim3(1), 0, ctx->stream, ctx->sc, t0, ctx->unfilled);
 }
 
 static int finish_init(sacx_ctx *ctx) {
@@ -1633,7 +1654,6 @@ int sacx_advance(sacx_ctx *ctx, int32_t nsteps, double t_end, int32_t *steps_don
         }
     }
     if (nsteps > 0) {
-        ctx->ghosts_due = true;
         ProfScope ps(ctx, 5);
         hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, ctx->stream, ctx->sc);
         HIPCHK(hipGetLastError());
@@ -2544,7 +2564,6 @@ int sacx_batch_advance(sacx_batch *b, int32_t nsteps, int32_t sync) {
         if (c->sur_on) return fail(SACX_EUNSUP, "a batched instance has a learned coefficient set: the batch uses the plain one");
         gsum += c->gen;
     }
-    for (sacx_ctx *c : *b->ctx) c->ghosts_due = c->ghosts_due || nsteps > 0;
     DeviceGuard dg(b->device);
     if (!dg.ok) return fail(SACX_EDEVICE, "cannot select the batch device");
     // One launch per stage over the tiles of every instance, against the
@@ -2991,8 +3010,7 @@ int sacx_domain_advance(sacx_domain *d, int32_t nsteps) {
     // tables that a later call may replace.
     bool together = !d->mixed;
     unsigned long long gen = 0;
-    for (sacx_ctx *c : *d->subs) {
-        c->ghosts_due = c->ghosts_due || nsteps > 0;
+    for (const sacx_ctx *c : *d->subs) {
         together = together && !c->grid.background_on && !narrow(c, 0) && (c->L.ny == 1 || !narrow(c, 1));
         gen += c->gen;
     }

@@ -82,11 +82,11 @@ def test_strips_on_sides_of_any_kind(kind, precision, hd, shape, xc, yc):
         s.close()
 
 
-@pytest.mark.parametrize("bc", [(0, 0, 0, 0), (1, 1, 0, 0), (1, 1, 1, 1)])
-@pytest.mark.parametrize("shape", [(60, 44), (300, 2), (2, 50)])
+@pytest.mark.parametrize("bc", [(0, 0, 0, 0), (1, 1, 0, 0), (0, 0, 1, 1), (1, 1, 1, 1)])
+@pytest.mark.parametrize("shape", [(60, 44), (300, 2), (2, 50), (3, 4), (5, 3), (257, 9)])
 def test_a_loaded_state_has_its_ghosts(bc, shape):
-    """Stage 1 and the strips' corners right after the state is loaded, and
-    after steps by sacx_advance, without a fill by the caller."""
+    """Stage 1 and the strips' corners right after the state is loaded, the
+    second time over steps taken before, without a fill by the caller."""
     torch = _torch()
     from paper_1710_06423_amd import Solver
     prob = W.random_smooth(*shape, seed=4, bc=bc)
@@ -185,3 +185,83 @@ def test_neighbours_of_other_kinds(precision, hd, kinds):
     assert lib.sacx_domain_destroy(d) == sacx.OK
     for r in ours + theirs:
         r[0].close()
+
+
+@pytest.mark.parametrize("kind,shape", [("orszag_tang", (60, 44)), ("brio_wu", (90, 1)), ("brio_wu", (50, 7)),
+                                        ("brio_wu", (1, 70))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_a_generated_state_has_its_ghosts(kind, shape, precision):
+    torch = _torch()
+    from paper_1710_06423_amd import Solver, sacx
+    print(f"case: {kind} {shape} precision {precision}", flush=True)
+    which = sacx.PROBLEM_ORSZAG_TANG if kind == "orszag_tang" else sacx.PROBLEM_BRIO_WU
+    runs = []
+    for by_stage in (False, True):
+        s = Solver(sacx.make_grid(*shape, 0.0, 1.0, 0.0, 1.0, precision, False), sacx.make_params(2.0))
+        s.init_problem(which)
+        if by_stage:
+            for st in range(4):
+                if st:
+                    s.fill_boundaries(0)
+                    s.fill_boundaries(1)
+                s.stage(None)
+        else:
+            s.advance(1)
+        runs.append(s.read_fields())
+        s.close()
+    assert torch.equal(*runs)
+
+
+@pytest.mark.parametrize("kind", [PERIODIC, OPEN])
+def test_a_captured_step_keeps_the_callers_ghosts(kind):
+    """A step captured as the first stage-level calls, the strips of its later
+    stages handed over inside, those of its first stage by the caller between
+    the replays; on open sides that is not what a fill would put there.  On
+    periodic ones the first replay reads the loaded state's own ghost cells."""
+    torch = _torch()
+    from paper_1710_06423_amd import Solver
+    from paper_1710_06423_amd.sacx import StepGraph
+    print(f"case: captured step, sides {kind}", flush=True)
+    prob = W.random_smooth(60, 44, seed=8)
+    one = Solver.from_problem(prob)
+    s = Solver.from_problem(prob, stream=torch.cuda.Stream())
+    if kind == OPEN:
+        s.set_boundaries((OPEN,) * 4)
+    strips = [s.halo_buffer(k) for k in range(4)]
+    torch.cuda.synchronize()
+
+    def hand_over():
+        for side in (0, 2):
+            s.halo_pack(side, strips[side])
+            s.halo_pack(side + 1, strips[side + 1])
+            s.halo_unpack(side, strips[side + 1])
+            s.halo_unpack(side + 1, strips[side])
+
+    def step():
+        s.stage(None)
+        for _ in range(3):
+            hand_over()
+            s.stage(None)
+
+    g = StepGraph(step, s.stream)
+    for k in range(4):
+        if k or kind == OPEN:
+            with torch.cuda.stream(s.stream):
+                hand_over()
+        g.replay()
+        torch.cuda.synchronize()
+        one.advance(1)
+        assert torch.equal(s.read_fields(), one.read_fields()), k
+    # a state loaded again is filled again
+    f = torch.stack([torch.from_numpy(prob.fields[k].copy()) for k in W.FIELDS]).cuda()
+    one.init_state(f)
+    s.init_state(f)
+    if kind == OPEN:
+        with torch.cuda.stream(s.stream):
+            hand_over()
+    g.replay()
+    torch.cuda.synchronize()
+    one.advance(1)
+    assert torch.equal(s.read_fields(), one.read_fields())
+    s.close()
+    one.close()
